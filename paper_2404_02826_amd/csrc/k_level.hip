@@ -1268,35 +1268,46 @@ __device__ inline void fuse_bases(const uint32_t (&t)[K], uint32_t (&b)[K], uint
     for (int k = 0; k < K; ++k) b[k] += (uint32_t)w < wv ? xs[w][k] : 0u;
 }
 
-// Radix select over the node's codes held in registers, for one or two
-// member groups at once: group g's member of rank rank[g] among the members
-// flagged in the lanes' bit masks m[g] (bit i: the lane's i-th member),
-// ordered by (code, member order).  Widest digit first, at most 8 bits per
-// pass, over the code range of all flagged members; pass p counts group g
-// into bins [512 (p & 1) + 256 g, ... + 256) and the scanning wavefront
-// posts its finds in red[2 W + 4 (p & 1) ...], so that a pass needs no
-// barrier after its reads: the next pass uses the other half, and the one
-// after it comes after the next pass's barriers.  Returns each group's code
-// in v[g] and, in rank[g], how many members equal to it precede it.  The
-// bins are zero on entry and on return (the scanning wavefront clears what
-// it read); red[0, 2 W) (the code range) is rewritten only after a later
-// barrier of the caller.
+// Ranges (mn[a], mx[a]) of the node's codes along two axes, from the lanes'
+// ranges (lo, hi), in one exchange over the node's wavefronts.  red holds
+// 4 W words, rewritten only after a later barrier of the caller.
+template <int W>
+__device__ inline void fuse_ranges(const uint32_t (&lo)[2], const uint32_t (&hi)[2], uint32_t (&mn)[2],
+                                   uint32_t (&mx)[2], uint32_t* red) {
+#pragma unroll
+  for (int a = 0; a < 2; ++a) mn[a] = wave_min_dpp(lo[a]), mx[a] = wave_max_dpp(hi[a]);
+  if (W == 1) return;
+  const uint32_t wv = threadIdx.x >> 6;
+  if ((threadIdx.x & 63) == 0)
+#pragma unroll
+    for (int a = 0; a < 2; ++a) red[2 * a * W + wv] = mn[a], red[(2 * a + 1) * W + wv] = mx[a];
+  __syncthreads();
+#pragma unroll
+  for (int a = 0; a < 2; ++a) {
+    mn[a] = red[2 * a * W], mx[a] = red[(2 * a + 1) * W];
+#pragma unroll
+    for (int w = 1; w < W; ++w)
+      mn[a] = umin32(mn[a], red[2 * a * W + w]), mx[a] = umax32(mx[a], red[(2 * a + 1) * W + w]);
+  }
+}
+
+// Radix select over the node's codes held in registers (all of them in
+// [mn, mx]), for one or two member groups at once: group g's member of rank
+// rank[g] among the members flagged in the lanes' bit masks m[g] (bit i: the
+// lane's i-th member), ordered by (code, member order).  Widest digit first,
+// at most 8 bits per pass, over the code range; pass p counts group g into
+// bins [512 (p & 1) + 256 g, ... + 256) and the scanning wavefront posts its
+// finds in red[4 (p & 1) ...], so that a pass needs no barrier after its
+// reads: the next pass uses the other half, and the one after it comes after
+// the next pass's barriers.  Returns each group's code in v[g] and, in
+// rank[g], how many members equal to it precede it.  The bins are zero on
+// entry and on return (the scanning wavefront clears what it read).
 template <int R, int W, int NG, typename Q>
-__device__ void reg_select(const Q& q, const uint32_t (&m)[NG], uint32_t (&rank)[NG],
-                           uint32_t* bins, uint32_t* red, uint32_t (&v)[NG]) {
+__device__ void reg_select(const Q& q, const uint32_t (&m)[NG], bool live, uint32_t mn, uint32_t mx,
+                           uint32_t (&rank)[NG], uint32_t* bins, uint32_t* red, uint32_t (&v)[NG]) {
   static_assert(NG == 1 || NG == 2, "one or two groups");
   const uint32_t lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
   const uint32_t all = NG == 1 ? m[0] : (m[0] | m[NG - 1]);
-  uint32_t lo, hi;
-  q.minmax(all, &lo, &hi);
-  uint32_t mn = wave_min_dpp(lo), mx = wave_max_dpp(hi);
-  if (W > 1) {
-    if (lane == 0) red[wv] = mn, red[W + wv] = mx;
-    __syncthreads();
-    mn = red[0], mx = red[W];
-#pragma unroll
-    for (int w = 1; w < W; ++w) mn = umin32(mn, red[w]), mx = umax32(mx, red[W + w]);
-  }
   const uint32_t Gs = mx > mn ? bitlen32(mx - mn) : 0u;
   uint32_t prefix[NG];
 #pragma unroll
@@ -1307,10 +1318,11 @@ __device__ void reg_select(const Q& q, const uint32_t (&m)[NG], uint32_t (&rank)
     const uint32_t hs = Gs - used;
     used += w;
     uint32_t* const bn = bins + 512 * half;
-    uint32_t* const rd = red + 2 * W + 4 * half;
+    uint32_t* const rd = red + 4 * half;
     half ^= 1;
     const uint32_t sh = Gs - used, mask = (1u << w) - 1;
-    if (hs == Gs) {  // first pass: every flagged member is a candidate
+    if (!live) {  // no member in the lane
+    } else if (hs == Gs) {  // first pass: every flagged member is a candidate
 #pragma unroll
       for (int i = 0; i < R; ++i) {
         const uint32_t k = q[i] - mn;
@@ -1384,9 +1396,8 @@ __device__ inline uint32_t wave_excl(uint32_t x, uint32_t* tot) {
   return incl - x;
 }
 
-// R consecutive elements [p0, p0 + R) of one array (those below s; fill
-// beyond) held by a lane, loaded with 16-byte loads when the array is
-// 16-byte aligned and the run is whole; 16-bit codes two to a register.
+// R consecutive slots [p0, p0 + R) of one array held by a lane, 16-bit codes
+// two to a register; slots outside [lo, hi) hold a fill value.
 template <typename T, int R>
 struct RegRun {
   static constexpr int V = 16 / sizeof(T), PER = 4 / sizeof(T);
@@ -1395,11 +1406,10 @@ struct RegRun {
   __device__ __forceinline__ uint32_t operator[](int i) const {
     return PER == 1 ? w[i] : ((i & 1) ? w[i >> 1] >> 16 : w[i >> 1] & 0xffffu);
   }
-  // smallest and largest of the elements flagged in m (bit i: element i);
-  // 16-bit codes of a lane whose every element is flagged go two at a time
-  __device__ __forceinline__ void minmax(uint32_t m, uint32_t* lo, uint32_t* hi) const {
+  // smallest and largest of the lane's slots; 16-bit codes two at a time
+  __device__ __forceinline__ void minmax(uint32_t* lo, uint32_t* hi) const {
     uint32_t a = 0xffffffffu, b = 0;
-    if (PER == 2 && m == (1u << R) - 1u) {
+    if (PER == 2) {
       typedef unsigned short u16x2 __attribute__((ext_vector_type(2)));
       u16x2 a2 = {0xffff, 0xffff}, b2 = {0, 0};
 #pragma unroll
@@ -1412,19 +1422,41 @@ struct RegRun {
       b = umax32(b2.x, b2.y);
     } else {
 #pragma unroll
-      for (int i = 0; i < R; ++i)
-        if ((m >> i) & 1u) a = umin32(a, (*this)[i]), b = umax32(b, (*this)[i]);
+      for (int i = 0; i < R; ++i) a = umin32(a, (*this)[i]), b = umax32(b, (*this)[i]);
     }
     *lo = a;
     *hi = b;
   }
-  __device__ __forceinline__ void load(const T* X, uint32_t p0, uint32_t s, bool vec, T fill) {
-    if (vec && p0 + R <= s) {
+  // the slots below lo and from hi on take the values below and above
+  __device__ __forceinline__ void patch(uint32_t p0, uint32_t lo, uint32_t hi, uint32_t below,
+                                        uint32_t above) {
+    if (p0 >= lo && p0 + R <= hi) return;
+#pragma unroll
+    for (int k = 0; k < R / PER; ++k) {
+      uint32_t x = 0;
+#pragma unroll
+      for (int h = 0; h < PER; ++h) {
+        const uint32_t p = p0 + (uint32_t)(k * PER + h);
+        x |= (p < lo ? below : p < hi ? (*this)[k * PER + h] : above) << (16 * h);
+      }
+      w[k] = x;
+    }
+  }
+  // X: slot 0.  vec: X is 16-byte aligned, and every 16 bytes from X on that
+  // hold a slot of [lo, hi) are readable; then whole vectors are loaded, also
+  // where the run begins before lo or ends after hi (a run of single 2-byte
+  // loads per lane touches as many cache lines as 16 vector loads).
+  // FULL: every slot is inside [lo, hi) and X is aligned.
+  template <bool FULL>
+  __device__ __forceinline__ void load(const T* X, uint32_t p0, uint32_t lo, uint32_t hi, bool vec, T fill) {
+    if (FULL || vec) {
 #pragma unroll
       for (int b = 0; b < R / V; ++b) {
-        const uint4 u = *(const uint4*)(X + p0 + b * V);
+        uint4 u = make_uint4(0, 0, 0, 0);
+        if (FULL || p0 + b * V < hi) u = *(const uint4*)(X + p0 + b * V);
         w[4 * b + 0] = u.x, w[4 * b + 1] = u.y, w[4 * b + 2] = u.z, w[4 * b + 3] = u.w;
       }
+      if (!FULL) patch(p0, lo, hi, (uint32_t)fill, (uint32_t)fill);
     } else {
 #pragma unroll
       for (int k = 0; k < R / PER; ++k) {
@@ -1432,7 +1464,7 @@ struct RegRun {
 #pragma unroll
         for (int h = 0; h < PER; ++h) {
           const uint32_t p = p0 + (uint32_t)(k * PER + h);
-          x |= (uint32_t)(p < s ? X[p] : fill) << (16 * h);
+          x |= (uint32_t)(p >= lo && p < hi ? X[p] : fill) << (16 * h);
         }
         w[k] = x;
       }
@@ -1440,14 +1472,14 @@ struct RegRun {
   }
 };
 
-// Stores E consecutive values [e0, e0 + E) (those below s) to X, with
+// Stores the slots [e0, e0 + E) that lie in [lo, hi) to X (slot 0), with
 // 16-byte stores when X is 16-byte aligned and the run is whole; get(k)
 // gives the value of slot e0 + k.
 template <int E, typename T, typename F>
-__device__ inline void store_run(T* X, uint32_t e0, uint32_t s, bool vec, F&& get) {
+__device__ inline void store_run(T* X, uint32_t e0, uint32_t lo, uint32_t hi, bool vec, F&& get) {
   constexpr int V = 16 / sizeof(T);
   static_assert(E % V == 0, "whole vectors");
-  if (vec && e0 + E <= s) {
+  if (vec && e0 >= lo && e0 + E <= hi) {
 #pragma unroll
     for (int b = 0; b < E / V; ++b) {
       union {
@@ -1461,7 +1493,7 @@ __device__ inline void store_run(T* X, uint32_t e0, uint32_t s, bool vec, F&& ge
   } else {
 #pragma unroll
     for (int k = 0; k < E; ++k)
-      if (e0 + k < s) X[e0 + k] = (T)get((uint32_t)k);
+      if (e0 + k >= lo && e0 + k < hi) X[e0 + k] = (T)get((uint32_t)k);
   }
 }
 
@@ -1490,40 +1522,54 @@ __device__ __forceinline__ void reg_fence(RegRun<T, R>& q) {
 // (a value is consumed before the barrier, so its load has returned), and no
 // other wavefront or block touches the node.  `lds` holds the select bins,
 // then the staged node (three 16-bit arrays with 16-bit codes, else one
-// 32-bit array at a time).  Every lane holds R members: those past the
-// node's end read as the top code of their axis, so they order after every
-// member of the node (a code as large or larger, a later member) and leave
-// each median, side and slot of the node's members as it is; they all fall
-// in the last grandchild, at slots s and up, which are never written back.
-template <typename KT, bool TRACK, int W>
-__device__ __forceinline__ void level_fused_body(uint32_t depth, const SetDesc& S, DevParams* P,
-                                                 uint64_t j, uint8_t* keys, uint32_t* idx,
+// 32-bit array at a time).
+// Member slots: a node of any start is read and written with 16-byte loads
+// and stores.  Slot 0 is the 16-byte boundary at or before the node's first
+// code, so the members take the slots [off, off + s), off < 16 bytes of
+// codes; every lane holds R slots, and those outside the node read as the
+// axis's smallest code of the node before it and its largest after it.  They
+// order before or after every member of the node (a code as small, an
+// earlier slot; a code as large, a later one), so with every rank counted
+// from slot 0 they leave each median and side of the node's members as it
+// is; they fall at the front of the first grandchild and at the end of the
+// last, keep their slots and are never written back.  Element loads and
+// stores, before, made nodes off a 16-byte boundary cost 2-3 times as much
+// (all nodes but those of power-of-two sets): the three pairs of the 2-D set
+// of 13,077,313 took 512 us and take 200, those of 33,554,467 FP64 particles
+// 1,719 and 834.  What bounds the pass is instruction issue and, for W = 16,
+// its barriers.  A node too large for off + s slots -- only just below the
+// capacity -- keeps off = 0 and single loads.
+template <typename KT, bool TRACK, int W, bool FULL>
+__device__ __forceinline__ void level_fused_node(uint32_t depth, const SetDesc& S, DevParams* P,
+                                                 uint64_t st, uint32_t sz, uint8_t* keys, uint32_t* idx,
                                                  uint32_t* lds, uint32_t* red, uint32_t (*xs)[W][4]) {
   constexpr int R = kFuseRows;
   const uint32_t lane = threadIdx.x & 63;
   const uint32_t wv = W == 1 ? 0u : (uint32_t)__builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
-  uint64_t st, sz64;
-  node_span(S.n, depth, j, &st, &sz64);
-  if (sz64 > (uint64_t)W * kFuseNode || sz64 <= S.r) {  // launch plan violated: never expected
-    if (threadIdx.x == 0) check_failed(P, kChkFusedIdx);
-    return;
-  }
-  const uint32_t s = (uint32_t)sz64;
+  const uint32_t s = FULL ? W * (uint32_t)kFuseNode : sz;
   const uint32_t dims = S.dims, d = depth % dims;
   const uint32_t a1 = (d + 1) % dims, a2 = dims > 2 ? (d + 2) % dims : d;
   const uint64_t kst = S.kst;
-  KT* X0 = (KT*)keys + st + (uint64_t)d * kst;
-  KT* X1 = (KT*)keys + st + (uint64_t)a1 * kst;
-  KT* X2 = (KT*)keys + st + (uint64_t)a2 * kst;
-  uint32_t* I = idx ? idx + st : nullptr;
-  // the code arrays are 64-element aligned per axis, so one test covers all
-  const bool vk = (st % (16 / sizeof(KT))) == 0, vi = (st % 4) == 0;
-  const uint32_t p0 = wv * (uint32_t)kFuseNode + lane * R;  // the lane's first member
+  // the code arrays are 64-element aligned per axis (kst is their padded
+  // length, and the buffers start at 256 bytes), so one offset serves all, and
+  // whole 16-byte reads stay inside an axis; a 16-byte boundary of the codes
+  // is one of the indices too
+  constexpr uint32_t V = 16 / sizeof(KT), C = W * kFuseNode;
+  const uint32_t mis = FULL ? 0u : (uint32_t)(st % V);
+  const uint32_t off = mis + s <= C ? mis : 0u;
+  const bool vec = mis == off;
+  const uint32_t hi = off + s;
+  KT* X0 = (KT*)keys + (st - off) + (uint64_t)d * kst;
+  KT* X1 = (KT*)keys + (st - off) + (uint64_t)a1 * kst;
+  KT* X2 = (KT*)keys + (st - off) + (uint64_t)a2 * kst;
+  uint32_t* I = idx ? idx + (st - off) : nullptr;
+  const bool vi = FULL || ((st - off) % 4) == 0;
+  const uint32_t p0 = wv * (uint32_t)kFuseNode + lane * R;  // the lane's first slot
   RegRun<KT, R> q0, q1;  // the split axis and the next one (the third axis, and
                          // the source indices, are read when they are staged)
-  auto top = [](uint32_t g) { return (KT)(g >= 32 ? 0xffffffffu : (1u << g) - 1u); };
-  q0.load(X0, p0, s, vk, top(P->G[d]));
-  q1.load(X1, p0, s, vk, top(P->G[a1]));
+  // until the node's ranges are known the other slots hold its first codes
+  q0.template load<FULL>(X0, p0, off, hi, vec, FULL ? (KT)0 : X0[off]);
+  q1.template load<FULL>(X1, p0, off, hi, vec, FULL ? (KT)0 : X1[off]);
   constexpr uint32_t all = (1u << R) - 1u;  // member flags: every member of the lane
   // between phases: the codes are taken up again from their packed
   // registers instead of holding unpacked copies across the phases
@@ -1534,13 +1580,29 @@ __device__ __forceinline__ void level_fused_body(uint32_t depth, const SetDesc& 
   __builtin_amdgcn_s_waitcnt(0);
   fuse_sync<W>();
 
+  uint32_t mn[2], mx[2];
+  {
+    uint32_t lo2[2], hi2[2];
+    q0.minmax(&lo2[0], &hi2[0]);
+    q1.minmax(&lo2[1], &hi2[1]);
+    fuse_ranges<W>(lo2, hi2, mn, mx, red);
+  }
+  if (!FULL) {
+    q0.patch(p0, off, hi, mn[0], mx[0]);
+    q1.patch(p0, off, hi, mn[1], mx[1]);
+  }
+  red += 4 * W;  // the selects' finds
+  // slots past the node order after every rank that is selected, so lanes of
+  // such slots alone count nothing (all in one bin, they would only collide)
+  const bool live = FULL || p0 < hi;
+
   // ---- level k: the node's median along d; each member's side (members
   // equal to the median go left while fewer than jeq of them did)
   uint32_t v, jeq;
   {
     const uint32_t m1[1] = {all};
-    uint32_t rk[1] = {s >> 1}, vv[1];
-    reg_select<R, W, 1>(q0, m1, rk, lds, red, vv);
+    uint32_t rk[1] = {off + (s >> 1)}, vv[1];
+    reg_select<R, W, 1>(q0, m1, live, mn[0], mx[0], rk, lds, red, vv);
     v = vv[0], jeq = rk[0];
   }
   fence();
@@ -1564,12 +1626,14 @@ __device__ __forceinline__ void level_fused_body(uint32_t depth, const SetDesc& 
   // ---- level k + 1: both children's medians along the next axis, then each
   // member's side within its child (counts of the two children packed in
   // the 16-bit halves of one word: they stay below 2^16)
-  const uint32_t sL = s >> 1, sR = s - sL, hL = sL >> 1, hR = sR >> 1;
+  // (the slots before the node lie in the first grandchild: its size and the
+  // left child's count them)
+  const uint32_t sL = off + (s >> 1), sR = s - (s >> 1), hL = off + (s >> 2), hR = sR >> 1;
   uint32_t vL, vR, jL, jR;
   {
     const uint32_t m2[2] = {left, right};
     uint32_t rk[2] = {hL, hR}, vv[2];
-    reg_select<R, W, 2>(q1, m2, rk, lds, red, vv);
+    reg_select<R, W, 2>(q1, m2, live, mn[1], mx[1], rk, lds, red, vv);
     vL = vv[0], vR = vv[1], jL = rk[0], jR = rk[1];
   }
   fence();
@@ -1587,7 +1651,7 @@ __device__ __forceinline__ void level_fused_body(uint32_t depth, const SetDesc& 
   }
   run2 += b2[0] | (b2[1] << 16);
   // grandchild of each member: g = 0 LL [0, hL), 1 LR [hL, sL), 2 RL
-  // [sL, sL + hR), 3 RR [sL + hR, s), two bits per member in gm
+  // [sL, sL + hR), 3 RR [sL + hR, hi), two bits per member in gm
   uint32_t gm = 0;
 #pragma unroll
   for (int i = 0; i < R; ++i) {
@@ -1614,12 +1678,11 @@ __device__ __forceinline__ void level_fused_body(uint32_t depth, const SetDesc& 
     fuse_bases<W, 4>(tt, b4, xs[2]);
   }
   // C member slots: every grandchild must count its own size (the last also
-  // the members past the node's end), then each member's slot lies inside
+  // the slots past the node's end), then each member's slot lies inside
   // its grandchild (the last wavefront sees the node totals)
-  constexpr uint32_t C = W * kFuseNode;
   if (wv == W - 1) {
     const uint32_t tt[4] = {tA & 0xffffu, tA >> 16, tB & 0xffffu, tB >> 16};
-    const uint32_t gs[4] = {hL, sL - hL, hR, sR - hR + (C - s)};
+    const uint32_t gs[4] = {hL, sL - hL, hR, sR - hR + (C - hi)};
     bool bad = false;
 #pragma unroll
     for (int g = 0; g < 4; ++g) bad |= b4[g] + tt[g] != gs[g];
@@ -1642,7 +1705,7 @@ __device__ __forceinline__ void level_fused_body(uint32_t depth, const SetDesc& 
   const uint32_t tid = W == 1 ? lane : threadIdx.x;
   if constexpr (sizeof(KT) == 2) {
     RegRun<KT, R> q2;
-    q2.load(X2, p0, s, vk, 0);  // no store to the node before the barrier below
+    q2.template load<FULL>(X2, p0, off, hi, vec, 0);  // no store to the node before the barrier below
     // one array of C 16-bit slots per axis, copied out 16 bytes at a time
     uint16_t* sg = (uint16_t*)lds;
 #pragma unroll
@@ -1653,15 +1716,15 @@ __device__ __forceinline__ void level_fused_body(uint32_t depth, const SetDesc& 
     }
     fuse_sync<W>();
     auto out = [&](KT* X, const uint16_t* g, uint32_t e0) {
-      if (vk && e0 + E <= s) {
+      if (FULL || (vec && e0 >= off && e0 + E <= hi)) {
         *(uint4*)(X + e0) = *(const uint4*)(g + e0);
       } else {
 #pragma unroll
         for (uint32_t k = 0; k < E; ++k)
-          if (e0 + k < s) X[e0 + k] = g[e0 + k];
+          if (e0 + k >= off && e0 + k < hi) X[e0 + k] = g[e0 + k];
       }
     };
-    for (uint32_t e0 = tid * E; e0 < s; e0 += T * E) {
+    for (uint32_t e0 = tid * E; e0 < hi; e0 += T * E) {
       out(X0, sg, e0);
       out(X1, sg + C, e0);
       if (dims > 2) out(X2, sg + 2 * C, e0);
@@ -1670,32 +1733,51 @@ __device__ __forceinline__ void level_fused_body(uint32_t depth, const SetDesc& 
   // 32-bit codes and source indices: one array at a time, each read from
   // the node before any wavefront stores to it
   uint32_t* stg32 = lds;
-  auto pass32 = [&](auto* X, const auto& val, bool vec) {
+  auto pass32 = [&](auto* X, const auto& val, bool v16) {
 #pragma unroll
     for (int i = 0; i < R; ++i) stg32[dst[i]] = val[i];
     fuse_sync<W>();
-    for (uint32_t e0 = tid * E; e0 < s; e0 += T * E)
-      store_run<E>(X, e0, s, vec, [&](uint32_t k) { return stg32[e0 + k]; });
+    for (uint32_t e0 = tid * E; e0 < hi; e0 += T * E)
+      store_run<E>(X, e0, off, hi, FULL || v16, [&](uint32_t k) { return stg32[e0 + k]; });
     fuse_sync<W>();  // the next array reuses the staging area
   };
   if constexpr (sizeof(KT) == 4) {
     fuse_sync<W>();
-    pass32(X0, q0, vk);
-    pass32(X1, q1, vk);
+    pass32(X0, q0, vec);
+    pass32(X1, q1, vec);
     if (dims > 2) {
       RegRun<KT, R> q2;
-      q2.load(X2, p0, s, vk, 0);
-      pass32(X2, q2, vk);
+      q2.template load<FULL>(X2, p0, off, hi, vec, 0);
+      pass32(X2, q2, vec);
     }
   }
   if constexpr (TRACK) {
     if (I) {
       fuse_sync<W>();
       RegRun<uint32_t, R> ix;
-      ix.load(I, p0, s, vi, 0);
+      ix.template load<FULL>(I, p0, off, hi, vi, 0);
       pass32(I, ix, vi);
     }
   }
+}
+
+// FULL: nodes of exactly W kFuseNode members that start on a 16-byte boundary
+// (power-of-two sets) take a body without the slots around the node (fluid
+// 2^27: the three pairs 1.40 ms against 1.54 in the general body).
+template <typename KT, bool TRACK, int W>
+__device__ __forceinline__ void level_fused_body(uint32_t depth, const SetDesc& S, DevParams* P,
+                                                 uint64_t j, uint8_t* keys, uint32_t* idx,
+                                                 uint32_t* lds, uint32_t* red, uint32_t (*xs)[W][4]) {
+  uint64_t st, sz;
+  node_span(S.n, depth, j, &st, &sz);
+  if (sz > (uint64_t)W * kFuseNode || sz <= S.r) {  // launch plan violated: never expected
+    if (threadIdx.x == 0) check_failed(P, kChkFusedIdx);
+    return;
+  }
+  if (sz == (uint64_t)W * kFuseNode && (st & 7) == 0)
+    level_fused_node<KT, TRACK, W, true>(depth, S, P, st, (uint32_t)sz, keys, idx, lds, red, xs);
+  else
+    level_fused_node<KT, TRACK, W, false>(depth, S, P, st, (uint32_t)sz, keys, idx, lds, red, xs);
 }
 
 // Levels k and k + 1 of the sets whose fused depth for W wavefronts per node
@@ -1704,7 +1786,7 @@ __device__ __forceinline__ void level_fused_body(uint32_t depth, const SetDesc& 
 template <int W>
 constexpr int fused_threads() { return W == 1 ? kBlock : 64 * W; }
 template <bool TRACK, int W>
-__global__ void __launch_bounds__(fused_threads<W>(), W == 4 ? 4 : 1) k_level_fused(uint32_t depth, uint32_t nsets,
+__global__ void __launch_bounds__(fused_threads<W>(), 4) k_level_fused(uint32_t depth, uint32_t nsets,
                                                         const uint64_t* pre, const SetDesc* sets,
                                                         DevParams* params, uint8_t* keys0,
                                                         uint8_t* keys1, uint32_t* idx0,
@@ -1715,9 +1797,10 @@ __global__ void __launch_bounds__(fused_threads<W>(), W == 4 ? 4 : 1) k_level_fu
   constexpr uint32_t kNodeWords = 3 * W * (uint32_t)kFuseNode / 4;
   constexpr uint32_t kNodes = W == 1 ? kBlock / 64 : 1;
   __shared__ __align__(16) uint64_t stage[kNodes * kNodeWords];
-  __shared__ uint32_t red[2 * W + 8];
+  __shared__ uint32_t red[4 * W + 8];
   __shared__ uint32_t xs[3][W][4];
-  const uint32_t wv = threadIdx.x >> 6;
+  // wavefront-uniform, so that the node's span and addresses stay in scalar registers
+  const uint32_t wv = (uint32_t)__builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
   const uint64_t gn = W == 1 ? (uint64_t)blockIdx.x * (kBlock / 64) + wv : blockIdx.x;
   if (gn >= pre[nsets]) return;  // whole wavefront (W = 1) or block
   const uint32_t s = find_set(pre, nsets, gn);
