@@ -238,6 +238,11 @@ __global__ void __launch_bounds__(kBlock) k_epilogue(const SetDesc* sets, const 
   *P = p;
 }
 
+// Copies of the root bins (a lane uses one of them; a word apart beyond the
+// bins, so that equal bins of two copies lie in different banks): with 13-bit
+// codes the first digit has 32 bins, which 64 lanes would hit at once.
+constexpr uint32_t kRootCopies = 4, kRootStride = kHistBins + 1;
+
 // Root histogram: when the depth-0 median is selected with global histograms,
 // quantization also counts the first radix digit of every axis-0 code into
 // the block's LDS bins (lh != null), so that level needs no pass of its own.
@@ -333,22 +338,25 @@ __global__ void __launch_bounds__(kBlock) k_quantize(uint32_t nsets, const uint6
   uint32_t* idx = S.track ? idx0 + S.idx_off : nullptr;
   // the depth-0 first-digit histogram, when depth 0 uses global histograms
   // with more than one digit pass (the same condition the level kernels use)
-  __shared__ uint32_t lh[kHistBins];
+  __shared__ uint32_t lh[kRootCopies * kRootStride];
+  uint32_t* const mine = lh + (threadIdx.x & (kRootCopies - 1)) * kRootStride;  // this lane's copy
   const DigitPlan pl = digit_plan(P->G[0]);
   const bool root = !S.split && !level_is_local(S.n, 0) && !level_fused(S, 0) && pl.npass >= 2 && S.n > S.r;
   const uint32_t hsh = pl.shift[0], hmask = (1u << pl.width[0]) - 1;
   if (root) {
-    lh[threadIdx.x] = 0;
+    for (uint32_t i = threadIdx.x; i < kRootCopies * kRootStride; i += kBlock) lh[i] = 0;
     __syncthreads();
   }
   if (S.dtype == BBX_F32)
-    quantize_set<float>(S, P, lb, nblk, keys0 + S.key_off, idx, root ? lh : nullptr, hsh, hmask);
+    quantize_set<float>(S, P, lb, nblk, keys0 + S.key_off, idx, root ? mine : nullptr, hsh, hmask);
   else
-    quantize_set<double>(S, P, lb, nblk, keys0 + S.key_off, idx, root ? lh : nullptr, hsh, hmask);
+    quantize_set<double>(S, P, lb, nblk, keys0 + S.key_off, idx, root ? mine : nullptr, hsh, hmask);
   if (root) {
     __syncthreads();
-    if (threadIdx.x <= hmask && lh[threadIdx.x])
-      atomicAdd(&hist0[S.hist_off + threadIdx.x], lh[threadIdx.x]);
+    uint32_t cnt = 0;
+#pragma unroll
+    for (uint32_t c = 0; c < kRootCopies; ++c) cnt += lh[c * kRootStride + threadIdx.x];
+    if (threadIdx.x <= hmask && cnt) atomicAdd(&hist0[S.hist_off + threadIdx.x], cnt);
   }
 }
 
