@@ -37,3 +37,50 @@ def test_fused_pair_alignment(bbx, orc, n, kind, dims, eb):
     pts = gen(kind, n, dims, dtype, seed=n)
     for want_perm in (False, True):
         check_parity(orc, bbx, pts, eb, "rel", 32, want_perm=want_perm)
+
+
+def _bytes(kind, n, seed):
+    rng = np.random.default_rng(seed)
+    if kind == "one":  # 1-bit codes, half of the windows without a code
+        return np.full(n, 9, np.uint8)
+    if kind == "two":
+        return rng.integers(0, 2, n).astype(np.uint8)
+    if kind == "flat":  # 8-bit codes throughout: a decode begun elsewhere never falls into step
+        return np.resize(np.arange(256), n).astype(np.uint8)
+    return rng.geometric(0.5, n).clip(0, 255).astype(np.uint8)  # 1- to 12-bit codes
+
+
+# Huffman chunks of one symbol to a full chunk (runs of no, one and many
+# words per lane), and the chunk after a full one.
+@pytest.mark.parametrize("n", [1, 2, 31, 33, 64, 257, 2047, 2049, 4095, 4096, 4097, 8191, 3 * 4096 + 511])
+@pytest.mark.parametrize("kind", ["one", "two", "flat", "geometric"])
+def test_huffman_chunks(bbx, orc, n, kind):
+    data = _bytes(kind, n, n)
+    ref = orc.huffman_encode(data.tobytes())
+    x = torch.from_numpy(data).cuda()
+    assert bbx.huffman_encode(x).cpu().numpy().tobytes() == ref
+    y = torch.from_numpy(np.frombuffer(ref, np.uint8).copy()).cuda()
+    assert np.array_equal(bbx.huffman_decode(y).cpu().numpy(), data)
+
+
+@pytest.mark.parametrize("kind", ["one", "two", "flat", "geometric"])
+def test_huffman_damaged_payload(bbx, orc, kind):
+    """Flipped payload bits and shifted chunk offsets: refused where the
+    oracle refuses, and the oracle's bytes where it decodes."""
+    n = 4096 + 300
+    good = np.frombuffer(orc.huffman_encode(_bytes(kind, n, 5).tobytes()), np.uint8).copy()
+    rng = np.random.default_rng(6)
+    for trial in range(24):
+        bad = good.copy()
+        at = rng.integers(176 if trial % 4 == 0 else 176 + 16, len(bad) - 8)  # not the padding
+        bad[at] ^= np.uint8(1 << rng.integers(0, 8))
+        try:
+            want = orc.huffman_decode(bad.tobytes())
+        except Exception:
+            want = None
+        try:
+            got = bbx.huffman_decode(torch.from_numpy(bad).cuda()).cpu().numpy().tobytes()
+        except bbx.BitboxError as e:
+            assert e.name == "ECORRUPT"
+            got = None
+        assert got == want, (trial, int(at))
