@@ -219,6 +219,18 @@ struct Carve {
   }
 };
 
+// Which reduction loops a batch launches, for one of its sets (rule 3's leaf
+// count is only bounded here).
+static void plan_reduce(const SetDesc& D, BatchPlan* bp) {
+  if (red_chip(D)) {
+    uint32_t& lds = red_chip_mask(D.r) == 4 ? bp->red_chip32 : bp->red_chip64;
+    lds = std::max(lds, (uint32_t)red_chip_bytes(D.n_leaves, D.r));
+    return;
+  }
+  if (D.n_leaves <= kRedLdsBoxes || D.split == 3) bp->red_lds_boxes = 1;
+  if (D.n_leaves > kRedLdsBoxes) bp->red_global = 1;
+}
+
 // Builds the per-set descriptors (without caller pointers when `in` lacks
 // them), the launch plan and the workspace layout of a batch.
 static void plan_batch(const SetIn* in, uint32_t nsets, BatchPlan* bp, std::vector<SetDesc>* descs,
@@ -291,10 +303,7 @@ static void plan_batch(const SetIn* in, uint32_t nsets, BatchPlan* bp, std::vect
       rw[s] = std::max<uint64_t>(1, std::min<uint64_t>((n + 2047) / 2048, 1024));
       bp->reduce = 1;
       bp->split = 1;
-      if (D.reduce) {
-        if (D.n_leaves <= kRedLdsBoxes || D.split == 3) bp->red_lds_boxes = 1;
-        if (D.n_leaves > kRedLdsBoxes) bp->red_global = 1;
-      }
+      if (D.reduce) plan_reduce(D, bp);
       D.mm_blocks = (uint32_t)mm[s];
       D.key_off = key_bytes;
       D.idx_off = idx_n;
@@ -349,10 +358,7 @@ static void plan_batch(const SetIn* in, uint32_t nsets, BatchPlan* bp, std::vect
         rl[s] = 1;
         rw[s] = std::max<uint64_t>(1, std::min<uint64_t>((n + 2047) / 2048, 1024));
         bp->reduce = 1;
-        if (D.n_leaves <= kRedLdsBoxes)
-          bp->red_lds_boxes = 1;
-        else
-          bp->red_global = 1;
+        plan_reduce(D, bp);
       }
       uint64_t max_nodes = 0, max_blocks = 0, bin_nodes = 0, max_lab = 0;
       for (uint32_t k = 0; k < D.gl; ++k) {

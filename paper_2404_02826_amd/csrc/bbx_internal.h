@@ -189,6 +189,20 @@ __host__ __device__ inline const uint32_t* cb_level(const SetDesc& S, uint32_t d
   return cb0 + S.cb_off + (depth & 1u) * S.cb_half;
 }
 
+// Bit box reduction sets whose whole loop state is kept on chip
+// (k_reduce_chip): leaves of at most 64 members (a mask of 32 or 64 bits; rule
+// 3 can leave more in one leaf), at most 4,096 of them, and 28 bytes plus two
+// masks per leaf within the CU's LDS.
+constexpr uint32_t kRedChipBytes = 156 * 1024;
+__host__ __device__ inline uint32_t red_chip_mask(uint32_t r) { return r <= 32 ? 4u : 8u; }
+__host__ __device__ inline uint64_t red_chip_bytes(uint64_t leaves, uint32_t r) {
+  return (leaves + 15) / 16 * 16 * (28 + 2 * red_chip_mask(r));  // 16 wavefronts share them evenly
+}
+__host__ __device__ inline bool red_chip(const SetDesc& S) {
+  return S.reduce != 0 && S.split != 3 && S.r <= 64 && S.n_leaves <= 4096 &&
+         red_chip_bytes(S.n_leaves, S.r) <= kRedChipBytes;
+}
+
 // widths of a box packed m_x | m_y << 8 | m_z << 16
 __device__ inline uint32_t red_m(uint32_t mp, uint32_t d) { return (mp >> (8 * d)) & 0xffu; }
 
@@ -197,8 +211,9 @@ __device__ inline uint32_t red_m(uint32_t mp, uint32_t d) { return (mp >> (8 * d
 // of (key, leaf).
 __device__ inline uint64_t red_key(uint32_t mp, uint32_t dims, uint32_t rule, uint32_t leaf) {
   uint64_t k = 0;
-  for (uint32_t d = 0; d < dims; ++d) {
-    const uint32_t m = red_m(mp, d);
+#pragma unroll
+  for (uint32_t d = 0; d < 3; ++d) {
+    const uint32_t m = d < dims ? red_m(mp, d) : 0u;
     k += rule == 2 ? ((1ull << m) - 1) : m;
   }
   return (k << 31) | leaf;
@@ -604,7 +619,8 @@ struct BatchPlan {
   uint8_t lv_pair[kMaxDepth];    // some set partitions global levels k, k + 1 together (k_pair.hip)
   uint8_t pair_wide[kMaxDepth];  // some paired set's nodes have > 256 chunks at level k
   uint32_t reduce;               // some set runs the bit box reduction
-  uint32_t red_lds_boxes;        // some reduce set keeps its boxes on chip (<= kRedLdsBoxes leaves)
+  uint32_t red_chip32, red_chip64;  // LDS bytes of the reduce sets that keep all their state on chip, by mask size (0: none)
+  uint32_t red_lds_boxes;        // some other reduce set keeps its boxes on chip (<= kRedLdsBoxes leaves)
   uint32_t red_global;           // some reduce set keeps them in the workspace
   uint32_t split;                // some set uses a split rule other than 0
   uint64_t g_rp, g_rl, g_rw;     // reduction: preparation, loop and packing blocks

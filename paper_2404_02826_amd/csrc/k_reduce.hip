@@ -125,9 +125,10 @@ __device__ inline bool red_inside(const uint4 q, const uint32_t c[3], const uint
                                   uint32_t dims) {
   bool in = true;
   const uint32_t v[3] = {q.x, q.y, q.z};
-  for (uint32_t d = 0; d < dims; ++d) {
+#pragma unroll
+  for (uint32_t d = 0; d < 3; ++d) {
     const uint32_t o = v[d] > c[d] ? v[d] - c[d] : c[d] - v[d];
-    in = in && o <= R[d];
+    in &= d >= dims || o <= R[d];
   }
   return in;
 }
@@ -138,9 +139,11 @@ __device__ inline bool red_meet(const uint4 b, const uint32_t c[3], const uint32
                                 uint32_t dims) {
   bool hit = true;
   const uint32_t o[3] = {b.x, b.y, b.z};
-  for (uint32_t d = 0; d < dims; ++d) {
-    const uint64_t gap = o[d] > c[d] ? o[d] - c[d] : c[d] - o[d];
-    hit = hit && gap <= (uint64_t)R[d] + red_reach(red_m(b.w, d));
+#pragma unroll
+  for (uint32_t d = 0; d < 3; ++d) {
+    // (codes below 2^30 and reaches below 2^30: no sum passes 32 bits)
+    const uint32_t gap = o[d] > c[d] ? o[d] - c[d] : c[d] - o[d];
+    hit &= d >= dims || gap <= R[d] + red_reach(red_m(b.w, d));
   }
   return hit;
 }
@@ -160,8 +163,10 @@ __device__ inline void red_refit(const RedSet& R, uint32_t st, uint32_t sz, uint
     const uint4 q = R.tq[st + k];
     if (red_inside(q, c, Rr, dims)) continue;
     const uint32_t v[3] = {q.x, q.y, q.z};
+#pragma unroll
     for (uint32_t d = 0; d < 3; ++d) mn[d] = umin32(mn[d], v[d]), mx[d] = umax32(mx[d], v[d]);
   }
+#pragma unroll
   for (uint32_t d = 0; d < 3; ++d) mn[d] = wave_min_dpp(mn[d]), mx[d] = wave_max_dpp(mx[d]);
   uint64_t bd = kDead;
   uint32_t bk = ~0u;
@@ -171,9 +176,10 @@ __device__ inline void red_refit(const RedSet& R, uint32_t st, uint32_t sz, uint
     if (red_inside(q, c, Rr, dims)) continue;
     const uint32_t v[3] = {q.x, q.y, q.z};
     uint64_t dist = 0;
-    for (uint32_t d = 0; d < dims; ++d) {
+#pragma unroll
+    for (uint32_t d = 0; d < 3; ++d) {
       const int64_t t = 2 * (int64_t)v[d] - (int64_t)mn[d] - (int64_t)mx[d];
-      dist += (uint64_t)(t * t);
+      if (d < dims) dist += (uint64_t)(t * t);
     }
     if (dist < bd) bd = dist, bk = k;  // k ascends within a lane: the first on ties
   }
@@ -185,9 +191,10 @@ __device__ inline void red_refit(const RedSet& R, uint32_t st, uint32_t sz, uint
   const uint4 q = R.tq[st + bk];
   const uint32_t v[3] = {q.x, q.y, q.z};
   uint32_t mp = 0;
-  for (uint32_t d = 0; d < dims; ++d) {
+#pragma unroll
+  for (uint32_t d = 0; d < 3; ++d) {
     const uint32_t D = umax32(v[d] - mn[d], mx[d] - v[d]);
-    mp |= red_width(D) << (8 * d);
+    if (d < dims) mp |= red_width(D) << (8 * d);
   }
   *ref_out = st + bk;
   *box_out = make_uint4(v[0], v[1], v[2], mp);
@@ -212,6 +219,25 @@ __device__ inline uint32_t red_exscan(uint32_t v, uint32_t* wsum, uint32_t* tota
   return off + incl - v;
 }
 
+// After the loop (whole block): the sequence count, and the payload bits per
+// sequence (zero past the last) for the offset scan.
+__device__ inline void red_finish(const SetDesc& S, DevParams* P, const RedSet& R, uint32_t B,
+                                  uint32_t nseq, uint32_t placed, uint64_t* bits) {
+  if (threadIdx.x == 0) {
+    P->nseq = nseq;
+    // every particle placed exactly once (slot writes past n were dropped)
+    if (placed != S.n) check_failed(P, kChkReduce);
+  }
+  for (uint32_t i = threadIdx.x; i < B; i += blockDim.x) {
+    uint64_t v = 0;
+    if (i < nseq) {
+      const uint4 q = R.seq[i];
+      v = (uint64_t)q.z * (red_m(q.y, 0) + red_m(q.y, 1) + red_m(q.y, 2));
+    }
+    bits[i] = v;
+  }
+}
+
 // The loop of one set.  LDS: the boxes' keys and records live in on-chip
 // memory for the whole loop (sets of at most kRedLdsBoxes leaves); else in
 // the workspace.  Each thread owns a contiguous range of boxes for the two
@@ -225,7 +251,7 @@ __global__ void __launch_bounds__(kRedBlock) k_reduce(uint32_t nsets, const uint
   if (P->status != BBX_OK || !S.reduce || S.n == 0) return;
   // a split-rule set's leaf count is found on the device
   const uint64_t NL = S.split ? P->nleaves : S.n_leaves;
-  if ((NL <= kRedLdsBoxes) != LDS) return;
+  if (red_chip(S) || (NL <= kRedLdsBoxes) != LDS) return;
   const RedSet R = red_set(S, w);
   const LeafRec* leaves = w.leaves + S.leaf_off;
   const uint32_t B = (uint32_t)NL, dims = S.dims;
@@ -363,22 +389,284 @@ __global__ void __launch_bounds__(kRedBlock) k_reduce(uint32_t nsets, const uint
     }
     __syncthreads();
   }
-  const uint32_t nseq = s_nseq;
-  if (threadIdx.x == 0) {
-    P->nseq = nseq;
-    // every particle placed exactly once (slot writes past n were dropped)
-    if (s_slot != S.n) check_failed(P, kChkReduce);
+  red_finish(S, P, R, B, s_nseq, s_slot, w.leaf_bits + S.leaf_off);
+}
+
+// ---- sets whose leaves fit a mask word (red_chip): the whole loop state on chip
+
+// Minimum over the wavefront (uniform); wide: keys of more than 32 bits.
+__device__ inline uint64_t red_wave_min(uint64_t x, bool wide) {
+  if (!wide) {
+    const uint32_t lo = wave_min_dpp((uint32_t)x);
+    return lo == 0xffffffffu ? kDead : (uint64_t)lo;
   }
-  // payload bits per sequence (zero past the last), for the offset scan
-  uint64_t* bits = w.leaf_bits + S.leaf_off;
-  for (uint32_t i = threadIdx.x; i < B; i += kRedBlock) {
-    uint64_t v = 0;
-    if (i < nseq) {
-      const uint4 q = R.seq[i];
-      v = (uint64_t)q.z * (red_m(q.y, 0) + red_m(q.y, 1) + red_m(q.y, 2));
+  const uint32_t hi = wave_min_dpp((uint32_t)(x >> 32));
+  const uint32_t lo = wave_min_dpp((uint32_t)(x >> 32) == hi ? (uint32_t)x : 0xffffffffu);
+  return (uint64_t)hi << 32 | lo;
+}
+
+// Minimum over the 32 lanes of each half of the wavefront (MT of 32 bits: two
+// boxes at a time) or over all 64, in every lane of them; K independent
+// values together, whose steps fill each other's DPP wait states.
+template <typename MT, int K>
+__device__ __forceinline__ void red_seg_min(uint32_t (&x)[K]) {
+  const int I = -1;
+#define RED_STEP(ctrl, rows)                                                                    \
+  _Pragma("unroll") for (int i = 0; i < K; ++i) x[i] = umin32(                                  \
+      x[i], (uint32_t)__builtin_amdgcn_update_dpp(I, (int)x[i], ctrl, rows, 0xf, false))
+  RED_STEP(0x111, 0xf);  // row_shr:1, 2, 4, 8, then row_bcast:15 and :31
+  RED_STEP(0x112, 0xf);
+  RED_STEP(0x114, 0xf);
+  RED_STEP(0x118, 0xf);
+  RED_STEP(0x142, 0xa);
+  if (sizeof(MT) == 8) RED_STEP(0x143, 0xc);
+#undef RED_STEP
+#pragma unroll
+  for (int i = 0; i < K; ++i) {
+    const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int)x[i], 63);
+    const uint32_t lo = sizeof(MT) == 8 ? hi : (uint32_t)__builtin_amdgcn_readlane((int)x[i], 31);
+    x[i] = (threadIdx.x & 32) ? hi : lo;
+  }
+}
+
+// The loop of one set with its whole state in LDS: per leaf its box (codes,
+// widths, the reference's place among the members), the members it still has
+// (a bit each), the ones the current pop takes, and its first position.  Box
+// b belongs to wavefront b mod W, so that the neighbours of a popped box,
+// which follow each other in leaf order, fall to different wavefronts; a
+// wavefront alone reads and rewrites its boxes.  A pop has one barrier:
+//   every wavefront  finds the popped box (the smallest of the W minima),
+//                    tests its own boxes against it, reads the members of
+//                    those that meet it (two boxes at a time where a leaf
+//                    has at most 32), refits the boxes that lose some and
+//                    lists them, and posts its new smallest key
+//   barrier
+//   every wavefront  sums the listed losses before each of its own boxes (its
+//                    catch's place in the output) and writes its catch;
+//                    wavefront 0 writes the popped box's own members and the
+//                    sequence record
+// What is posted is double-buffered by the pop's parity (the list's length
+// by pop mod 3, since the next pop's must be zero before its barrier).  A pop
+// is a chain of a few LDS reads, one round of member reads and one barrier:
+// 65,536 uniform particles (2,048 leaves) took 19.0 ms with the members'
+// flags in memory and six barriers a pop, and take 5.6 (16 wavefronts; 8 and 4 take 6.5 and
+// 10: the boxes tested per pop bound it, then the chain of one pop).
+constexpr uint32_t kChipWaves = 16;
+constexpr uint32_t kRedGone = 0xffffffffu;  // packed widths of a popped or empty box
+
+template <typename MT>
+__global__ void __launch_bounds__(64 * kChipWaves) k_reduce_chip(uint32_t nsets, const uint64_t* pre, Ws w) {
+  extern __shared__ __align__(16) uint8_t red_dyn[];
+  constexpr uint32_t W = kChipWaves, M = 8 * sizeof(MT);  // M: members per mask
+  const uint32_t s = find_set(pre, nsets, blockIdx.x);
+  const SetDesc& S = w.sets[s];
+  DevParams* P = w.params + s;
+  if (P->status != BBX_OK || !S.reduce || S.n == 0) return;
+  if (!red_chip(S) || (red_chip_mask(S.r) == 4) != (sizeof(MT) == 4)) return;
+  const uint64_t NL = S.split ? P->nleaves : S.n_leaves;
+  const RedSet R = red_set(S, w);
+  const LeafRec* leaves = w.leaves + S.leaf_off;
+  const uint32_t B = (uint32_t)(NL < S.n_leaves ? NL : S.n_leaves), dims = S.dims;
+  const uint32_t lane = threadIdx.x & 63;
+  const uint32_t wv = (uint32_t)__builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+  const uint32_t perW = (B + W - 1) / W, slots = perW * W;
+  uint4* const C = (uint4*)red_dyn;
+  MT* const alive = (MT*)(C + slots);
+  MT* const caught = alive + slots;
+  uint32_t* const start = (uint32_t*)(caught + slots);
+  uint32_t* const list = start + slots;  // two of `slots` entries: box | losses << 16
+  __shared__ uint64_t s_min[2][W];
+  __shared__ unsigned long long s_nlist[3];  // entries | their losses << 32
+  const bool wide = S.reduce == 2;
+  // box b at slot (b mod W) perW + b / W
+  for (uint32_t x = threadIdx.x; x < slots; x += 64 * W) {
+    const uint32_t b = (x % perW) * W + x / perW;
+    uint4 c = make_uint4(0, 0, 0, kRedGone);
+    MT m = 0;
+    uint32_t st = 0;
+    if (b < B) {
+      const LeafRec L = leaves[b];
+      st = L.start;
+      m = L.size >= M ? (MT) ~(MT)0 : (MT)(((MT)1 << L.size) - 1);
+      c = R.ctr[b];
+      c.w = (c.w & 0xffffffu) | ((R.ref[b] - st) << 24);
     }
-    bits[i] = v;
+    C[x] = c;
+    alive[x] = m;
+    start[x] = st;
   }
+  if (threadIdx.x < 3) s_nlist[threadIdx.x] = 0;
+  __syncthreads();
+  const uint32_t mine0 = wv * perW;  // the wavefront's slots [mine0, mine0 + perW)
+  // the smallest (key, leaf) of the wavefront's boxes other than `skip`
+  auto own_min = [&](uint32_t skip) {
+    uint64_t best = kDead;
+    for (uint32_t x = lane; x < perW; x += 64) {
+      const uint32_t mp = C[mine0 + x].w, b = x * W + wv;
+      if (mp == kRedGone || b == skip) continue;
+      const uint64_t k = red_key(mp, dims, S.reduce, 0) >> 19 | b;  // key << 12 | leaf
+      best = k < best ? k : best;
+    }
+    return red_wave_min(best, wide);
+  };
+  uint64_t omin = own_min(~0u);  // kept until one of the boxes changes
+  if (lane == 0) s_min[0][wv] = omin;
+  __syncthreads();
+  uint32_t slot = 0, nseq = 0;
+  for (uint32_t t = 0;; ++t) {
+    const uint64_t best = red_wave_min(s_min[t & 1][lane & (W - 1)], wide);  // (repeated: any W below 64)
+    if (best == kDead) break;  // uniform: every box popped or empty
+    const uint32_t cur = (uint32_t)(best & 0xfffu), cs = (cur % W) * perW + cur / W;
+    const uint4 cb = C[cs];
+    const uint32_t c[3] = {cb.x, cb.y, cb.z};
+    const uint32_t Rr[3] = {red_reach(red_m(cb.w, 0)), red_reach(red_m(cb.w, 1)),
+                            red_reach(red_m(cb.w, 2))};
+    uint32_t* const lst = list + (t & 1) * slots;
+    const uint32_t nl_at = t % 3;
+    bool changed = false;
+    for (uint32_t x0 = 0; x0 < perW; x0 += 64) {
+      bool hit = false;
+      if (x0 + lane < perW) {
+        const uint4 o = C[mine0 + x0 + lane];
+        hit = o.w != kRedGone && (x0 + lane) * W + wv != cur && red_meet(o, c, Rr, dims);
+      }
+      uint64_t hm = __ballot(hit);
+      while (hm) {
+        // two groups of boxes, one (M = 64) or two (M = 32, a half of the
+        // wavefront each) at a time; both groups' members are read first
+        constexpr int G = 2;
+        const uint32_t k = lane & (M - 1);
+        uint32_t x[G];
+        bool valid[G];
+        uint4 q[G];
+#pragma unroll
+        for (int g = 0; g < G; ++g) {
+          bool has = hm != 0;
+          x[g] = has ? x0 + (uint32_t)__builtin_ctzll(hm) : 0u;
+          hm &= hm - 1;  // (zero stays zero)
+          if (M == 32) {
+            const bool has2 = hm != 0;
+            const uint32_t x2 = has2 ? x0 + (uint32_t)__builtin_ctzll(hm) : 0u;
+            hm &= hm - 1;
+            if (lane & 32) has = has2, x[g] = x2;
+          }
+          x[g] += mine0;
+          valid[g] = has && ((alive[x[g]] >> k) & 1);
+          q[g] = make_uint4(0, 0, 0, 0);
+          if (valid[g]) q[g] = R.tq[start[x[g]] + k];
+        }
+#pragma unroll
+        for (int g = 0; g < G; ++g) {
+          const bool in = valid[g] && red_inside(q[g], c, Rr, dims);
+          const uint64_t im = __ballot(in);
+          if (!im) continue;
+          const bool stay = valid[g] && !in;
+          const uint64_t sm = __ballot(stay);
+          const MT inm = (MT)(M == 32 && (lane & 32) ? im >> 32 : im);
+          const MT stm = (MT)(M == 32 && (lane & 32) ? sm >> 32 : sm);
+          // the box of what stays: AABB, the member nearest its centre
+          // (squared distance in doubled code space, the first on ties), Eq. 2
+          const uint32_t v[3] = {q[g].x, q[g].y, q[g].z};
+          uint32_t e[6];  // minima, and maxima as minima of the complement
+#pragma unroll
+          for (int d = 0; d < 3; ++d) e[d] = stay ? v[d] : ~0u, e[3 + d] = stay ? ~v[d] : ~0u;
+          red_seg_min<MT, 6>(e);
+          uint32_t u[3], span = 0;
+#pragma unroll
+          for (int d = 0; d < 3; ++d) {
+            const uint32_t mn = e[d], mx = ~e[3 + d];
+            // |2 v - mn - mx|, at most the box's extent (axes not in use: all 0)
+            const uint32_t t2 = 2 * v[d], sum = mn + mx;
+            u[d] = t2 > sum ? t2 - sum : sum - t2;
+            span |= stay ? mx - mn : 0u;
+          }
+          uint64_t fm;  // the members at the smallest distance
+          if (__ballot(span >= 32768u) == 0) {  // three squares fit 32 bits
+            const uint32_t dist = u[0] * u[0] + u[1] * u[1] + u[2] * u[2];
+            uint32_t m[1] = {stay ? dist : ~0u};
+            red_seg_min<MT, 1>(m);
+            fm = __ballot(stay && dist == m[0]);
+          } else {
+            const uint64_t dist = (uint64_t)u[0] * u[0] + (uint64_t)u[1] * u[1] + (uint64_t)u[2] * u[2];
+            const uint32_t dh = (uint32_t)(dist >> 32), dl = (uint32_t)dist;
+            uint32_t m[1] = {stay ? dh : ~0u};
+            red_seg_min<MT, 1>(m);
+            const bool top = stay && dh == m[0];
+            uint32_t l[1] = {top ? dl : ~0u};
+            red_seg_min<MT, 1>(l);
+            fm = __ballot(top && dl == l[0]);
+          }
+          if (M == 32) fm = (lane & 32) ? fm >> 32 : fm & 0xffffffffull;
+          const uint32_t bk = fm ? (uint32_t)__builtin_ctzll(fm) : 0u;
+          const int from = (int)((lane & ~(M - 1)) | bk);
+          uint32_t rv[3], mp = 0;
+#pragma unroll
+          for (int d = 0; d < 3; ++d) {
+            rv[d] = (uint32_t)__shfl((int)v[d], from);
+            mp |= red_width(umax32(rv[d] - e[d], ~e[3 + d] - rv[d])) << (8 * d);
+          }
+          mp = stm ? mp | (bk << 24) : kRedGone;
+          if (k == 0 && inm) {
+            C[x[g]] = make_uint4(rv[0], rv[1], rv[2], mp);
+            alive[x[g]] = stm;
+            caught[x[g]] = inm;
+            // the list's length and the sum of its losses in one word
+            const uint32_t lost = (uint32_t)__popcll((uint64_t)inm);
+            const uint32_t at = (uint32_t)(atomicAdd(&s_nlist[nl_at], 1ull | ((unsigned long long)lost << 32)));
+            lst[at] = ((x[g] - mine0) * W + wv) | (lost << 16);
+          }
+          changed = true;
+        }
+      }
+    }
+    if (changed || cur % W == wv) {
+      wave_sync();  // the boxes' new records, read by other lanes now
+      omin = own_min(cur);
+    }
+    if (lane == 0) s_min[(t + 1) & 1][wv] = omin;
+    if (threadIdx.x == 0) s_nlist[(t + 1) % 3] = 0;
+    __syncthreads();
+    // ---- places in the output: the popped box's reference, its other
+    // members, then the catches in leaf order
+    const uint64_t nlist = s_nlist[nl_at];
+    const uint32_t nl = (uint32_t)__builtin_amdgcn_readfirstlane((int)nlist), total = (uint32_t)(nlist >> 32);
+    const MT own = alive[cs];
+    const uint32_t nown = (uint32_t)__popcll((uint64_t)own);
+    for (uint32_t e0 = 0; e0 < nl && changed; e0 += 64) {  // (a wavefront without a catch has no entry)
+      const uint32_t ent = e0 + lane < nl ? lst[e0 + lane] : 0u;
+      uint64_t om = __ballot(e0 + lane < nl && (ent & 0xffffu) % W == wv);
+      while (om) {
+        const uint32_t b = (uint32_t)__builtin_amdgcn_readlane((int)ent, __builtin_ctzll(om)) & 0xffffu;
+        om &= om - 1;
+        uint32_t before = 0;
+        for (uint32_t e1 = 0; e1 < nl; e1 += 64) {
+          const uint32_t o = e1 + lane < nl ? lst[e1 + lane] : 0u;
+          before += (uint32_t)__builtin_amdgcn_readlane(
+              (int)wave_incl((o & 0xffffu) < b ? o >> 16 : 0u), 63);
+        }
+        const uint32_t x = mine0 + b / W;
+        const uint64_t m = (uint64_t)caught[x];
+        const uint32_t at = slot + nown + before + lanes_below(m);
+        if (((m >> lane) & 1) && at < S.n) R.slot_pos[at] = start[x] + lane;
+      }
+    }
+    const uint32_t ref = cb.w >> 24;
+    if (wv == 0) {
+      const uint64_t m = (uint64_t)own & ~(1ull << ref);
+      const uint32_t at = slot + 1 + lanes_below(m), st = start[cs];
+      if (((m >> lane) & 1) && at < S.n) R.slot_pos[at] = st + lane;
+      if (lane == 0) {
+        if (slot < S.n) R.slot_pos[slot] = st + ref;
+        R.seq[nseq] = make_uint4(st + ref, cb.w & 0xffffffu, nown - 1 + total, slot);
+      }
+    }
+    if (cur % W == wv && lane == 0) C[cs].w = kRedGone;
+    wave_sync();
+    slot += nown + total;
+    ++nseq;
+  }
+  __syncthreads();  // every sequence record is written
+  red_finish(S, P, R, B, nseq, slot, w.leaf_bits + S.leaf_off);
 }
 
 // ---------------------------------------------------------------- packing
@@ -501,11 +789,26 @@ hipError_t launch_reduce(const BatchPlan& bp, const Ws& w, hipStream_t s) {
   if (!bp.reduce) return hipGetLastError();
   // the on-chip variant keeps 24 bytes per box: above the default 64 KB of
   // dynamic LDS, so its limit is raised once (gfx950 has 160 KB per CU)
-  static hipError_t lds_set = hipFuncSetAttribute(
-      (const void*)k_reduce<true>, hipFuncAttributeMaxDynamicSharedMemorySize, 24 * kRedLdsBoxes);
+  static hipError_t lds_set = [] {
+    hipError_t e = hipFuncSetAttribute((const void*)k_reduce<true>,
+                                       hipFuncAttributeMaxDynamicSharedMemorySize, 24 * kRedLdsBoxes);
+    if (e == hipSuccess)
+      e = hipFuncSetAttribute((const void*)k_reduce_chip<uint32_t>,
+                              hipFuncAttributeMaxDynamicSharedMemorySize, kRedChipBytes);
+    if (e == hipSuccess)
+      e = hipFuncSetAttribute((const void*)k_reduce_chip<uint64_t>,
+                              hipFuncAttributeMaxDynamicSharedMemorySize, kRedChipBytes);
+    return e;
+  }();
   if (lds_set != hipSuccess) return lds_set;
   if (bp.g_rp > 0) BBX_LAUNCH("reduce_prep", k_red_prep, bp.g_rp, kBlock, 0, s, bp.nsets, w.pre + bp.o_rp, w);
   if (bp.g_rl > 0) {
+    if (bp.red_chip32)
+      BBX_LAUNCH("reduce", k_reduce_chip<uint32_t>, bp.g_rl, 64 * kChipWaves, bp.red_chip32, s, bp.nsets,
+                 w.pre + bp.o_rl, w);
+    if (bp.red_chip64)
+      BBX_LAUNCH("reduce", k_reduce_chip<uint64_t>, bp.g_rl, 64 * kChipWaves, bp.red_chip64, s, bp.nsets,
+                 w.pre + bp.o_rl, w);
     if (bp.red_lds_boxes)
       BBX_LAUNCH("reduce", k_reduce<true>, bp.g_rl, kRedBlock, (size_t)24 * kRedLdsBoxes, s, bp.nsets,
                  w.pre + bp.o_rl, w);

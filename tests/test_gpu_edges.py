@@ -84,3 +84,20 @@ def test_huffman_damaged_payload(bbx, orc, kind):
             assert e.name == "ECORRUPT"
             got = None
         assert got == want, (trial, int(at))
+
+
+# The on-chip reduction loop: leaves of exactly a mask (32, 64 members), the
+# sizes just past it, few leaves and the most, many boxes meeting the popped
+# one (coarse codes: more than a wavefront of them), both keys.
+@pytest.mark.parametrize("kind,n,dims,eb,r,kr", [
+    ("uniform", 32 * 16, 3, 1e-3, 32, 1), ("uniform", 33 * 17, 3, 1e-3, 33, 1),
+    ("uniform", 64 * 40, 3, 1e-3, 64, 2), ("uniform", 65 * 8, 3, 1e-3, 65, 1),
+    ("ties", 9000, 3, 1e-1, 32, 1), ("ties", 9000, 2, 1e-1, 64, 2), ("cosmology", 8192, 2, 1e-2, 2, 1),
+    ("cosmology", 4096, 3, 1e-2, 1, 2), ("uniform", 131072, 3, 1e-3, 32, 1),
+    ("cosmology", 120001, 3, 1e-4, 64, 1)])
+def test_reduction_on_chip(bbx, orc, kind, n, dims, eb, r, kr):
+    pts = gen(kind, n, dims, np.float32, seed=n + r)
+    want, want_perm = orc.compress_reduced(pts, eb, "rel", r, key_rule=kr - 1, want_perm=True)
+    s, perm = bbx.compress(torch.from_numpy(pts).cuda(), eb, "rel", r, want_perm=True, reduce=kr)
+    assert s.cpu().numpy().tobytes() == want
+    assert np.array_equal(perm.cpu().numpy().astype(np.uint32), want_perm)
