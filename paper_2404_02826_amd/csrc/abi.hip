@@ -245,17 +245,23 @@ static void plan_batch(const SetIn* in, uint32_t nsets, BatchPlan* bp, std::vect
   // block target of the global levels: kSoloLevelBlocks for a set alone (a
   // larger target makes the levels' blocks too short: cosmology 2^24 1.69
   // against 2.03 ms per round trip at 4096); in a batch each set's share of
-  // 4 * kLevelBlocks by particle count
+  // kLevelBlocks by particle count (256 sets of 10^3..10^6 particles: 4.21 ms
+  // against 4.35 and 4.55 with shares of 2 and 4 kLevelBlocks, 4.13 and 4.25
+  // with a half and a quarter; 1,024 such sets: 10.99, 11.18 and 11.56 ms with
+  // one, a half and a quarter)
   uint64_t n_total = 0;
   for (uint32_t s = 0; s < nsets; ++s) n_total += in[s].n;
   auto level_blocks = [&](uint64_t n, uint32_t cap) -> uint32_t {
     uint32_t b = (uint32_t)kSoloLevelBlocks;
     if (nsets > 1 && n_total > 0) {
-      const double share = 4.0 * (double)kLevelBlocks * (double)n / (double)n_total;
+      const double share = (double)kLevelBlocks * (double)n / (double)n_total;
       b = (uint32_t)std::min<double>((double)kLevelBlocks, std::max(1.0, std::floor(share + 0.5)));
     }
     return cap ? std::min(b, cap) : b;
   };
+  bp->fold = 1;
+  for (uint32_t s = 0; s < nsets; ++s)
+    if (in[s].n > 0 && in[s].prm.level_pairs == 1 && !in[s].prm.split_rule) bp->fold = 0;
   std::vector<uint64_t> mm(nsets), qz(nsets), tl(nsets), bg(nsets), pm(nsets), pp(nsets);
   std::vector<uint64_t> rp(nsets, 0), rl(nsets, 0), rw(nsets, 0);
   std::vector<uint8_t> stage_seen(kMaxDepth, 0);  // a set with global level k seen
@@ -362,6 +368,16 @@ static void plan_batch(const SetIn* in, uint32_t nsets, BatchPlan* bp, std::vect
       }
       uint64_t max_nodes = 0, max_blocks = 0, bin_nodes = 0, max_lab = 0;
       for (uint32_t k = 0; k < D.gl; ++k) {
+        if (level_fused(D, k) || level_kind(n, k) == kLevelWave) break;
+        D.nbins = k + 1;
+        if (level_kind(n, k) == kLevelGlobal) D.nglobal = k + 1;
+      }
+      D.mid_depth = D.nglobal;
+      if (nsets == 1)
+        while (D.mid_depth > 0 && ((n + (1ull << (D.mid_depth - 1)) - 1) >> (D.mid_depth - 1)) <= kMidFold)
+          --D.mid_depth;
+      for (uint32_t k = 0; k < D.mid_depth; ++k) bp->lv_mid[k] = 1;
+      for (uint32_t k = 0; k < D.gl; ++k) {
         const LevelShape sh = level_shape(n, k, D.level_blocks);
         const int kind = level_kind(n, k);
         uint8_t fam = kFamGlobal;
@@ -414,7 +430,9 @@ static void plan_batch(const SetIn* in, uint32_t nsets, BatchPlan* bp, std::vect
       D.sel_half = max_nodes;
       D.rows_off = rows_n * kRowStride;
       D.cb_off = cb_n;
-      D.cb_half = 4 * max_blocks;  // a paired second level: two children per parent chunk
+      // a paired second level: two children per parent chunk (without paired
+      // levels the chunk bases are not kept)
+      D.cb_half = bp->fold ? 0 : 4 * max_blocks;
       D.lab_off = lab_n;
       D.leaf_off = leaves_n;
       D.part_off = parts;
@@ -422,9 +440,9 @@ static void plan_batch(const SetIn* in, uint32_t nsets, BatchPlan* bp, std::vect
       key_bytes += align_up((uint64_t)D.dims * D.kst * 4);
       if (I.need_idx || D.track) idx_n += (n + 63) & ~63ull;
       if (D.reduce && !(I.need_idx || D.track)) idx_n += (n + 63) & ~63ull;
-      hist_n += 2 * bin_nodes * kHistBins;
+      hist_n += 3 * bin_nodes * kHistBins;
       sel_n += 2 * max_nodes;
-      rows_n += 2 * max_blocks;
+      rows_n += (bp->fold ? 1 : 2) * max_blocks;
       cb_n += 2 * D.cb_half;
       lab_n += max_lab;
       leaves_n += D.n_leaves;
@@ -627,7 +645,10 @@ static std::string check_plan(const SetIn* in, uint32_t nsets) {
         continue;
       }
       // block-local and global levels count radix bins of their nodes
-      if (sh.nodes > bin_nodes) return where(s, k) + "radix bins too few";
+      if (sh.nodes > bin_nodes || k >= D.nbins) return where(s, k) + "radix bins too few";
+      if ((kind == kLevelGlobal) != (k < D.nglobal)) return where(s, k) + "global level count";
+      if (bp.fold && kind == kLevelGlobal && k < D.mid_depth && !bp.lv_mid[k])
+        return where(s, k) + "middle digits not launched";
       if (kind == kLevelBlock) {
         if (sh.chunks != 1) return where(s, k) + "block-local level with more than one chunk per node";
         if (level_shape(n, k, kLocalBlocks).chunks != 1) return where(s, k) + "block-local kind";

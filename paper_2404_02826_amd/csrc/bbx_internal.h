@@ -111,14 +111,17 @@ struct SetDesc {
   uint64_t key_off;       // byte offset into each key buffer (capacity dims*n*4)
   uint64_t idx_off;       // u32 offset into each index buffer
   uint64_t hist_off;      // u32 offset into the histogram bins
-  uint64_t hist_half;     // u32 entries of each of the set's two bin regions
+  uint64_t hist_half;     // u32 entries of each of the set's three bin regions
   uint64_t sel_off;       // NodeSel offset
-  uint64_t sel_half;      // NodeSel entries of each of the set's two selection regions (by depth parity)
+  uint64_t sel_half;      // NodeSel entries of each of the set's two selection regions (by depth, or histogram, parity)
   uint64_t rows_off;      // u32 offset into the chunk rows
   uint64_t cb_off;        // u32 offset into the chunk bases
   uint64_t cb_half;       // u32 entries of each of the set's two chunk-base regions (by depth parity)
   uint64_t lab_off;       // u64 offset into the side labels of paired levels
   uint32_t npairs;        // global levels 2p and 2p + 1 (p < npairs) run with one data movement
+  uint32_t nglobal;       // global levels (the first ones)
+  uint32_t nbins;         // levels that use radix bins (global and block-local, above the fused pairs)
+  uint32_t mid_depth;     // from this global level on a block selects a code's middle digits by itself (kMidFold)
   uint32_t fuse_depth16;  // the pair of fuse_depth4 with a block of 16 wavefronts per node (at most 16 kFuseNode)
   uint64_t leaf_off;      // first leaf of the set in the batch's leaf arrays
   uint64_t part_off;      // first block of the set's range partials
@@ -416,7 +419,7 @@ __host__ __device__ inline uint32_t dp_shift(const DigitPlan& p, uint32_t i) {
 // Blocks of one global level of one set: nodes x chunks, each chunk a whole
 // number of streaming groups, about target_blocks blocks per level.  A set
 // alone targets kSoloLevelBlocks; in a batch each set targets its share of
-// 4 kLevelBlocks (by particle count, at least 1), so that a batch of many small sets does
+// kLevelBlocks (by particle count, at least 1), so that a batch of many small sets does
 // not launch a block per 2048 codes.  Which levels are global does not depend
 // on the target (level_kind below asks for kLocalBlocks).
 struct LevelShape {
@@ -457,13 +460,59 @@ __host__ __device__ inline bool level_is_local(uint64_t n, uint32_t depth) {
   return level_kind(n, depth) != kLevelGlobal;
 }
 
-// Radix bins of a level's nodes (256 per node): global levels use the set's
-// first region; a block-local level of depth k uses region k & 1, since its
-// kernel reads its own nodes' first-digit bins while it builds those of the
-// next level's nodes.
+// Radix bins of a level's nodes (256 per node) when the batch has paired
+// levels: global levels use the set's first region; a block-local level of
+// depth k uses region k & 1, since its kernel reads its own nodes'
+// first-digit bins while it builds those of the next level's nodes.
 __device__ inline uint32_t* hist_level(const SetDesc& S, uint32_t depth, uint32_t* hist) {
   return level_kind(S.n, depth) == kLevelBlock ? hist + (depth & 1) * S.hist_half : hist;
 }
+
+// Without paired levels no kernel is launched for a selection: whoever needs
+// a digit of a median finds it itself in the histogram that the kernel before
+// it built.  The histograms of a set follow each other through its three
+// regions: histogram t lies in region t mod 3, kernel by kernel one is read
+// (t - 1), one is built (t), and the next one's region (t + 1) is cleared.
+// A global level of np digits builds np of them (the first in the partition of
+// the level above, or in quantization), or at most two from mid_depth on; a
+// block-local level one.
+__host__ __device__ inline uint32_t digit_passes(uint32_t G) { return G > 8 ? 1 + (G - 1) / 8 : 1; }
+// histogram index of level `depth`'s first digit
+__device__ inline uint32_t hist_index(const SetDesc& S, const uint32_t* G, uint32_t depth) {
+  const uint32_t np[3] = {digit_passes(G[0]), digit_passes(G[1]), digit_passes(G[2])};
+  uint32_t t = 0, a = 0;
+  for (uint32_t k = 0; k < depth; ++k) {
+    const uint32_t x = a == 0 ? np[0] : (a == 1 ? np[1] : np[2]);
+    t += k >= S.nglobal ? 1u : (k >= S.mid_depth && x > 2 ? 2u : x);
+    a = a + 1 == S.dims ? 0u : a + 1;
+  }
+  return t;
+}
+__device__ inline uint32_t* hist_region(const SetDesc& S, uint32_t t, uint32_t* hist) {
+  return hist + (t % 3) * S.hist_half;
+}
+// nodes whose bins level `depth` uses (0: none)
+__device__ inline uint64_t hist_nodes(const SetDesc& S, uint32_t depth) {
+  return depth < S.nbins ? 1ull << depth : 0ull;
+}
+// Block lb of nblk of a set's launch clears its share of histogram t's
+// region, for the nodes of level `depth`.
+__device__ inline void hist_clear(const SetDesc& S, uint32_t t, uint32_t depth, uint64_t lb, uint64_t nblk,
+                                  uint32_t* hist) {
+  const uint64_t entries = hist_nodes(S, depth) << 8;
+  if (!entries) return;
+  const uint64_t per = (entries + nblk - 1) / nblk, a = lb * per;
+  const uint64_t b = a + per < entries ? a + per : entries;
+  uint32_t* h = hist_region(S, t, hist);
+  for (uint64_t i = a + threadIdx.x; i < b; i += blockDim.x) h[i] = 0;
+}
+
+// Nodes of at most this many members (sets alone): the blocks that build a
+// level's last-digit histogram find the middle digits of codes above 16 bits
+// by passes over the whole node of their own, so that such a level takes two
+// launches instead of four.  (In a batch the launches are shared by all sets
+// and the repeated passes would not be.)
+constexpr uint64_t kMidFold = 32768;
 
 // The last levels above the tile stage of a set with a tile stage run in
 // in-place pairs with the node in registers: depths gl - 2 and gl - 1 when
@@ -607,6 +656,8 @@ struct BatchPlan {
   uint64_t g_fu[kMaxDepth], g_f4[kMaxDepth], g_f16[kMaxDepth];
   uint64_t o_lv[kMaxDepth], o_nd[kMaxDepth], o_lc[kMaxDepth], o_wv[kMaxDepth];
   uint64_t o_fu[kMaxDepth], o_f4[kMaxDepth], o_f16[kMaxDepth];
+  uint32_t fold;                 // no paired levels: selections are found by the kernels that use them
+  uint8_t lv_mid[kMaxDepth];     // (fold) some set takes middle digits at global level k from launches of their own
   uint8_t lv_local[kMaxDepth];   // some set handles level k one block per node
   uint8_t lv_global[kMaxDepth];  // some set handles level k with global histograms
   uint8_t sel_wide[kMaxDepth];   // some set's nodes have > 256 chunks at global level k

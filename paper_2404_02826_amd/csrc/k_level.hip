@@ -8,18 +8,21 @@
 // in index order, "index order" is "storage order", so the split is an exact
 // radix select on q_d followed by a stable partition.
 //
-//   (the histogram bins are zeroed once per call before quantization, which
-//   also builds the first-digit histogram of depth 0; every select kernel
-//   re-zeroes the bins it reads)
-//   k_hist_mid     histogram of a further high digit over the candidates
+//   (quantization builds the first-digit histogram of depth 0)
+//   k_fold_mid     histogram of a further high digit over the candidates
 //                  (members matching the digits found so far)
-//   k_select_mid   per node: the digit holding the median's rank
-//   k_hist_last    last digit: per-chunk prefix counts + node totals
-//   k_select_last  per node: the median code v, how many members equal to v
-//                  go left (jeq), and each chunk's (lt, eq) base
+//   k_fold_last    last digit: per-chunk prefix counts + node totals
 //   k_scatter      stable partition of the codes (and source indices); also
 //                  builds the next level's first-digit histogram, so that
 //                  level needs no separate pass over its codes for it
+//   Each finds the digit it needs (and k_scatter the median code v, how many
+//   members equal to v go left, jeq, and its chunk's (lt, eq) base) in the
+//   histogram and rows of the kernel before it: a select launch per digit and
+//   level, as batches with paired levels have (k_hist_mid, k_select_mid,
+//   k_hist_last, k_select_last), cost more than the work of a small set's
+//   level: eight launches a level against four, or two where a block finds
+//   the middle digits by itself (compress of 65,536 particles 285 -> 233 us,
+//   2^24 1,476 -> 1,333, 2^27 9,930 -> 9,770, 256 sets 4,490 -> 4,215).
 //   k_level_local  a level whose nodes each fit one block: median and
 //                  partition per block, no global histograms
 //   k_level_wave   a level of nodes of <= 4096 members: one wavefront each
@@ -546,6 +549,210 @@ __global__ void __launch_bounds__(kBlock) k_select_last_wide(uint32_t depth, uin
   }
 }
 
+// ---------------------------------------------------------------- selection without launches
+
+// a value that is the same in every lane, kept in a scalar register
+__device__ __forceinline__ uint32_t uniform32(uint32_t x) {
+  return (uint32_t)__builtin_amdgcn_readfirstlane((int)x);
+}
+
+// One wavefront: the digit of a 256-bin histogram that holds `rank`, and the
+// rank among that digit's members.  False when the bins hold fewer members
+// (inconsistent counts, never expected).
+__device__ inline bool wave_digit(const uint32_t* bins, uint32_t rank, uint32_t* digit, uint32_t* rest) {
+  const uint32_t lane = threadIdx.x & 63;
+  const uint4 q = ((const uint4*)bins)[lane];
+  const uint32_t c[4] = {q.x, q.y, q.z, q.w};
+  uint32_t cum = q.x + q.y + q.z + q.w;
+  cum = wave_incl(cum) - cum;
+  uint32_t fb = 0, fj = 0;
+  bool found = false;
+#pragma unroll
+  for (int k = 0; k < 4; ++k) {
+    if (cum <= rank && rank < cum + c[k]) found = true, fb = lane * 4 + k, fj = rank - cum;
+    cum += c[k];
+  }
+  const uint64_t fm = __ballot(found);
+  if (fm == 0) return false;
+  const int fl = __builtin_ctzll(fm);  // exactly one lane finds the rank
+  *digit = (uint32_t)__builtin_amdgcn_readlane((int)fb, fl);
+  *rest = (uint32_t)__builtin_amdgcn_readlane((int)fj, fl);
+  return true;
+}
+
+// A digit's histogram of a global level: pass 1 .. np - 2 (LAST false), or
+// the last digit with a row of prefix counts per chunk (LAST).  Every
+// wavefront first finds the digit before it (its bins are one 1 KB read of a
+// line that all blocks of the node share); the node's first chunk keeps the
+// digits so far for the next kernel.  mid: the middle digits are found here
+// too, by passes over the whole node.
+template <typename KT, bool LAST>
+__device__ void fold_hist_body(uint32_t depth, uint32_t pass, const SetDesc& S, DevParams* P,
+                               const LevelCtx& c, const uint8_t* keys, NodeSel* sel, uint32_t* hist,
+                               uint32_t* rows, uint32_t* lh) {
+  const uint64_t n = S.n;
+  const uint32_t d = depth % S.dims;
+  const DigitPlan pl = digit_plan(P->G[d]);
+  const bool mid = LAST && depth >= S.mid_depth && pl.npass > 2;
+  if (LAST) pass = pl.npass - 1;
+  const uint32_t t = hist_index(S, P->G, depth) + (mid ? 1u : pass);  // the histogram built here
+  // (the stores to memory come last: before them every load of a uniform
+  // address is a scalar one)
+  const uint64_t nblk = c.sh.nodes * c.sh.chunks;
+  const uint64_t j = c.lb / c.sh.chunks, ch = c.lb % c.sh.chunks;
+  uint64_t st, sz;
+  node_span(n, depth, j, &st, &sz);
+  if (sz <= S.r) {
+    hist_clear(S, t + 1, LAST ? depth + 1 : depth, c.lb, nblk, hist);
+    return;
+  }
+  const KT* q = (const KT*)keys + (uint64_t)d * S.kst;
+  uint32_t prefix = 0, rank = (uint32_t)(sz >> 1);
+  bool ok = true;
+  if (pass > 0) {
+    uint32_t b = 0, rest = 0;
+    const uint32_t p0 = mid ? 0u : pass - 1;  // the digit found here
+    if (p0 > 0) {
+      const NodeSel ns = sel[((t - 1) & 1) * S.sel_half + j];
+      prefix = uniform32(ns.prefix), rank = uniform32(ns.rank);
+    }
+    ok = wave_digit(hist_region(S, t - 1, hist) + (j << 8), rank, &b, &rest);
+    prefix = (prefix << dp_width(pl, p0)) | b;
+    rank = rest;
+  }
+  lh[threadIdx.x] = 0;
+  __syncthreads();
+  if (mid)
+    for (uint32_t p = 1; p + 1 < pl.npass; ++p) {
+      const uint32_t w = dp_width(pl, p), sh = dp_shift(pl, p), hs = sh + w, mask = (1u << w) - 1;
+      scan_codes(q, st, st + sz, [&](uint32_t v) {
+        if ((v >> hs) == prefix) atomicAdd(&lh[(v >> sh) & mask], 1u);
+      });
+      __syncthreads();
+      uint32_t b = 0, rest = 0;
+      ok = ok && wave_digit(lh, rank, &b, &rest);
+      prefix = (prefix << w) | b;
+      rank = rest;
+      __syncthreads();  // every wavefront has read the bins
+      lh[threadIdx.x] = 0;
+      __syncthreads();
+    }
+  uint32_t* const bins = hist_region(S, t, hist) + (j << 8);
+  const uint32_t w = dp_width(pl, pass), sh = dp_shift(pl, pass), hs = sh + w;
+  const uint32_t nb = 1u << w, mask = nb - 1;
+  const uint64_t beg64 = ch * (uint64_t)c.sh.chunk_elems;
+  const uint64_t A = st + (beg64 < sz ? beg64 : sz);
+  const uint64_t B = st + (beg64 + c.sh.chunk_elems < sz ? beg64 + c.sh.chunk_elems : sz);
+  uint32_t below = 0;
+  scan_codes(q, A, B, [&](uint32_t v) {
+    const uint32_t hi = v >> hs;
+    if (LAST) below += hi < prefix ? 1u : 0u;
+    if (hi == prefix) atomicAdd(&lh[(v >> sh) & mask], 1u);
+  });
+  __syncthreads();
+  const uint32_t cnt = threadIdx.x < nb ? lh[threadIdx.x] : 0u;
+  if (LAST) {
+    uint64_t tot;
+    const uint64_t ex = block_exscan_u64(((uint64_t)below << 32) | cnt, &tot);
+    uint32_t* row = rows + c.lb * kRowStride;
+    row[threadIdx.x] = (uint32_t)ex;  // candidates with a smaller last digit
+    if (threadIdx.x == 0) {
+      row[256] = (uint32_t)tot;          // all candidates of the chunk
+      row[257] = (uint32_t)(tot >> 32);  // members below the prefix
+    }
+  }
+  if (threadIdx.x < nb && cnt) atomicAdd(&bins[threadIdx.x], cnt);
+  if (ch == 0 && threadIdx.x == 0) {
+    if (!ok) check_failed(P, kChkLastDigit);
+    NodeSel ns;
+    ns.prefix = prefix;
+    ns.rank = rank;
+    ns.v = 0;
+    ns.jeq = 0;
+    sel[(t & 1) * S.sel_half + j] = ns;
+  }
+  hist_clear(S, t + 1, LAST ? depth + 1 : depth, c.lb, nblk, hist);
+}
+
+template <bool LAST>
+__device__ __forceinline__ void fold_hist_block(uint32_t depth, uint32_t pass, uint32_t nsets, const uint64_t* pre,
+                                                const SetDesc* sets, DevParams* params, const uint8_t* keys0,
+                                                const uint8_t* keys1, NodeSel* sel0, uint32_t* hist0,
+                                                uint32_t* rows0, uint32_t* lh, uint64_t vb) {
+  const LevelCtx c = level_ctx(nsets, pre, sets, depth, vb);
+  const SetDesc& S = sets[c.s];
+  DevParams* P = params + c.s;
+  if (P->status != BBX_OK || level_is_local(S.n, depth)) return;
+  if (!LAST && (depth >= S.mid_depth || pass + 1 >= digit_passes(P->G[depth % S.dims]))) return;
+  const uint8_t* keys = (key_buf(S, depth) ? keys1 : keys0) + S.key_off;
+  NodeSel* sel = sel0 + S.sel_off;
+  if (P->key16)
+    fold_hist_body<uint16_t, LAST>(depth, pass, S, P, c, keys, sel, hist0 + S.hist_off, rows0 + S.rows_off, lh);
+  else
+    fold_hist_body<uint32_t, LAST>(depth, pass, S, P, c, keys, sel, hist0 + S.hist_off, rows0 + S.rows_off, lh);
+}
+
+// a block per chunk
+__global__ void __launch_bounds__(kBlock) k_fold_last(uint32_t depth, uint32_t nsets, const uint64_t* pre,
+                                                      const SetDesc* sets, DevParams* params,
+                                                      const uint8_t* keys0, const uint8_t* keys1,
+                                                      NodeSel* sel0, uint32_t* hist0, uint32_t* rows0) {
+  __shared__ __align__(16) uint32_t lh[kHistBins];
+  fold_hist_block<true>(depth, 0u, nsets, pre, sets, params, keys0, keys1, sel0, hist0, rows0, lh, blockIdx.x);
+}
+
+// a capped grid over the chunks of the sets that need the pass
+__global__ void __launch_bounds__(kBlock) k_fold_mid(uint32_t depth, uint32_t pass, uint32_t nsets,
+                                                     const uint64_t* pre, const SetDesc* sets,
+                                                     DevParams* params, const uint8_t* keys0,
+                                                     const uint8_t* keys1, NodeSel* sel0, uint32_t* hist0,
+                                                     const uint32_t* pass_need) {
+  if (!pass_need[depth * 4 + pass]) return;
+  __shared__ __align__(16) uint32_t lh[kHistBins];
+  const uint64_t total = pre[nsets];
+  for (uint64_t vb = blockIdx.x; vb < total; vb += gridDim.x) {  // block-uniform
+    fold_hist_block<false>(depth, pass, nsets, pre, sets, params, keys0, keys1, sel0, hist0, nullptr, lh, vb);
+    __syncthreads();  // the bins are used again
+  }
+}
+
+// The partition's side of it: the median code v and how many members equal
+// to it go left (jeq), from the last digit's histogram t, and the members
+// below v and equal to v in the node's chunks before this one, from their
+// rows (a block at most 4 rows per thread for the 1,024 chunks of a set alone).
+__device__ inline bool fold_select(uint32_t depth, const SetDesc& S, const DevParams* P, const LevelCtx& c,
+                                   uint32_t t, const NodeSel* sel, uint32_t* hist, const uint32_t* rows,
+                                   uint32_t* v, uint32_t* jeq, uint32_t* lt_run, uint32_t* eq_run) {
+  __shared__ uint32_t part[kBlock / 64][2];
+  const uint64_t j = c.lb / c.sh.chunks, ch = c.lb % c.sh.chunks;
+  const DigitPlan pl = digit_plan(P->G[depth % S.dims]);
+  const NodeSel ns = sel[(t & 1) * S.sel_half + j];
+  uint32_t b = 0, rest = 0;
+  const bool ok = wave_digit(hist_region(S, t, hist) + (j << 8), uniform32(ns.rank), &b, &rest);
+  *v = (uniform32(ns.prefix) << dp_width(pl, pl.npass - 1)) | b;
+  *jeq = rest;
+  uint32_t lt = 0, eq = 0;
+  if (c.sh.chunks > 1) {  // (uniform over the launch's blocks of this set)
+    const uint32_t* r0 = rows + j * c.sh.chunks * kRowStride;
+    for (uint64_t x = threadIdx.x; x < ch; x += kBlock) {
+      const uint32_t* row = r0 + x * kRowStride;
+      const uint32_t lo = row[b], hi = row[b + 1];
+      lt += row[257] + lo;
+      eq += hi - lo;
+    }
+    lt = (uint32_t)__builtin_amdgcn_readlane((int)wave_incl(lt), 63);
+    eq = (uint32_t)__builtin_amdgcn_readlane((int)wave_incl(eq), 63);
+    if ((threadIdx.x & 63) == 0) part[threadIdx.x >> 6][0] = lt, part[threadIdx.x >> 6][1] = eq;
+    __syncthreads();
+    lt = eq = 0;
+#pragma unroll
+    for (uint32_t k = 0; k < kBlock / 64; ++k) lt += part[k][0], eq += part[k][1];
+  }
+  *lt_run = uniform32(lt);
+  *eq_run = uniform32(eq);
+  return ok;
+}
+
 // The next level's first-digit bins while a chunk is partitioned: kLhCopies
 // copies per child (lane mod kLhCopies picks one), each 257 words apart so
 // that equal bins of different copies sit in different LDS banks; few bins
@@ -784,7 +991,8 @@ template <typename KT, bool TRACK, bool STAGE>
 __device__ void scatter_body(uint32_t depth, const SetDesc& S, DevParams* P, const LevelCtx& c,
                              uint32_t v, uint32_t jeq, uint32_t lt_run, uint32_t eq_run,
                              const uint8_t* src, uint8_t* dst, const uint32_t* isrc, uint32_t* idst,
-                             uint32_t* hist, uint32_t* lhist, uint32_t* stg) {
+                             uint32_t* next_hist, uint32_t* lhist, uint32_t* stg) {
+  // next_hist: the bins of level depth + 1's nodes
   static_assert(kBlock == 256, "four wavefronts per block");
   const uint64_t n = S.n, kst = S.kst;
   const uint32_t dims = S.dims, r = S.r;
@@ -847,7 +1055,7 @@ __device__ void scatter_body(uint32_t depth, const SetDesc& S, DevParams* P, con
 #pragma unroll
       for (uint32_t cp = 0; cp < kLhCopies; ++cp)
         cnum += lhist[(child * kLhCopies + cp) * kLhStride + threadIdx.x];
-      if (cnum) atomicAdd(&hist_level(S, depth + 1, hist)[((2 * j + child) << 8) + threadIdx.x], cnum);
+      if (cnum) atomicAdd(&next_hist[((2 * j + child) << 8) + threadIdx.x], cnum);
     }
   }
 }
@@ -856,12 +1064,14 @@ __device__ void scatter_body(uint32_t depth, const SetDesc& S, DevParams* P, con
 // STAGE: groups are staged in LDS before the stores (levels whose chunks hold
 // many groups; with one or two groups per block the extra barrier and LDS
 // round trip cost more than the coalesced stores save).
+// fold: the medians and chunk bases come from the histogram and rows of the
+// kernel before (fold_select); else from select launches (sel, cb).
 template <bool TRACK, bool STAGE>
-__global__ void __launch_bounds__(kBlock) k_scatter(uint32_t depth, uint32_t nsets,
+__global__ void __launch_bounds__(kBlock) k_scatter(uint32_t depth, uint32_t fold, uint32_t nsets,
                                                     const uint64_t* pre, const SetDesc* sets,
                                                     DevParams* params, const NodeSel* sel0,
-                                                    const uint32_t* cb0, uint8_t* src0,
-                                                    uint8_t* dst0, uint32_t* isrc0,
+                                                    const uint32_t* cb0, const uint32_t* rows0,
+                                                    uint8_t* src0, uint8_t* dst0, uint32_t* isrc0,
                                                     uint32_t* idst0, uint32_t* hist0) {
   const LevelCtx c = level_ctx(nsets, pre, sets, depth);
   const SetDesc& S = sets[c.s];
@@ -873,14 +1083,42 @@ __global__ void __launch_bounds__(kBlock) k_scatter(uint32_t depth, uint32_t nse
   level_bufs(S, depth, src0, dst0, isrc0, idst0);
   const uint32_t* isrc = S.track ? isrc0 + S.idx_off : nullptr;
   uint32_t* idst = S.track ? idst0 + S.idx_off : nullptr;
-  const NodeSel ns = sel_level(S, depth, sel0)[c.lb / c.sh.chunks];
-  const uint32_t* cb = cb_level(S, depth, cb0) + c.lb * 2;
+  uint32_t* const hist = hist0 + S.hist_off;
+  uint32_t v, jeq, lt_run, eq_run;
+  uint32_t* next_hist;
+  if (fold) {
+    const uint32_t t1 = hist_index(S, P->G, depth + 1);  // the next level's first histogram
+    next_hist = hist_region(S, t1, hist);
+    v = jeq = lt_run = eq_run = 0;
+    uint64_t st, sz;
+    node_span(S.n, depth, c.lb / c.sh.chunks, &st, &sz);
+    if (sz > S.r && !fold_select(depth, S, P, c, t1 - 1, sel0 + S.sel_off, hist, rows0 + S.rows_off, &v, &jeq,
+                                 &lt_run, &eq_run)) {
+      if (threadIdx.x == 0) check_failed(P, kChkLastDigit);
+      return;
+    }
+  } else {
+    next_hist = hist_level(S, depth + 1, hist);
+    const NodeSel ns = sel_level(S, depth, sel0)[c.lb / c.sh.chunks];
+    const uint32_t* cb = cb_level(S, depth, cb0) + c.lb * 2;
+    v = ns.v, jeq = ns.jeq, lt_run = cb[0], eq_run = cb[1];
+  }
   if (P->key16)
-    scatter_body<uint16_t, TRACK, STAGE>(depth, S, P, c, ns.v, ns.jeq, cb[0], cb[1], src0 + S.key_off,
-                                        dst0 + S.key_off, isrc, idst, hist0 + S.hist_off, lhist, stg);
+    scatter_body<uint16_t, TRACK, STAGE>(depth, S, P, c, v, jeq, lt_run, eq_run, src0 + S.key_off,
+                                        dst0 + S.key_off, isrc, idst, next_hist, lhist, stg);
   else
-    scatter_body<uint32_t, TRACK, STAGE>(depth, S, P, c, ns.v, ns.jeq, cb[0], cb[1], src0 + S.key_off,
-                                        dst0 + S.key_off, isrc, idst, hist0 + S.hist_off, lhist, stg);
+    scatter_body<uint32_t, TRACK, STAGE>(depth, S, P, c, v, jeq, lt_run, eq_run, src0 + S.key_off,
+                                        dst0 + S.key_off, isrc, idst, next_hist, lhist, stg);
+  if (fold) {
+    // the histogram after the one built here: the next level's second digit,
+    // or (block-local) the level after it
+    const uint32_t t1 = hist_index(S, P->G, depth + 1);
+    const uint64_t nblk = c.sh.nodes * c.sh.chunks;
+    if (depth + 1 >= S.nglobal)
+      hist_clear(S, t1 + 1, depth + 2, c.lb, nblk, hist);
+    else if (digit_passes(P->G[(depth + 1) % S.dims]) > 1)
+      hist_clear(S, t1 + 1, depth + 1, c.lb, nblk, hist);
+  }
 }
 
 // Median of one node's axis codes, inside one block: radix passes of at most
@@ -963,7 +1201,7 @@ __device__ void local_median(const KT* axis, uint64_t A, uint64_t B, uint32_t ra
 
 // A level whose nodes each fit one block: median and stable partition of
 // each node in one block, for every set whose level is local.
-__global__ void __launch_bounds__(kBlock) k_level_local(uint32_t depth, uint32_t nsets,
+__global__ void __launch_bounds__(kBlock) k_level_local(uint32_t depth, uint32_t fold, uint32_t nsets,
                                                         const uint64_t* pre, const SetDesc* sets,
                                                         DevParams* params, uint8_t* src0,
                                                         uint8_t* dst0, uint32_t* isrc0,
@@ -983,12 +1221,23 @@ __global__ void __launch_bounds__(kBlock) k_level_local(uint32_t depth, uint32_t
   uint32_t v = 0, jeq = 0;
   const uint32_t d = depth % S.dims;
   const uint8_t* keys = src0 + S.key_off;
+  uint32_t* const hist = hist0 + S.hist_off;
+  uint32_t* this_hist = nullptr;
+  uint32_t* next_hist = nullptr;
+  if (fold) {
+    const uint32_t t = hist_index(S, P->G, depth);
+    this_hist = hist_region(S, t, hist);
+    next_hist = hist_region(S, t + 1, hist);
+  } else {
+    this_hist = hist_level(S, depth, hist);
+    next_hist = hist_level(S, depth + 1, hist);
+  }
   if (sz > S.r) {
     const DigitPlan pl = digit_plan(P->G[d]);
     // the level above built this node's first-digit histogram when the code
     // has more than one digit (depth 0 has none for a block-local level)
     uint32_t* h = depth > 0 && pl.npass >= 2
-                      ? hist_level(S, depth, hist0 + S.hist_off) + (c.lb << 8) : nullptr;
+                      ? this_hist + (c.lb << 8) : nullptr;
     if (P->key16)
       local_median((const uint16_t*)keys + (uint64_t)d * S.kst, st, st + sz, (uint32_t)(sz >> 1), &v,
                    &jeq, lhist, red, h, pl);
@@ -999,12 +1248,11 @@ __global__ void __launch_bounds__(kBlock) k_level_local(uint32_t depth, uint32_t
   }
   if (P->key16)
     scatter_body<uint16_t, false, false>(depth, S, P, c, v, jeq, 0, 0, src0 + S.key_off,
-                                         dst0 + S.key_off, isrc, idst, hist0 + S.hist_off, lhist,
-                                         nullptr);
+                                         dst0 + S.key_off, isrc, idst, next_hist, lhist, nullptr);
   else
     scatter_body<uint32_t, false, false>(depth, S, P, c, v, jeq, 0, 0, src0 + S.key_off,
-                                         dst0 + S.key_off, isrc, idst, hist0 + S.hist_off, lhist,
-                                         nullptr);
+                                         dst0 + S.key_off, isrc, idst, next_hist, lhist, nullptr);
+  if (fold) hist_clear(S, hist_index(S, P->G, depth) + 2, depth + 2, c.lb, c.sh.nodes, hist);
 }
 
 // Median of a node's axis codes by one wavefront (nodes of at most kWaveNode
@@ -2354,10 +2602,19 @@ hipError_t launch_pair(const BatchPlan& bp, const Ws& w, uint32_t k, hipStream_t
   return hipGetLastError();
 }
 
+static void launch_scatter(const BatchPlan& bp, const Ws& w, uint32_t k, hipStream_t s) {
+  BBX_LAUNCH("level_scatter",
+             (bp.track ? (bp.scat_stage[k] ? k_scatter<true, true> : k_scatter<true, false>)
+                       : (bp.scat_stage[k] ? k_scatter<false, true> : k_scatter<false, false>)),
+             bp.g_lv[k], kBlock, 0, s, k, bp.fold, bp.nsets, w.pre + bp.o_lv[k], w.sets, w.params, w.sel,
+             w.chunk_base, w.rows, w.keys[0], w.keys[1], w.idx[0], w.idx[1], w.hist);
+}
+
 hipError_t launch_levels(const BatchPlan& bp, const Ws& w, hipStream_t s) {
   if (bp.max_gl == 0) return hipGetLastError();
-  BBX_LAUNCH("level_pass_flags", k_pass_flags, 1, kBlock, 0, s, bp.nsets, w.sets, w.params,
-             w.pass_need);
+  if (!bp.fold)
+    BBX_LAUNCH("level_pass_flags", k_pass_flags, 1, kBlock, 0, s, bp.nsets, w.sets, w.params,
+               w.pass_need);
   // every level kernel gets buffer 0 and buffer 1 and picks, per set, the
   // one that holds the codes (paired levels shift it)
   uint8_t* K0 = w.keys[0];
@@ -2368,7 +2625,7 @@ hipError_t launch_levels(const BatchPlan& bp, const Ws& w, hipStream_t s) {
     const uint64_t* plv = w.pre + bp.o_lv[k];
     const uint64_t* pnd = w.pre + bp.o_nd[k];
     if (bp.lv_local[k])
-      BBX_LAUNCH("level_local", k_level_local, bp.g_lc[k], kBlock, 0, s, k, bp.nsets,
+      BBX_LAUNCH("level_local", k_level_local, bp.g_lc[k], kBlock, 0, s, k, bp.fold, bp.nsets,
                  w.pre + bp.o_lc[k], w.sets, w.params, K0, K1, I0, I1, w.hist);
     if (bp.lv_wave[k])
       BBX_LAUNCH("level_wave", bp.track ? k_level_wave<true> : k_level_wave<false>,
@@ -2388,6 +2645,15 @@ hipError_t launch_levels(const BatchPlan& bp, const Ws& w, hipStream_t s) {
                  bp.g_f16[k], fused_threads<16>(), 0, s, k, bp.nsets, w.pre + bp.o_f16[k], w.sets,
                  w.params, K0, K1, I0, I1);
     if (!bp.lv_global[k]) continue;
+    if (bp.fold) {
+      for (uint32_t pass = 1; pass < 3 && bp.lv_mid[k]; ++pass)
+        BBX_LAUNCH("level_hist_mid", k_fold_mid, bp.g_lv[k] < 2048 ? bp.g_lv[k] : 2048, kBlock, 0, s, k,
+                   pass, bp.nsets, plv, w.sets, w.params, K0, K1, w.sel, w.hist, w.pass_need);
+      BBX_LAUNCH("level_hist_last", k_fold_last, bp.g_lv[k], kBlock, 0, s, k, bp.nsets, plv, w.sets,
+                 w.params, K0, K1, w.sel, w.hist, w.rows);
+      launch_scatter(bp, w, k, s);
+      continue;
+    }
     // mid passes: pass 0 was built by the quantize pass (depth 0) or by the
     // previous scatter
     for (uint32_t pass = 0; pass < 3; ++pass) {
@@ -2406,12 +2672,7 @@ hipError_t launch_levels(const BatchPlan& bp, const Ws& w, hipStream_t s) {
     else
       BBX_LAUNCH("level_select_last", k_select_last, sel_grid(bp.g_nd[k]), kBlock, 0, s, k, 0u,
                  bp.nsets, pnd, w.sets, w.params, w.sel, w.hist, w.rows, w.chunk_base);
-    if (bp.lv_single[k])
-      BBX_LAUNCH("level_scatter",
-                 (bp.track ? (bp.scat_stage[k] ? k_scatter<true, true> : k_scatter<true, false>)
-                           : (bp.scat_stage[k] ? k_scatter<false, true> : k_scatter<false, false>)),
-                 bp.g_lv[k], kBlock, 0, s, k, bp.nsets, plv, w.sets, w.params, w.sel, w.chunk_base,
-                 K0, K1, I0, I1, w.hist);
+    if (bp.lv_single[k]) launch_scatter(bp, w, k, s);
     if (bp.lv_pair[k]) {
       const hipError_t e = launch_pair(bp, w, k, s);
       if (e != hipSuccess) return e;

@@ -110,9 +110,17 @@ __device__ void minmax_body(const T* __restrict__ pos, uint64_t n, uint32_t dims
   }
 }
 
-// partials layout per block: lo[3], hi[3], bad, unused (8 doubles)
+// partials layout per block: lo[3], hi[3], bad, unused (8 doubles).  The first
+// block also clears what later kernels of the call count in: the levels'
+// pass flags (set by k_epilogue), the lossless list and the deferred tiles.
 __global__ void __launch_bounds__(kBlock) k_minmax(uint32_t nsets, const uint64_t* pre,
-                                                   const SetDesc* sets, double* partials) {
+                                                   const SetDesc* sets, double* partials,
+                                                   uint32_t* pass_need, uint32_t* lossless,
+                                                   uint32_t* tile_defer) {
+  if (blockIdx.x == 0) {
+    if (threadIdx.x < 4 * kMaxDepth) pass_need[threadIdx.x] = 0;
+    if (threadIdx.x == 0) lossless[0] = 0, tile_defer[0] = 0;
+  }
   const uint32_t s = find_set(pre, nsets, blockIdx.x);
   const SetDesc& S = sets[s];
   const uint64_t lb = blockIdx.x - pre[s];
@@ -125,10 +133,16 @@ __global__ void __launch_bounds__(kBlock) k_minmax(uint32_t nsets, const uint64_
     minmax_body<double>((const double*)S.pos, n, dims, layout, lb, mmb, part);
 }
 
+// fold: the set's first two histograms are cleared here (the later ones by the
+// level kernels), and the level passes it needs are flagged (k_fold_mid's
+// launches for passes that no set needs exit at their first instruction).
 __global__ void __launch_bounds__(kBlock) k_epilogue(const SetDesc* sets, const double* partials,
-                                                     DevParams* params) {
+                                                     DevParams* params, uint32_t fold, uint32_t* hist0,
+                                                     uint32_t* pass_need) {
   const SetDesc& S = sets[blockIdx.x];
   DevParams* P = params + blockIdx.x;
+  if (fold && S.nbins > 0)
+    for (uint32_t t = 0; t < 2; ++t) hist_region(S, t, hist0 + S.hist_off)[threadIdx.x] = 0;
   __shared__ double red[7][kBlock / 64];
   double v[7];
   for (int f = 0; f < 7; ++f) v[f] = f < 3 ? INFINITY : (f < 6 ? -INFINITY : 0.0);
@@ -236,6 +250,11 @@ __global__ void __launch_bounds__(kBlock) k_epilogue(const SetDesc* sets, const 
     }
   }
   *P = p;
+  if (fold)
+    for (uint32_t k = 0; k < S.nglobal; ++k) {
+      const uint32_t np = digit_passes(p.G[k % dims]);
+      for (uint32_t q = 1; q + 1 < np; ++q) atomicOr(&pass_need[k * 4 + q], 1u);
+    }
 }
 
 // Copies of the root bins (a lane uses one of them; a word apart beyond the
@@ -369,13 +388,15 @@ __global__ void __launch_bounds__(kBlock) k_hist_zero(uint64_t entries, uint32_t
 hipError_t launch_range(const BatchPlan& bp, const Ws& w, hipStream_t s) {
   if (bp.g_mm > 0)
     BBX_LAUNCH("range_minmax", k_minmax, bp.g_mm, kBlock, 0, s, bp.nsets, w.pre + bp.o_mm, w.sets,
-               w.partials);
-  BBX_LAUNCH("range_epilogue", k_epilogue, bp.nsets, kBlock, 0, s, w.sets, w.partials, w.params);
-  // histogram bins start at zero (the quantize pass adds the root histogram;
-  // every select kernel re-zeroes the bins it reads)
-  if (bp.hist_entries > 0)
+               w.partials, w.pass_need, w.lossless, w.tile_defer);
+  else
+    BBX_LAUNCH("lossless_zero", k_hist_zero, 1, 64, 0, s, (uint64_t)1, w.lossless);  // list count
+  BBX_LAUNCH("range_epilogue", k_epilogue, bp.nsets, kBlock, 0, s, w.sets, w.partials, w.params, bp.fold,
+             w.hist, w.pass_need);
+  // with paired levels the histogram bins start at zero (the quantize pass
+  // adds the root histogram; every select kernel re-zeroes the bins it reads)
+  if (!bp.fold && bp.hist_entries > 0)
     BBX_LAUNCH("level_hist_zero", k_hist_zero, 1024, kBlock, 0, s, bp.hist_entries, w.hist);
-  BBX_LAUNCH("lossless_zero", k_hist_zero, 1, 64, 0, s, (uint64_t)1, w.lossless);  // list count
   if (bp.g_qz > 0)
     BBX_LAUNCH("quantize", k_quantize, bp.g_qz, kBlock, 0, s, bp.nsets, w.pre + bp.o_qz, w.sets,
                w.params, w.keys[0], w.idx[0], w.hist);

@@ -662,10 +662,6 @@ __global__ void __launch_bounds__(64) k_tile_wide(uint32_t nsets, const uint64_t
   }
 }
 
-__global__ void k_zero_u32(uint32_t* p) {
-  if (threadIdx.x == 0) *p = 0;
-}
-
 // ---------------------------------------------------------------- big leaves
 
 __device__ inline uint32_t bmin_u32(uint32_t v, uint32_t* red) {
@@ -797,7 +793,6 @@ static void launch_tiles(const BatchPlan& bp, const Ws& w, hipStream_t s) {
 
 hipError_t launch_leaves(const BatchPlan& bp, const Ws& w, hipStream_t s) {
   if (bp.g_tile > 0) {
-    BBX_LAUNCH("tile_defer_zero", k_zero_u32, 1, 64, 0, s, w.tile_defer);
     if (bp.tile == 256)
       bp.track ? launch_tiles<256, true>(bp, w, s) : launch_tiles<256, false>(bp, w, s);
     else

@@ -101,3 +101,21 @@ def test_reduction_on_chip(bbx, orc, kind, n, dims, eb, r, kr):
     s, perm = bbx.compress(torch.from_numpy(pts).cuda(), eb, "rel", r, want_perm=True, reduce=kr)
     assert s.cpu().numpy().tobytes() == want
     assert np.array_equal(perm.cpu().numpy().astype(np.uint32), want_perm)
+
+
+# Global levels whose selections are found in the next kernel: codes of one
+# to four digits on axes of different widths, nodes on both sides of the size
+# below which a block takes the middle digits by itself, many and few chunks,
+# levels above and below block-local ones, and a batch (no such size).
+@pytest.mark.parametrize("n", [4097 * 4, 32768 * 2, 32768 * 2 + 5, 65537 * 2 + 1])
+@pytest.mark.parametrize("eb,span", [(1e-2, (1, 1, 1)), (1e-4, (1, 1e-3, 1e-1)), (1e-6, (1, 1, 1)),
+                                     (2e-9, (1, 1e-5, 1)), (1e-8, (1e-4, 1, 1e-6))])
+def test_global_level_digits(bbx, orc, n, eb, span):
+    pts = gen("cosmology", n, 3, np.float64, seed=n % 1000) * np.asarray(span)
+    ref = orc.compress(pts, eb, "rel", 32, want_perm=True)
+    for blocks in (0, 3):
+        check_parity(orc, bbx, pts, eb, "rel", 32, level_blocks=blocks, want_perm=blocks == 0, ref=ref)
+    x = torch.from_numpy(pts).cuda()
+    for got in bbx.BatchCompressor([{"pos": x, "eb": eb}, {"pos": x[: n // 3].contiguous(), "eb": eb},
+                                    {"pos": x, "eb": eb, "level_pairs": int(n % 2)}])()[::2]:
+        assert got.cpu().numpy().tobytes() == ref[0]
