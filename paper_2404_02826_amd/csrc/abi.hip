@@ -693,70 +693,96 @@ static std::string check_plan(const SetIn* in, uint32_t nsets) {
   return std::string();
 }
 
-// A small descriptor blob travels as a kernel argument: no host-to-device
-// copy, so the host never waits for the stream and the upload can be
-// recorded in a graph.
-constexpr uint32_t kArgBlob = 2304;  // one set at any size fits
-struct ArgBlob {
-  uint32_t words;
-  uint32_t w[kArgBlob / 4];
-};
-
-__global__ void __launch_bounds__(kBlock) k_put_blob(ArgBlob b, uint32_t* dst) {
+__global__ void __launch_bounds__(kBlock) k_put_blob(ArgBlob b, uint64_t* dst) {
   for (uint32_t i = threadIdx.x; i < b.words; i += blockDim.x) dst[i] = b.w[i];
 }
 
-// Uploads descriptors and prefix arrays (stream-ordered).
-static bbx_status batch_upload(const SetIn* in, uint32_t nsets, void* d_ws, size_t ws_size,
-                               hipStream_t stream) {
+// A batch's plan with its descriptors as the workspace will hold them.
+struct Planned {
   BatchPlan bp;
   std::vector<SetDesc> descs;
   std::vector<uint64_t> pre;
   WsLayout lay;
-  plan_batch(in, nsets, &bp, &descs, &pre, &lay);
+};
+static bbx_status plan_in(const SetIn* in, uint32_t nsets, void* d_ws, size_t ws_size, Planned* p) {
+  plan_batch(in, nsets, &p->bp, &p->descs, &p->pre, &p->lay);
   if (!d_ws || ((uintptr_t)d_ws & 255)) return fail(BBX_EINVAL, "workspace must be 256-byte aligned");
-  if (ws_size < lay.total) return fail(BBX_ENOMEM, "workspace too small: need " + std::to_string(lay.total));
+  if (ws_size < p->lay.total) return fail(BBX_ENOMEM, "workspace too small: need " + std::to_string(p->lay.total));
   for (uint32_t s = 0; s < nsets; ++s)
-    if (seq_stream(descs[s]) && descs[s].n > 0)
-      descs[s].perm = (uint32_t*)((uint8_t*)d_ws + lay.red_perm) + descs[s].idx_off;
-  std::vector<uint8_t> blob(lay.pre + 8 * pre.size() - lay.sets);
-  memcpy(blob.data(), descs.data(), sizeof(SetDesc) * nsets);
-  memcpy(blob.data() + (lay.pre - lay.sets), pre.data(), 8 * pre.size());
-  if (blob.size() <= kArgBlob) {
-    ArgBlob ab;
-    memset(&ab, 0, sizeof(ab));
-    ab.words = (uint32_t)((blob.size() + 3) / 4);
-    memcpy(ab.w, blob.data(), blob.size());
-    BBX_LAUNCH("upload", k_put_blob, 1, kBlock, 0, stream, ab, (uint32_t*)((uint8_t*)d_ws + lay.sets));
+    if (seq_stream(p->descs[s]) && p->descs[s].n > 0)
+      p->descs[s].perm = (uint32_t*)((uint8_t*)d_ws + p->lay.red_perm) + p->descs[s].idx_off;
+  return BBX_OK;
+}
+
+// Descriptors and prefix arrays in one piece (the workspace from `sets` on).
+static size_t blob_bytes(const Planned& p) { return p.lay.pre + 8 * p.pre.size() - p.lay.sets; }
+static void fill_blob(const Planned& p, uint8_t* to) {
+  memcpy(to, p.descs.data(), sizeof(SetDesc) * p.descs.size());
+  memcpy(to + (p.lay.pre - p.lay.sets), p.pre.data(), 8 * p.pre.size());
+}
+static bool arg_blob(const Planned& p, ArgBlob* b) {
+  if (blob_bytes(p) > kArgBlob) return false;
+  memset(b, 0, sizeof(*b));
+  b->words = (blob_bytes(p) + 7) / 8;
+  fill_blob(p, (uint8_t*)b->w);
+  return true;
+}
+
+// Uploads descriptors and prefix arrays (stream-ordered).
+static bbx_status upload_planned(const Planned& p, void* d_ws, hipStream_t stream) {
+  ArgBlob ab;
+  if (arg_blob(p, &ab)) {
+    BBX_LAUNCH("upload", k_put_blob, 1, kBlock, 0, stream, ab, (uint64_t*)((uint8_t*)d_ws + p.lay.sets));
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return fail(BBX_EHIP, std::string("descriptor upload failed: ") + hipGetErrorString(e));
     return BBX_OK;
   }
-  hipError_t e = hipMemcpyAsync((uint8_t*)d_ws + lay.sets, blob.data(), blob.size(),
+  std::vector<uint8_t> blob(blob_bytes(p));
+  fill_blob(p, blob.data());
+  hipError_t e = hipMemcpyAsync((uint8_t*)d_ws + p.lay.sets, blob.data(), blob.size(),
                                 hipMemcpyHostToDevice, stream);
   if (e != hipSuccess) return fail(BBX_EHIP, std::string("descriptor upload failed: ") + hipGetErrorString(e));
   return BBX_OK;
 }
 
 // Enqueues every kernel of the batch; no host synchronization, no copies.
-static bbx_status batch_launch(const SetIn* in, uint32_t nsets, void* d_ws, size_t ws_size,
-                               hipStream_t stream) {
-  BatchPlan bp;
-  std::vector<SetDesc> descs;
-  std::vector<uint64_t> pre;
-  WsLayout lay;
-  plan_batch(in, nsets, &bp, &descs, &pre, &lay);
-  if (!d_ws || ((uintptr_t)d_ws & 255)) return fail(BBX_EINVAL, "workspace must be 256-byte aligned");
-  if (ws_size < lay.total) return fail(BBX_ENOMEM, "workspace too small: need " + std::to_string(lay.total));
-  const Ws w = carve_ws(lay, (uint8_t*)d_ws);
-  hipError_t e = launch_range(bp, w, stream);
-  if (e == hipSuccess) e = launch_split(bp, descs.data(), w, stream);
-  if (e == hipSuccess) e = launch_levels(bp, w, stream);
-  if (e == hipSuccess) e = launch_leaves(bp, w, stream);
-  if (e == hipSuccess) e = launch_reduce(bp, w, stream);
-  if (e == hipSuccess) e = launch_pack(bp, w, stream);
+// blob: the descriptors, when they are not in the workspace yet.
+static bbx_status launch_planned(const Planned& p, void* d_ws, const ArgBlob* blob, hipStream_t stream) {
+  const Ws w = carve_ws(p.lay, (uint8_t*)d_ws);
+  hipError_t e = launch_range(p.bp, w, blob, stream);
+  if (e == hipSuccess) e = launch_split(p.bp, p.descs.data(), w, stream);
+  if (e == hipSuccess) e = launch_levels(p.bp, w, stream);
+  if (e == hipSuccess) e = launch_leaves(p.bp, w, stream);
+  if (e == hipSuccess) e = launch_reduce(p.bp, w, stream);
+  if (e == hipSuccess) e = launch_pack(p.bp, w, stream);
   if (e != hipSuccess) return fail(BBX_EHIP, std::string("kernel launch failed: ") + hipGetErrorString(e));
   return BBX_OK;
+}
+
+static bbx_status batch_upload(const SetIn* in, uint32_t nsets, void* d_ws, size_t ws_size,
+                               hipStream_t stream) {
+  Planned p;
+  const bbx_status st = plan_in(in, nsets, d_ws, ws_size, &p);
+  return st != BBX_OK ? st : upload_planned(p, d_ws, stream);
+}
+
+static bbx_status batch_launch(const SetIn* in, uint32_t nsets, void* d_ws, size_t ws_size,
+                               hipStream_t stream) {
+  Planned p;
+  const bbx_status st = plan_in(in, nsets, d_ws, ws_size, &p);
+  return st != BBX_OK ? st : launch_planned(p, d_ws, nullptr, stream);
+}
+
+// Upload and launch with one plan; a set alone takes its descriptors along
+// with its first kernel instead of one before it.
+static bbx_status batch_run(const SetIn* in, uint32_t nsets, void* d_ws, size_t ws_size, hipStream_t stream) {
+  Planned p;
+  bbx_status st = plan_in(in, nsets, d_ws, ws_size, &p);
+  if (st != BBX_OK) return st;
+  ArgBlob ab;
+  if (nsets == 1 && p.bp.g_mm > 0 && arg_blob(p, &ab)) return launch_planned(p, d_ws, &ab, stream);
+  st = upload_planned(p, d_ws, stream);
+  return st != BBX_OK ? st : launch_planned(p, d_ws, nullptr, stream);
 }
 
 // ---------------------------------------------------------------- stream header
@@ -996,9 +1022,7 @@ bbx_status bbx_compress(const void* d_pos, uint64_t n, uint32_t dims, bbx_dtype 
   in.need_idx = true;  // same plan as bbx_compress_workspace_size
   st = check_set(in);
   if (st != BBX_OK) return st;
-  st = batch_upload(&in, 1, d_ws, ws_size, stream);
-  if (st != BBX_OK) return st;
-  st = batch_launch(&in, 1, d_ws, ws_size, stream);
+  st = batch_run(&in, 1, d_ws, ws_size, stream);
   if (st != BBX_OK) return st;
   if (h_out_size) {
     DevParams hp;
@@ -1073,9 +1097,11 @@ bbx_status bbx_batch_launch(const bbx_set* sets, uint32_t nsets, void* d_ws, siz
 
 bbx_status bbx_compress_batch(const bbx_set* sets, uint32_t nsets, void* d_ws, size_t ws_size,
                               hipStream_t stream) {
-  bbx_status st = bbx_batch_upload(sets, nsets, d_ws, ws_size, stream);
+  std::vector<SetIn> v;
+  if (!sets_from_abi(sets, nsets, &v)) return fail(BBX_EINVAL, "sets is NULL");
+  const bbx_status st = check_batch(v.data(), nsets);
   if (st != BBX_OK) return st;
-  return bbx_batch_launch(sets, nsets, d_ws, ws_size, stream);
+  return batch_run(v.data(), nsets, d_ws, ws_size, stream);
 }
 
 bbx_status bbx_plan_check(const bbx_set* sets, uint32_t nsets) {

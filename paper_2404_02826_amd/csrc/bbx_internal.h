@@ -711,8 +711,20 @@ uint64_t scan_blocks(uint64_t count);
 // Sets the calling thread's error message (bbx_last_error) and returns st.
 bbx_status set_error(bbx_status st, const char* msg);
 
+// A small descriptor blob (the set descriptors and prefix arrays as the
+// workspace holds them) travels as a kernel argument: no host-to-device copy,
+// so the host never waits for the stream and the upload can be recorded in a
+// graph.
+constexpr uint32_t kArgBlob = 2304;  // one set at any size fits
+struct ArgBlob {
+  uint64_t words;
+  uint64_t w[kArgBlob / 8];
+};
+
 // launchers (one group per translation unit)
-hipError_t launch_range(const BatchPlan& bp, const Ws& w, hipStream_t s);
+// blob: the descriptors of a set alone, still to be put in the workspace
+// (null: they are there)
+hipError_t launch_range(const BatchPlan& bp, const Ws& w, const ArgBlob* blob, hipStream_t s);
 hipError_t launch_levels(const BatchPlan& bp, const Ws& w, hipStream_t s);
 hipError_t launch_pair(const BatchPlan& bp, const Ws& w, uint32_t depth, hipStream_t s);
 hipError_t launch_leaves(const BatchPlan& bp, const Ws& w, hipStream_t s);

@@ -5,10 +5,16 @@
 //        exclusive prefix sum of the per-leaf payload bits over the whole
 //        batch (depth-first leaf order inside each set); a set's offsets are
 //        differences against its first leaf's offset
-//   k_set_sizes     per set: payload and meta bits, stream size, capacity check
-//   k_pack_meta     one thread per 64-bit meta word: gathers the fixed-stride
+//        (k_scan_down adds up the block totals before its own by itself up to
+//        kScanFold of them; k_scan_sizes does it all in one block for up to
+//        kScanOne leaves, and k_set_sizes's work with it: a small set's leaves
+//        are scanned faster than a launch starts)
+//   k_set_sizes     per set: payload and meta bits, stream size, capacity
+//                   check, the 128-byte header, and the size and status
+//   k_pack_meta, k_pack_payload, k_pack (both in one launch, for small sets):
+//   pack_meta       one thread per 64-bit meta word: gathers the fixed-stride
 //                   leaf records (widths, reference codes) that overlap it
-//   k_pack_payload  leaf-aligned blocks: each block owns the payload words
+//   pack_payload    leaf-aligned blocks: each block owns the payload words
 //                   that start inside its leaves, ORs every member code
 //                   q - q_ref + 2^(m-1) into an LDS copy of those words (LDS
 //                   atomics; 8 consecutive members per thread, assembled in
@@ -17,8 +23,6 @@
 //                   member per lane), then writes every owned word once with
 //                   a coalesced plain store (no global atomics, no zeroing of
 //                   the output)
-//   k_header        the 128-byte header
-//   k_finish        reports size and status
 #include "bbx_internal.h"
 
 namespace bbx {
@@ -91,9 +95,20 @@ __global__ void __launch_bounds__(kBlock) k_scan_top(uint64_t nparts, uint64_t* 
   }
 }
 
+// fold: part holds the block totals themselves (no k_scan_top before): each
+// block sums those before its own, and the last one also reports the total as
+// k_scan_top does.
+constexpr uint64_t kScanFold = 1024;
 __global__ void __launch_bounds__(kBlock) k_scan_down(uint64_t count, uint64_t* bits,
-                                                      const uint64_t* part, const DevParams* P) {
+                                                      const uint64_t* part, uint32_t fold, uint64_t* total,
+                                                      DevParams* P, uint64_t expect) {
   if (P && P->status != BBX_OK) return;
+  uint64_t before = fold ? 0 : part[blockIdx.x];
+  if (fold) {
+    uint64_t mine = 0;
+    for (uint32_t b = threadIdx.x; b < blockIdx.x; b += kBlock) mine += part[b];
+    (void)bexscan(mine, &before);
+  }
   const uint64_t base = blockIdx.x * kScanChunk + (uint64_t)threadIdx.x * kScanPer;
   uint64_t v[kScanPer];
   uint64_t s = 0;
@@ -102,20 +117,29 @@ __global__ void __launch_bounds__(kBlock) k_scan_down(uint64_t count, uint64_t* 
     s += v[k];
   }
   uint64_t tot;
-  uint64_t run = bexscan(s, &tot) + part[blockIdx.x];
+  uint64_t run = bexscan(s, &tot) + before;
   for (int k = 0; k < kScanPer; ++k)
     if (base + k < count) {
       bits[base + k] = run;
       run += v[k];
     }
+  if (fold && blockIdx.x == gridDim.x - 1 && threadIdx.x == 0) {
+    if (total) *total = before + tot;
+    if (P) {
+      if (before + tot != expect) P->status = BBX_ECORRUPT;
+      P->payload_bits = before + tot;
+    }
+  }
 }
 
 static hipError_t scan_launch(uint64_t count, uint64_t* bits, uint64_t* part, uint64_t* total,
                               DevParams* P, uint64_t expect, hipStream_t s) {
   const uint64_t nb = scan_blocks(count);
+  const uint32_t fold = nb > 0 && nb <= kScanFold;
   if (nb > 0) BBX_LAUNCH("scan_reduce", k_scan_reduce, nb, kBlock, 0, s, count, bits, part, P);
-  BBX_LAUNCH("scan_top", k_scan_top, 1, kBlock, 0, s, nb, part, total, P, expect);
-  if (nb > 0) BBX_LAUNCH("scan_down", k_scan_down, nb, kBlock, 0, s, count, bits, part, P);
+  if (!fold) BBX_LAUNCH("scan_top", k_scan_top, 1, kBlock, 0, s, nb, part, total, P, expect);
+  if (nb > 0)
+    BBX_LAUNCH("scan_down", k_scan_down, nb, kBlock, 0, s, count, bits, part, fold, total, P, expect);
   return hipGetLastError();
 }
 
@@ -124,12 +148,44 @@ hipError_t launch_dec_scan(uint64_t count, uint64_t* bits, uint64_t* part, DevPa
   return scan_launch(count, bits, part, nullptr, params, expect_payload, s);
 }
 
-// per set: payload/meta bits, stream size, capacity check
-__global__ void k_set_sizes(uint32_t nsets, const SetDesc* sets, DevParams* params,
-                            const uint64_t* off, uint64_t total_leaves, const uint64_t* total,
-                            uint32_t* lossless) {
-  const uint32_t s = blockIdx.x * blockDim.x + threadIdx.x;
-  if (s >= nsets) return;
+// The 128-byte header of a set whose stream is written.
+__device__ void write_header(const SetDesc& S, const DevParams* P) {
+  const bool lossless = P->status == kStatusLossless;
+  const uint32_t dims = S.dims;
+  uint64_t h[16];
+#pragma unroll
+  for (int k = 0; k < 16; ++k) h[k] = 0;
+  const uint64_t ver = lossless ? 3 : (seq_stream(S) ? 2 : 1);
+  h[0] = (uint64_t)kMagic | (ver << 32) | ((uint64_t)S.dtype << 48) | ((uint64_t)dims << 56);
+  h[1] = S.n;
+  h[3] = __double_as_longlong(P->eb_user);
+  h[4] = __double_as_longlong(P->eb_abs);
+  h[14] = P->payload_bits;
+  if (lossless) {  // no grid, no leaves, no meta section; no reference field
+    h[2] = (uint64_t)S.r | ((uint64_t)S.eb_mode << 32) | ((uint64_t)S.mbits << 56);
+  } else {
+    h[2] = (uint64_t)S.r | ((uint64_t)S.eb_mode << 32) | ((uint64_t)S.split << 40) |
+           ((uint64_t)S.ref_mode << 48) | ((uint64_t)S.mbits << 56);
+    h[5] = __double_as_longlong(P->eb_eff);
+    h[6] = __double_as_longlong(P->w);
+    h[7] = __double_as_longlong(P->inv_w);
+#pragma unroll
+    for (uint32_t d = 0; d < 3; ++d) h[8 + d] = d < dims ? __double_as_longlong(P->lo[d]) : 0;
+    h[11] = (uint64_t)P->G[0] | ((uint64_t)(dims > 1 ? P->G[1] : 0) << 8) |
+            ((uint64_t)(dims > 2 ? P->G[2] : 0) << 16);
+    h[12] = S.split ? P->nleaves : S.n_leaves;  // a split-rule partition's count is the device's
+    h[13] = P->meta_bits;
+    h[15] = seq_stream(S) ? P->nseq : 0;  // version 2: the sequence count
+  }
+  uint64_t* o = (uint64_t*)S.out;
+#pragma unroll
+  for (int k = 0; k < 16; ++k) o[k] = h[k];
+}
+
+// One set (one thread): payload/meta bits, stream size, capacity check, then
+// the header and the caller's size and status (nothing later can fail).
+__device__ void set_sizes(uint32_t s, const SetDesc* sets, DevParams* params, const uint64_t* off,
+                          uint64_t total_leaves, uint64_t total, uint32_t* lossless) {
   const SetDesc& S = sets[s];
   DevParams* P = params + s;
   if (P->status == kStatusLossless) {  // every coordinate as its bits, no meta section
@@ -140,24 +196,74 @@ __global__ void k_set_sizes(uint32_t nsets, const SetDesc* sets, DevParams* para
     if (P->total_bytes > S.out_cap)
       P->status = BBX_ENOSPC;
     else
-      lossless[1 + atomicAdd(lossless, 1u)] = s;  // for k_lossless
-    return;
+      lossless[1 + atomicAdd(lossless, 1u)] = s;  // its coordinates are copied by k_pack
+  } else if (P->status == BBX_OK) {
+    const uint64_t b = S.leaf_off, e = S.leaf_off + S.n_leaves;
+    const uint64_t base = S.n_leaves ? off[b] : 0;
+    const uint64_t endv = S.n_leaves ? (e < total_leaves ? off[e] : total) : 0;
+    uint32_t sumG = 0;  // reference field: codes, or original coordinates with ref_mode 1
+    for (uint32_t d = 0; d < S.dims; ++d) sumG += S.ref_mode ? coord_bits(S.dtype) : P->G[d];
+    // one record per leaf; with the bit box reduction one per sequence, with
+    // a 32-bit particle count
+    const uint64_t meta = seq_stream(S) ? P->nseq * (uint64_t)(S.dims * S.mbits + sumG + 32)
+                                        : S.n_leaves * (uint64_t)(S.dims * S.mbits + sumG);
+    P->payload_base = base;
+    P->meta_bits = meta;
+    P->payload_bits = endv - base;
+    P->total_bytes = kHeaderBytes + ((meta + 63) / 64) * 8 + ((P->payload_bits + 63) / 64) * 8;
+    if (P->total_bytes > S.out_cap) P->status = BBX_ENOSPC;
   }
-  if (P->status != BBX_OK) return;
-  const uint64_t b = S.leaf_off, e = S.leaf_off + S.n_leaves;
-  const uint64_t base = S.n_leaves ? off[b] : 0;
-  const uint64_t endv = S.n_leaves ? (e < total_leaves ? off[e] : *total) : 0;
-  uint32_t sumG = 0;  // reference field: codes, or original coordinates with ref_mode 1
-  for (uint32_t d = 0; d < S.dims; ++d) sumG += S.ref_mode ? coord_bits(S.dtype) : P->G[d];
-  // one record per leaf; with the bit box reduction one per sequence, with
-  // a 32-bit particle count
-  const uint64_t meta = seq_stream(S) ? P->nseq * (uint64_t)(S.dims * S.mbits + sumG + 32)
-                                 : S.n_leaves * (uint64_t)(S.dims * S.mbits + sumG);
-  P->payload_base = base;
-  P->meta_bits = meta;
-  P->payload_bits = endv - base;
-  P->total_bytes = kHeaderBytes + ((meta + 63) / 64) * 8 + ((P->payload_bits + 63) / 64) * 8;
-  if (P->total_bytes > S.out_cap) P->status = BBX_ENOSPC;
+  const uint32_t st = P->status == kStatusLossless ? (uint32_t)BBX_OK : P->status;
+  if (st == BBX_OK) write_header(S, P);
+  if (S.d_size) *S.d_size = st == BBX_OK ? P->total_bytes : ~0ull;
+  if (S.d_status) *S.d_status = st;
+}
+
+__global__ void k_set_sizes(uint32_t nsets, const SetDesc* sets, DevParams* params,
+                            const uint64_t* off, uint64_t total_leaves, const uint64_t* total,
+                            uint32_t* lossless) {
+  const uint32_t s = blockIdx.x * blockDim.x + threadIdx.x;
+  if (s < nsets) set_sizes(s, sets, params, off, total_leaves, *total, lossless);
+}
+
+// The scan and the set sizes of a batch of few leaves in one block.
+constexpr uint64_t kScanOne = 8192;
+constexpr uint32_t kScanThreads = 1024;
+__global__ void __launch_bounds__(kScanThreads) k_scan_sizes(uint32_t nsets, const SetDesc* sets,
+                                                             DevParams* params, uint64_t count, uint64_t* bits,
+                                                             uint32_t* lossless) {
+  constexpr uint32_t W = kScanThreads / 64, kPer = kScanOne / kScanThreads;
+  __shared__ uint64_t wsum[W];
+  const uint32_t lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+  const uint64_t base = (uint64_t)threadIdx.x * kPer;
+  uint64_t v[kPer], sum = 0;
+#pragma unroll
+  for (uint32_t k = 0; k < kPer; ++k) {
+    v[k] = base + k < count ? bits[base + k] : 0;
+    sum += v[k];
+  }
+  uint64_t x = sum;
+  for (int o = 1; o < 64; o <<= 1) {
+    const uint64_t y = __shfl_up(x, o);
+    if ((int)lane >= o) x += y;
+  }
+  if (lane == 63) wsum[wv] = x;
+  __syncthreads();
+  uint64_t run = x - sum, total = 0;
+#pragma unroll
+  for (uint32_t k = 0; k < W; ++k) {
+    run += k < wv ? wsum[k] : 0ull;
+    total += wsum[k];
+  }
+#pragma unroll
+  for (uint32_t k = 0; k < kPer; ++k)
+    if (base + k < count) {
+      bits[base + k] = run;
+      run += v[k];
+    }
+  __syncthreads();
+  for (uint32_t s = threadIdx.x; s < nsets; s += kScanThreads)
+    set_sizes(s, sets, params, bits, count, total, lossless);
 }
 
 // ---------------------------------------------------------------- packing
@@ -183,15 +289,15 @@ __device__ inline uint64_t ref_coord_bits(const SetDesc& S, uint32_t src, uint32
   return ((const uint64_t*)S.pos)[k];
 }
 
-__global__ void __launch_bounds__(kBlock) k_pack_meta(uint32_t nsets, const uint64_t* pre,
-                                                      const SetDesc* sets,
-                                                      const DevParams* params,
-                                                      const LeafRec* leaves0) {
-  const uint32_t s = find_set(pre, nsets, blockIdx.x);
+// (forced inline: a function that two kernels call is otherwise outlined, with
+// its uniform values in vector registers)
+__device__ __forceinline__ void pack_meta(uint32_t nsets, const uint64_t* pre, uint64_t vb, const SetDesc* sets,
+                          const DevParams* params, const LeafRec* leaves0) {
+  const uint32_t s = find_set(pre, nsets, vb);
   const SetDesc& S = sets[s];
   const DevParams* P = params + s;
   if (P->status != BBX_OK) return;
-  const uint64_t lb = blockIdx.x - pre[s], nblk = pre[s + 1] - pre[s];
+  const uint64_t lb = vb - pre[s], nblk = pre[s + 1] - pre[s];
   const uint32_t dims = S.dims, mbits = S.mbits;
   const uint32_t G[3] = {P->G[0], P->G[1], P->G[2]};
   const uint64_t nwords = (P->meta_bits + 63) / 64;
@@ -209,17 +315,24 @@ __global__ void __launch_bounds__(kBlock) k_pack_meta(uint32_t nsets, const uint
       for (uint64_t i = i0; i <= i1; ++i) {
         const LeafRec rec = leaves[i];
         uint64_t at = i * Sb;
-        for (uint32_t d = 0; d < dims; ++d, at += mbits)
+#pragma unroll
+        for (uint32_t d = 0; d < 3; ++d) {
+          if (d >= dims) break;
           or_into(word, b0, (rec.m >> (8 * d)) & 0xffu, at, mbits);
-        for (uint32_t d = 0; d < dims; ++d, at += M)
+          at += mbits;
+        }
+#pragma unroll
+        for (uint32_t d = 0; d < 3; ++d) {
+          if (d >= dims) break;
           or_into(word, b0, ref_coord_bits(S, rec.ref_src, d), at, M);
+          at += M;
+        }
       }
       meta[w] = word;
     }
     return;
   }
-  uint32_t Sb = dims * mbits;
-  for (uint32_t d = 0; d < dims; ++d) Sb += G[d];
+  uint32_t Sb = dims * mbits + G[0] + (dims > 1 ? G[1] : 0u) + (dims > 2 ? G[2] : 0u);
   for (uint64_t w = lb * blockDim.x + threadIdx.x; w < nwords; w += nblk * blockDim.x) {
     const uint64_t b0 = w * 64;
     const uint64_t i0 = b0 / Sb;
@@ -230,11 +343,15 @@ __global__ void __launch_bounds__(kBlock) k_pack_meta(uint32_t nsets, const uint
       const LeafRec rec = leaves[i];
       u128 v = 0;
       uint32_t at = 0;
-      for (uint32_t d = 0; d < dims; ++d) {
+#pragma unroll
+      for (uint32_t d = 0; d < 3; ++d) {
+        if (d >= dims) break;
         v |= (u128)((rec.m >> (8 * d)) & 0xffu) << at;
         at += mbits;
       }
-      for (uint32_t d = 0; d < dims; ++d) {
+#pragma unroll
+      for (uint32_t d = 0; d < 3; ++d) {
+        if (d >= dims) break;
         v |= (u128)rec.qref[d] << at;
         at += G[d];
       }
@@ -316,7 +433,7 @@ constexpr uint32_t kPackLdsWords = 3072;  // payload words of one block's member
 // adds those few members from global memory.  Blocks whose bits exceed the LDS
 // copy (very large leaves) assemble each word from global memory instead.
 template <typename KT>
-__device__ void pack_payload_body(const SetDesc& S, const DevParams* P, uint64_t blk,
+__device__ __forceinline__ void pack_payload_body(const SetDesc& S, const DevParams* P, uint64_t blk,
                                   const LeafRec* leaves, const uint64_t* off, const KT* keys,
                                   LeafRec* s_rec, uint64_t* s_off, unsigned long long* s_w) {
   const uint64_t kst = S.kst, nl = S.n_leaves, base = P->payload_base, pbits = P->payload_bits;
@@ -519,22 +636,16 @@ __device__ void pack_payload_body(const SetDesc& S, const DevParams* P, uint64_t
   for (uint64_t w = w_first + threadIdx.x; w < w_end; w += kBlock) pay[w] = s_w[w - wlo];
 }
 
-__global__ void __launch_bounds__(kBlock) k_pack_payload(uint32_t nsets, const uint64_t* pre,
-                                                         const SetDesc* sets,
-                                                         const DevParams* params,
-                                                         const LeafRec* leaves0,
-                                                         const uint64_t* off0,
-                                                         const uint8_t* keys0,
-                                                         const uint8_t* keys1) {
-  const uint32_t s = find_set(pre, nsets, blockIdx.x);
+__device__ __forceinline__ void pack_payload(uint32_t nsets, const uint64_t* pre, uint64_t vb, const SetDesc* sets,
+                             const DevParams* params, const LeafRec* leaves0, const uint64_t* off0,
+                             const uint8_t* keys0, const uint8_t* keys1, LeafRec* s_rec, uint64_t* s_off,
+                             unsigned long long* s_w) {
+  const uint32_t s = find_set(pre, nsets, vb);
   const SetDesc& S = sets[s];
   const DevParams* P = params + s;
   if (P->status != BBX_OK) return;
   if (P->payload_bits == 0) return;
-  __shared__ LeafRec s_rec[kLeafStage];
-  __shared__ uint64_t s_off[kLeafStage];
-  __shared__ unsigned long long s_w[kPackLdsWords];
-  const uint64_t blk = blockIdx.x - pre[s];
+  const uint64_t blk = vb - pre[s];
   const uint8_t* keys = (S.final_buf ? keys1 : keys0) + S.key_off;
   const LeafRec* leaves = leaves0 + S.leaf_off;
   const uint64_t* off = off0 + S.leaf_off;
@@ -542,55 +653,6 @@ __global__ void __launch_bounds__(kBlock) k_pack_payload(uint32_t nsets, const u
     pack_payload_body<uint16_t>(S, P, blk, leaves, off, (const uint16_t*)keys, s_rec, s_off, s_w);
   else
     pack_payload_body<uint32_t>(S, P, blk, leaves, off, (const uint32_t*)keys, s_rec, s_off, s_w);
-}
-
-__global__ void k_header(const SetDesc* sets, const DevParams* params) {
-  const SetDesc& S = sets[blockIdx.x];
-  const DevParams* P = params + blockIdx.x;
-  const bool lossless = P->status == kStatusLossless;
-  if (P->status != BBX_OK && !lossless) return;
-  if (threadIdx.x != 0) return;
-  const uint32_t dims = S.dims;
-  uint64_t h[16];
-  for (int k = 0; k < 16; ++k) h[k] = 0;
-  const uint64_t ver = lossless ? 3 : (seq_stream(S) ? 2 : 1);
-  h[0] = (uint64_t)kMagic | (ver << 32) | ((uint64_t)S.dtype << 48) | ((uint64_t)dims << 56);
-  if (lossless) {  // no grid, no leaves, no meta section; no reference field
-    h[1] = S.n;
-    h[2] = (uint64_t)S.r | ((uint64_t)S.eb_mode << 32) | ((uint64_t)S.mbits << 56);
-    h[3] = __double_as_longlong(P->eb_user);
-    h[4] = __double_as_longlong(P->eb_abs);
-    h[14] = P->payload_bits;
-    uint64_t* o = (uint64_t*)S.out;
-    for (int k = 0; k < 16; ++k) o[k] = h[k];
-    return;
-  }
-  h[1] = S.n;
-  h[2] = (uint64_t)S.r | ((uint64_t)S.eb_mode << 32) | ((uint64_t)S.split << 40) |
-         ((uint64_t)S.ref_mode << 48) | ((uint64_t)S.mbits << 56);
-  h[3] = __double_as_longlong(P->eb_user);
-  h[4] = __double_as_longlong(P->eb_abs);
-  h[5] = __double_as_longlong(P->eb_eff);
-  h[6] = __double_as_longlong(P->w);
-  h[7] = __double_as_longlong(P->inv_w);
-  for (uint32_t d = 0; d < 3; ++d) h[8 + d] = d < dims ? __double_as_longlong(P->lo[d]) : 0;
-  h[11] = (uint64_t)P->G[0] | ((uint64_t)(dims > 1 ? P->G[1] : 0) << 8) |
-          ((uint64_t)(dims > 2 ? P->G[2] : 0) << 16);
-  h[12] = S.split ? P->nleaves : S.n_leaves;  // a split-rule partition's count is the device's
-  h[13] = P->meta_bits;
-  h[14] = P->payload_bits;
-  h[15] = seq_stream(S) ? P->nseq : 0;  // version 2: the sequence count
-  uint64_t* o = (uint64_t*)S.out;
-  for (int k = 0; k < 16; ++k) o[k] = h[k];
-}
-
-__global__ void k_finish(uint32_t nsets, const SetDesc* sets, const DevParams* params) {
-  const uint32_t s = blockIdx.x * blockDim.x + threadIdx.x;
-  if (s >= nsets) return;
-  const SetDesc& S = sets[s];
-  const uint32_t st = params[s].status == kStatusLossless ? BBX_OK : params[s].status;
-  if (S.d_size) *S.d_size = st == BBX_OK ? params[s].total_bytes : ~0ull;
-  if (S.d_status) *S.d_status = st;
 }
 
 __device__ void lossless_copy(const SetDesc& S, uint64_t lb, uint64_t nblk) {
@@ -617,37 +679,80 @@ __device__ void lossless_copy(const SetDesc& S, uint64_t lb, uint64_t nblk) {
     for (uint64_t i = lb * kBlock + threadIdx.x; i < S.n; i += step) perm[i] = (uint32_t)i;
 }
 
-// The sets stored losslessly (listed by k_set_sizes): their coordinates'
+// The sets stored losslessly (listed by set_sizes): their coordinates'
 // bits, particle by particle in input order (x, y, z), M bits each,
-// zero-padded to 8 bytes; perm is the identity.  A fixed grid shares each
-// listed set's copy; with no such set every block exits at once.
+// zero-padded to 8 bytes; perm is the identity.  A fixed number of blocks
+// shares each listed set's copy; with no such set every one exits at once.
 constexpr uint32_t kLosslessBlocks = 256;
-__global__ void __launch_bounds__(kBlock) k_lossless(const SetDesc* sets, const uint32_t* list) {
+
+__device__ inline void pack_lossless(uint64_t lb, const SetDesc* sets, const uint32_t* list) {
   const uint32_t count = list[0];
-  for (uint32_t li = 0; li < count; ++li) {
-    const SetDesc& S = sets[list[1 + li]];
-    lossless_copy(S, blockIdx.x, kLosslessBlocks);
-  }
+  for (uint32_t li = 0; li < count; ++li) lossless_copy(sets[list[1 + li]], lb, kLosslessBlocks);
+}
+
+// The meta words (g_pm blocks), and the lossless sets behind them.
+__global__ void __launch_bounds__(kBlock) k_pack_meta(uint32_t nsets, const uint64_t* pre, uint64_t g_pm,
+                                                      const SetDesc* sets, const DevParams* params,
+                                                      const LeafRec* leaves0, const uint32_t* list) {
+  if (blockIdx.x < g_pm)
+    pack_meta(nsets, pre, blockIdx.x, sets, params, leaves0);
+  else
+    pack_lossless(blockIdx.x - g_pm, sets, list);
+}
+
+__global__ void __launch_bounds__(kBlock) k_pack_payload(uint32_t nsets, const uint64_t* pre,
+                                                         const SetDesc* sets, const DevParams* params,
+                                                         const LeafRec* leaves0, const uint64_t* off0,
+                                                         const uint8_t* keys0, const uint8_t* keys1) {
+  __shared__ LeafRec s_rec[kLeafStage];
+  __shared__ uint64_t s_off[kLeafStage];
+  __shared__ unsigned long long s_w[kPackLdsWords];
+  pack_payload(nsets, pre, blockIdx.x, sets, params, leaves0, off0, keys0, keys1, s_rec, s_off, s_w);
+}
+
+// Both in one launch, for few payload blocks (up to kPackOnce): a launch
+// costs such sets more than the payload's LDS takes from the meta words'
+// occupancy.  With more blocks that is the other way round (fluid 2^27: 633
+// us in one launch, 478 + 77 in two).
+constexpr uint64_t kPackOnce = 2048;
+__global__ void __launch_bounds__(kBlock) k_pack(uint32_t nsets, const uint64_t* pre_pp, uint64_t g_pp,
+                                                 const uint64_t* pre_pm, uint64_t g_pm, const SetDesc* sets,
+                                                 const DevParams* params, const LeafRec* leaves0,
+                                                 const uint64_t* off0, const uint8_t* keys0,
+                                                 const uint8_t* keys1, const uint32_t* list) {
+  __shared__ LeafRec s_rec[kLeafStage];
+  __shared__ uint64_t s_off[kLeafStage];
+  __shared__ unsigned long long s_w[kPackLdsWords];
+  const uint64_t b = blockIdx.x;
+  if (b < g_pp)
+    pack_payload(nsets, pre_pp, b, sets, params, leaves0, off0, keys0, keys1, s_rec, s_off, s_w);
+  else if (b < g_pp + g_pm)
+    pack_meta(nsets, pre_pm, b - g_pp, sets, params, leaves0);
+  else
+    pack_lossless(b - g_pp - g_pm, sets, list);
 }
 
 hipError_t launch_pack(const BatchPlan& bp, const Ws& w, hipStream_t s) {
-  hipError_t e = scan_launch(bp.total_leaves, w.leaf_bits, w.scan_part, w.scan_total, nullptr, 0, s);
-  if (e != hipSuccess) return e;
-  const uint32_t g = (bp.nsets + kBlock - 1) / kBlock;
-  BBX_LAUNCH("set_sizes", k_set_sizes, g, kBlock, 0, s, bp.nsets, w.sets, w.params, w.leaf_bits,
-             bp.total_leaves, w.scan_total, w.lossless);
-  if (bp.g_pm > 0)
-    BBX_LAUNCH("pack_meta", k_pack_meta, bp.g_pm, kBlock, 0, s, bp.nsets, w.pre + bp.o_pm, w.sets,
-               w.params, w.leaves);
-  if (bp.g_pp > 0)
-    BBX_LAUNCH("pack_payload", k_pack_payload, bp.g_pp, kBlock, 0, s, bp.nsets, w.pre + bp.o_pp,
-               w.sets, w.params, w.leaves, w.leaf_bits, w.keys[0], w.keys[1]);
-  e = launch_reduce_pack(bp, w, s);
-  if (e != hipSuccess) return e;
-  BBX_LAUNCH("lossless", k_lossless, kLosslessBlocks, kBlock, 0, s, w.sets, w.lossless);
-  BBX_LAUNCH("header", k_header, bp.nsets, 64, 0, s, w.sets, w.params);
-  BBX_LAUNCH("finish", k_finish, g, kBlock, 0, s, bp.nsets, w.sets, w.params);
-  return hipGetLastError();
+  if (bp.total_leaves <= kScanOne) {
+    BBX_LAUNCH("scan_sizes", k_scan_sizes, 1, kScanThreads, 0, s, bp.nsets, w.sets, w.params, bp.total_leaves,
+               w.leaf_bits, w.lossless);
+  } else {
+    const hipError_t e = scan_launch(bp.total_leaves, w.leaf_bits, w.scan_part, w.scan_total, nullptr, 0, s);
+    if (e != hipSuccess) return e;
+    BBX_LAUNCH("set_sizes", k_set_sizes, (bp.nsets + 63) / 64, 64, 0, s, bp.nsets, w.sets, w.params,
+               w.leaf_bits, bp.total_leaves, w.scan_total, w.lossless);
+  }
+  if (bp.g_pp <= kPackOnce) {
+    BBX_LAUNCH("pack_payload", k_pack, bp.g_pp + bp.g_pm + kLosslessBlocks, kBlock, 0, s, bp.nsets,
+               w.pre + bp.o_pp, bp.g_pp, w.pre + bp.o_pm, bp.g_pm, w.sets, w.params, w.leaves, w.leaf_bits,
+               w.keys[0], w.keys[1], w.lossless);
+  } else {
+    BBX_LAUNCH("pack_meta", k_pack_meta, bp.g_pm + kLosslessBlocks, kBlock, 0, s, bp.nsets, w.pre + bp.o_pm,
+               bp.g_pm, w.sets, w.params, w.leaves, w.lossless);
+    BBX_LAUNCH("pack_payload", k_pack_payload, bp.g_pp, kBlock, 0, s, bp.nsets, w.pre + bp.o_pp, w.sets,
+               w.params, w.leaves, w.leaf_bits, w.keys[0], w.keys[1]);
+  }
+  return launch_reduce_pack(bp, w, s);
 }
 
 }  // namespace bbx

@@ -42,7 +42,7 @@ __device__ inline double wave_max(double v) {
 // consecutive particles (DIMS 16-byte loads) at a time, so each loaded
 // element's axis is fixed; the remaining particles go one by one.
 template <typename T, int DIMS>
-__device__ uint64_t minmax_aos_vec(const T* __restrict__ pos, uint64_t n, uint64_t t0, uint64_t nt,
+__device__ __forceinline__ uint64_t minmax_aos_vec(const T* __restrict__ pos, uint64_t n, uint64_t t0, uint64_t nt,
                                    double* lo, double* hi, double& bad) {
   constexpr uint32_t V = 16 / sizeof(T);
   const uint64_t ng = n / V;
@@ -67,7 +67,7 @@ __device__ uint64_t minmax_aos_vec(const T* __restrict__ pos, uint64_t n, uint64
 }
 
 template <typename T>
-__device__ void minmax_body(const T* __restrict__ pos, uint64_t n, uint32_t dims, uint32_t layout,
+__device__ __forceinline__ void minmax_body(const T* __restrict__ pos, uint64_t n, uint32_t dims, uint32_t layout,
                             uint64_t lb, uint32_t mm_blocks, double* part) {
   double lo[3] = {INFINITY, INFINITY, INFINITY};
   double hi[3] = {-INFINITY, -INFINITY, -INFINITY};
@@ -113,17 +113,15 @@ __device__ void minmax_body(const T* __restrict__ pos, uint64_t n, uint32_t dims
 // partials layout per block: lo[3], hi[3], bad, unused (8 doubles).  The first
 // block also clears what later kernels of the call count in: the levels'
 // pass flags (set by k_epilogue), the lossless list and the deferred tiles.
-__global__ void __launch_bounds__(kBlock) k_minmax(uint32_t nsets, const uint64_t* pre,
-                                                   const SetDesc* sets, double* partials,
-                                                   uint32_t* pass_need, uint32_t* lossless,
-                                                   uint32_t* tile_defer) {
+__device__ inline void minmax_clear(uint32_t* pass_need, uint32_t* lossless, uint32_t* tile_defer) {
   if (blockIdx.x == 0) {
     if (threadIdx.x < 4 * kMaxDepth) pass_need[threadIdx.x] = 0;
     if (threadIdx.x == 0) lossless[0] = 0, tile_defer[0] = 0;
   }
-  const uint32_t s = find_set(pre, nsets, blockIdx.x);
-  const SetDesc& S = sets[s];
-  const uint64_t lb = blockIdx.x - pre[s];
+}
+// (forced inline: two kernels share it, and outlined its uniform values would
+// take vector registers)
+__device__ __forceinline__ void minmax_set(const SetDesc& S, uint64_t lb, double* partials) {
   double* part = partials + (S.part_off + lb) * 8;
   const uint64_t n = S.n;
   const uint32_t dims = S.dims, layout = S.layout, mmb = S.mm_blocks;
@@ -131,6 +129,25 @@ __global__ void __launch_bounds__(kBlock) k_minmax(uint32_t nsets, const uint64_
     minmax_body<float>((const float*)S.pos, n, dims, layout, lb, mmb, part);
   else
     minmax_body<double>((const double*)S.pos, n, dims, layout, lb, mmb, part);
+}
+__global__ void __launch_bounds__(kBlock) k_minmax(uint32_t nsets, const uint64_t* pre,
+                                                   const SetDesc* sets, double* partials,
+                                                   uint32_t* pass_need, uint32_t* lossless,
+                                                   uint32_t* tile_defer) {
+  const uint32_t s = find_set(pre, nsets, blockIdx.x);
+  minmax_set(sets[s], blockIdx.x - pre[s], partials);
+  minmax_clear(pass_need, lossless, tile_defer);
+}
+
+// A set alone whose descriptors come with the launch: the first block also
+// puts them in the workspace, for the kernels that follow.
+__global__ void __launch_bounds__(kBlock) k_minmax_blob(ArgBlob b, uint64_t* dst, double* partials,
+                                                        uint32_t* pass_need, uint32_t* lossless,
+                                                        uint32_t* tile_defer) {
+  minmax_set(*(const SetDesc*)b.w, blockIdx.x, partials);
+  if (blockIdx.x == 0)
+    for (uint32_t i = threadIdx.x; i < b.words; i += kBlock) dst[i] = b.w[i];
+  minmax_clear(pass_need, lossless, tile_defer);
 }
 
 // fold: the set's first two histograms are cleared here (the later ones by the
@@ -385,8 +402,11 @@ __global__ void __launch_bounds__(kBlock) k_hist_zero(uint64_t entries, uint32_t
     hist[i] = 0;
 }
 
-hipError_t launch_range(const BatchPlan& bp, const Ws& w, hipStream_t s) {
-  if (bp.g_mm > 0)
+hipError_t launch_range(const BatchPlan& bp, const Ws& w, const ArgBlob* blob, hipStream_t s) {
+  if (blob)
+    BBX_LAUNCH("range_minmax", k_minmax_blob, bp.g_mm, kBlock, 0, s, *blob, (uint64_t*)w.sets, w.partials,
+               w.pass_need, w.lossless, w.tile_defer);
+  else if (bp.g_mm > 0)
     BBX_LAUNCH("range_minmax", k_minmax, bp.g_mm, kBlock, 0, s, bp.nsets, w.pre + bp.o_mm, w.sets,
                w.partials, w.pass_need, w.lossless, w.tile_defer);
   else

@@ -646,7 +646,10 @@ __global__ void __launch_bounds__(64) k_tile(uint32_t nsets, const uint64_t* pre
                                    leaf_bits0, defer, blockIdx.x, sm);
 }
 
-// second pass: the deferred tiles, 32-bit tile codes (capped grid, striding)
+// second pass: the deferred tiles, 32-bit tile codes (capped grid, striding);
+// without a list every tile, as the only pass of grids of few tiles, where a
+// second launch costs more than wider codes (about 4 us of a set of 65,536)
+constexpr uint64_t kTileOnce = 2048;
 template <int TILE, bool TRACK>
 __global__ void __launch_bounds__(64) k_tile_wide(uint32_t nsets, const uint64_t* pre,
                                                   const SetDesc* sets, DevParams* params,
@@ -654,10 +657,10 @@ __global__ void __launch_bounds__(64) k_tile_wide(uint32_t nsets, const uint64_t
                                                   uint32_t* idx1, LeafRec* leaves0,
                                                   uint64_t* leaf_bits0, const uint32_t* defer) {
   __shared__ WaveTile<TILE, uint32_t, TRACK> sm;
-  const uint32_t count = defer[0];
+  const uint32_t count = defer ? defer[0] : gridDim.x;
   for (uint32_t q = blockIdx.x; q < count; q += gridDim.x) {
     tile_node<TILE, uint32_t, TRACK>(nsets, pre, sets, params, keys0, keys1, idx0, idx1, leaves0,
-                                     leaf_bits0, nullptr, defer[1 + q], sm);
+                                     leaf_bits0, nullptr, defer ? defer[1 + q] : q, sm);
     wave_sync();  // the next tile reuses the LDS
   }
 }
@@ -782,6 +785,12 @@ __global__ void __launch_bounds__(kBlock) k_bigleaf(uint32_t nsets, const uint64
 
 template <int TILE, bool TRACK>
 static void launch_tiles(const BatchPlan& bp, const Ws& w, hipStream_t s) {
+  if (bp.g_tile <= kTileOnce) {
+    BBX_LAUNCH("tile", (k_tile_wide<TILE, TRACK>), bp.g_tile, 64, 0, s, bp.nsets, w.pre + bp.o_tile,
+               w.sets, w.params, w.keys[0], w.keys[1], w.idx[0], w.idx[1], w.leaves, w.leaf_bits,
+               (const uint32_t*)nullptr);
+    return;
+  }
   BBX_LAUNCH("tile", (k_tile<TILE, TRACK>), bp.g_tile, 64, 0, s, bp.nsets, w.pre + bp.o_tile, w.sets,
              w.params, w.keys[0], w.keys[1], w.idx[0], w.idx[1], w.leaves, w.leaf_bits,
              w.tile_defer);
