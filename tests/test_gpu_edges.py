@@ -119,3 +119,44 @@ def test_global_level_digits(bbx, orc, n, eb, span):
     for got in bbx.BatchCompressor([{"pos": x, "eb": eb}, {"pos": x[: n // 3].contiguous(), "eb": eb},
                                     {"pos": x, "eb": eb, "level_pairs": int(n % 2)}])()[::2]:
         assert got.cpu().numpy().tobytes() == ref[0]
+
+
+# Decoding from the records themselves: one leaf to many per block, leaves
+# that do not divide a thread's four slots, equal leaves, the last block of few.
+@pytest.mark.parametrize("n,r", [(1, 1), (7, 1), (2048, 8), (2049, 8), (5000, 9), (65536, 32), (3000, 3000),
+                                 (9000, 2100), (40961, 300), (6000, 100)])
+@pytest.mark.parametrize("dtype,ref_mode,layout", [(np.float32, 0, "aos"), (np.float32, 1, "soa"),
+                                                   (np.float64, 1, "aos")])
+def test_decode_shapes(bbx, orc, n, r, dtype, ref_mode, layout):
+    for dims in (2, 3):
+        pts = gen("cosmology", n, dims, dtype, seed=r)
+        check_parity(orc, bbx, pts, 1e-3, "rel", r, layout=layout, ref_mode=ref_mode)
+
+
+@pytest.mark.parametrize("ref_mode", [0, 1])
+def test_decode_damaged(bbx, orc, ref_mode):
+    """Flipped bits of the records and codes: refused where the oracle
+    refuses, its positions where it decodes."""
+    n = 3001
+    good = orc.compress(gen("uniform", n, 3, np.float32, seed=8), 1e-3, "rel", 32, ref_mode=ref_mode)
+    good = np.frombuffer(good, np.uint8).copy()
+    rng = np.random.default_rng(9)
+    refused = 0
+    for trial in range(40):
+        bad = good.copy()
+        at = int(rng.integers(128, 128 + 600 if trial % 2 else len(bad) - 8))
+        bad[at] ^= np.uint8(1 << rng.integers(0, 8))
+        try:
+            want = orc.decompress(bad.tobytes())
+        except Exception:
+            want = None
+        try:
+            got = bbx.decompress(torch.from_numpy(bad).cuda()).cpu().numpy()
+        except bbx.BitboxError as e:
+            assert e.name == "ECORRUPT"
+            got = None
+        assert (got is None) == (want is None), (trial, at)
+        if want is not None:
+            assert got.tobytes() == np.ascontiguousarray(want).tobytes(), (trial, at)
+        refused += want is None
+    assert 0 < refused < 40
