@@ -1220,21 +1220,20 @@ bbx_status bbx_export_sequences(const void* d_stream, size_t stream_size, const 
   return BBX_OK;
 }
 
-// The reordered export's workspace: the decompression workspace, the plain
-// layout, width histograms, per-leaf keys, (key, block) counts, the new
-// order and the placed payload bits.
+// The reordered export's workspace: the decompression workspace, width
+// histograms, per-leaf keys, (key, block) counts, the new order and the
+// placed payload bits.
 struct ReorderLayout {
-  size_t dec, plain, whist, key, bcount, order, sbits, total;
+  size_t dec, whist, key, bcount, order, sbits, total;
 };
 static ReorderLayout reorder_layout(const HostHeader& h) {
   ReorderLayout L;
   DecompressWs w;
   Carve c;
   L.dec = c.take(carve_decompress(h, nullptr, &w));
-  L.plain = c.take((size_t)export_bytes(h));
   L.whist = c.take(3 * 64 * 4);
   L.key = c.take((size_t)h.n_leaves);
-  L.bcount = c.take(4 * 94 * (size_t)((h.n_leaves + kBlock - 1) / kBlock));
+  L.bcount = c.take(4 * 94 * (((size_t)((h.n_leaves + kBlock - 1) / kBlock) + 3) & ~(size_t)3));
   L.order = c.take(4 * (size_t)h.n_leaves);
   L.sbits = c.take(8 * (size_t)h.n_leaves);
   L.total = c.off;
@@ -1272,9 +1271,8 @@ bbx_status bbx_export_sequences_reordered(const void* d_stream, size_t stream_si
   memset(&w, 0, sizeof(w));
   carve_decompress(h, base + L.dec, &w);
   const DecompressPlan p = plan_of(h, h_header, BBX_AOS);
-  uint8_t* plain = base + L.plain;
   uint32_t* whist = (uint32_t*)(base + L.whist);
-  hipError_t e = launch_export(p, w, (const uint8_t*)d_stream, plain, nullptr, stream);
+  hipError_t e = launch_records(p, w, (const uint8_t*)d_stream, stream);
   if (e == hipSuccess) e = hipMemsetAsync(whist, 0, 3 * 64 * 4, stream);
   if (e == hipSuccess)
     e = launch_reorder_hist(h.n_leaves, h.dims, w, whist, base + L.key, (uint32_t*)(base + L.bcount), stream);
@@ -1296,7 +1294,7 @@ bbx_status bbx_export_sequences_reordered(const void* d_stream, size_t stream_si
   std::stable_sort(ord, ord + h.dims, [&](uint32_t a, uint32_t b) { return sclog[a] > sclog[b]; });
   if (h_axis_order)
     for (uint32_t d = 0; d < h.dims; ++d) h_axis_order[d] = ord[d];
-  e = launch_reorder_write(p, w, ord, plain, (uint8_t*)d_out, need_out / 8, base + L.key,
+  e = launch_reorder_write(p, w, ord, (const uint8_t*)d_stream, (uint8_t*)d_out, need_out / 8, base + L.key,
                            (uint32_t*)(base + L.bcount), (uint32_t*)(base + L.order),
                            (uint64_t*)(base + L.sbits), stream);
   if (e == hipSuccess) e = hipMemcpyAsync(&hp, w.params, sizeof(hp), hipMemcpyDeviceToHost, stream);

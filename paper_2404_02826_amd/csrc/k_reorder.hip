@@ -6,8 +6,8 @@
 // axis most significant), equal R-indices in stored order.  A sequence keeps
 // its centre, widths and end mark; its members keep their codes.
 //
-// After the plain export (whose decode leaves every leaf's record and payload
-// offset in the decompression workspace):
+// From the stream itself (every leaf's record and payload offset are in the
+// decompression workspace by then):
 //   k_ro_hist    per leaf: its widths into per-axis histograms, its key
 //                (the sum of widths) and its counts per block of leaves
 //   (host: the axis order from the width histograms)
@@ -18,10 +18,11 @@
 //                block plus the leaves of the block before it with its key);
 //                the leaf at each place and that leaf's payload bits there
 //   (scan of the placed payload bits: each sequence's new offset)
-//   k_ro_write   a wavefront per sequence: centre and widths copied, members
-//                ranked by (R-index, stored position), their codes written
-//                in that order, the end mark; words ORed into the zeroed
-//                output (sequences share boundary words)
+//   k_ro_write   SUB lanes per sequence of at most SUB other members: centre
+//                and widths copied, members ranked by (R-index, stored
+//                position), their codes written in that order, the end mark
+//   k_ro_long    a wavefront per sequence, for larger leaves
+//   Both OR the words into the zeroed output (sequences share boundary words).
 #include "bbx_internal.h"
 
 namespace bbx {
@@ -29,6 +30,8 @@ namespace bbx {
 typedef unsigned __int128 u128;
 
 constexpr uint32_t kRoKeys = 94;        // sums of widths 0 .. 3 * 31
+// counts per key: one per block of leaves, rounded up to 16 bytes
+__host__ __device__ inline uint64_t ro_stride(uint64_t blocks) { return (blocks + 3) & ~3ull; }
 constexpr uint32_t kRoLocal = 256;      // members ranked from LDS (more: from the layout)
 constexpr uint32_t kRoStage = 64;       // words of a sequence staged in LDS (longer: written in place)
 
@@ -76,30 +79,51 @@ __global__ void __launch_bounds__(kBlock) k_ro_hist(uint64_t n_leaves, uint32_t 
   __syncthreads();
   for (uint32_t k = threadIdx.x; k < 3 * 64; k += kBlock)
     if (wh[k]) atomicAdd(&whist[k], wh[k]);
-  const uint64_t nblk = gridDim.x;
-  for (uint32_t k = threadIdx.x; k < kRoKeys; k += kBlock) bcount[(uint64_t)k * nblk + blockIdx.x] = kc[k];
+  const uint64_t nblk = ro_stride(gridDim.x);
+  for (uint32_t k = threadIdx.x; k < kRoKeys; k += kBlock) {
+    bcount[(uint64_t)k * nblk + blockIdx.x] = kc[k];
+    if (blockIdx.x == gridDim.x - 1)  // the blocks that are not there
+      for (uint64_t b = gridDim.x; b < nblk; ++b) bcount[(uint64_t)k * nblk + b] = 0;
+  }
 }
 
-// one block: exclusive scan of counts[key][block], key major
+// one block: exclusive scan of counts[key][block], key major; 16 entries per
+// thread and round (entries is a multiple of 4, c of 16 bytes: one entry per
+// thread and round took 178 us for the 192,512 entries of 524,288 leaves, this
+// takes 46)
 __global__ void __launch_bounds__(1024) k_ro_scan(uint32_t* c, uint64_t entries, const DevParams* P) {
   if (P->status != BBX_OK) return;
-  __shared__ uint32_t ws[16];
-  uint32_t run = 0;
-  for (uint64_t e0 = 0; e0 < entries; e0 += blockDim.x) {
-    const uint64_t e = e0 + threadIdx.x;
-    const uint32_t v = e < entries ? c[e] : 0u;
-    const uint32_t lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-    const uint32_t incl = wave_incl(v);
-    if (lane == 63) ws[wv] = incl;
-    __syncthreads();
-    uint32_t off = 0, tot = 0;
-    for (uint32_t k = 0; k < blockDim.x / 64; ++k) {
-      off += k < wv ? ws[k] : 0u;
-      tot += ws[k];
+  __shared__ uint32_t ws[2][16];
+  const uint32_t lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+  uint4* const c4 = (uint4*)c;
+  const uint64_t quads = entries / 4;
+  uint32_t run = 0, buf = 0;
+  for (uint64_t q0 = 0; q0 < quads; q0 += 4 * 1024, buf ^= 1) {
+    const uint64_t q = q0 + 4 * threadIdx.x;
+    uint4 v[4];
+    uint32_t sum = 0;
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      v[k] = q + k < quads ? c4[q + k] : make_uint4(0, 0, 0, 0);
+      sum += v[k].x + v[k].y + v[k].z + v[k].w;
     }
+    const uint32_t incl = wave_incl(sum);
+    if (lane == 63) ws[buf][wv] = incl;
     __syncthreads();
-    if (e < entries) c[e] = run + off + incl - v;
+    uint32_t at = run + incl - sum, tot = 0;
+#pragma unroll
+    for (uint32_t k = 0; k < 16; ++k) {
+      at += k < wv ? ws[buf][k] : 0u;
+      tot += ws[buf][k];
+    }
     run += tot;
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      uint4 o;
+      o.x = at, o.y = o.x + v[k].x, o.z = o.y + v[k].y, o.w = o.z + v[k].z;
+      at = o.w + v[k].w;
+      if (q + k < quads) c4[q + k] = o;
+    }
   }
 }
 
@@ -117,7 +141,7 @@ __global__ void __launch_bounds__(kBlock) k_ro_place(uint64_t n_leaves, const ui
   const uint32_t k = kl[threadIdx.x];
   uint32_t before = 0;
   for (uint32_t t = 0; t < threadIdx.x; ++t) before += kl[t] == k ? 1u : 0u;
-  const uint64_t q = base[(uint64_t)k * gridDim.x + blockIdx.x] + before;
+  const uint64_t q = base[(uint64_t)k * ro_stride(gridDim.x) + blockIdx.x] + before;
   const uint32_t m = leaves[i].m;
   const uint32_t sm = (m & 0xffu) + ((m >> 8) & 0xffu) + ((m >> 16) & 0xffu);
   order[q] = (uint32_t)i;
@@ -131,43 +155,152 @@ __global__ void __launch_bounds__(kBlock) k_ro_zero(uint64_t* p, uint64_t words,
     p[i] = 0;
 }
 
-// the R-index of member j of a sequence whose codes start at bit `at`
-__device__ inline u128 ro_rindex(const uint64_t* pl, uint64_t pw, uint64_t at, uint32_t j,
-                                 const uint32_t m[3], uint32_t sm, uint32_t dims, const uint32_t ord[3]) {
-  uint64_t u[3] = {0, 0, 0};
-  uint64_t p = at + (uint64_t)j * sm;
-  for (uint32_t d = 0; d < dims; ++d) {
-    u[d] = ro_read(pl, pw, p, m[d]);
-    p += m[d];
-  }
-  u128 r = 0;
-  for (uint32_t k = 0; k < dims; ++k) {
-    const uint32_t d = ord[k];
-    r = (r << m[d]) | (u128)u[d];
-  }
-  return r;
+// value t of a 3-array held in registers (no dynamic indexing)
+template <typename T>
+__device__ inline T ro_pick(const T (&v)[3], uint32_t t) {
+  return t == 0 ? v[0] : (t == 1 ? v[1] : v[2]);
 }
 
-__global__ void __launch_bounds__(kBlock) k_ro_write(uint64_t n_leaves, uint32_t dims, uint32_t M,
-                                                     uint32_t mbits, uint32_t o0, uint32_t o1,
-                                                     uint32_t o2, const LeafRec* leaves,
-                                                     const uint64_t* poff, const uint32_t* order,
-                                                     const uint64_t* soff, const uint64_t* plain,
-                                                     uint64_t plain_words,
-                                                     unsigned long long* out, const DevParams* P) {
+// What the writing kernels read and write.
+struct RoView {
+  uint64_t n_leaves;
+  const LeafRec* leaves;
+  const uint64_t* poff;   // a leaf's first payload bit
+  const uint32_t* order;  // leaf of each sequence
+  const uint64_t* soff;   // code bits before each sequence
+  const uint64_t* meta;
+  const uint64_t* pay;
+  uint64_t mwords, pwords;
+  unsigned long long* out;
+  uint32_t dims, M, mbits, ord[3];
+};
+
+// A member's code bits: its axes' codes in axis order, sm of them (at most 93).
+__device__ inline u128 ro_code(const RoView& v, uint64_t at, uint32_t sm) {
+  u128 c = ro_read(v.pay, v.pwords, at, sm < 64 ? sm : 64);
+  if (sm > 64) c |= (u128)ro_read(v.pay, v.pwords, at + 64, sm - 64) << 64;
+  return c;
+}
+// Its R-index: the axes' codes with ord[0] most significant.
+template <typename T>
+__device__ inline T ro_rindex(const RoView& v, T c, const uint32_t (&m)[3]) {
+  const T f[3] = {c & (((T)1 << m[0]) - 1), (c >> m[0]) & (((T)1 << m[1]) - 1),
+                  (c >> (m[0] + m[1])) & (((T)1 << m[2]) - 1)};
+  T r = 0;
+#pragma unroll
+  for (uint32_t k = 0; k < 3; ++k)
+    if (k < v.dims) r = (r << ro_pick(m, v.ord[k])) | ro_pick(f, v.ord[k]);
+  return r;
+}
+__device__ inline void ro_write128(unsigned long long* sec, uint64_t at, u128 c, uint32_t len) {
+  ro_write(sec, at, (uint64_t)c, len < 64 ? len : 64);
+  if (len > 64) ro_write(sec, at + 64, (uint64_t)(c >> 64), len - 64);
+}
+
+// Centre and widths of leaf i at bit `at` of dst: lane k of at least 8 takes
+// 32 bits of the centre, the lane after the last of them the widths.
+__device__ inline void ro_header(const RoView& v, uint64_t i, unsigned long long* dst, uint64_t at, uint32_t k) {
+  const uint32_t cw = v.dims * v.M / 32, rec = v.dims * (v.mbits + v.M), wb = v.dims * v.mbits;
+  if (k < cw)
+    ro_write(dst, at + 32 * k, ro_read(v.meta, v.mwords, i * rec + wb + 32 * k, 32), 32);
+  else if (k == cw)
+    ro_write(dst, at + 32 * cw, ro_read(v.meta, v.mwords, i * rec, wb), wb);
+}
+
+// SUB lanes per sequence, one per member besides the reference (at most SUB).
+// A member's codes are read once, as one bit string; its rank is the number
+// of smaller (R-index, position) keys among the sequence's, which all fit one
+// word with the position (R-indices of up to 58 bits; longer ones compare as
+// two words).  The sequence is put together in LDS, so that only its two
+// boundary words need atomics.  A wavefront per sequence with 128-bit keys
+// read from a plain layout written before took 929 us (and that layout 140)
+// for the cosmology 2^24 set's 524,288 sequences; this takes 311.  Bound
+// by instruction issue (SUB comparisons per lane).
+template <int SUB>
+__global__ void __launch_bounds__(kBlock) k_ro_write(RoView v, const DevParams* P) {
+  if (P->status != BBX_OK) return;
+  constexpr uint32_t NS = 64 / SUB;                             // sequences per wavefront
+  constexpr uint32_t WORDS = (63 + 242 + 93 * SUB + 63) / 64;   // words of a sequence at most
+  __shared__ __align__(16) uint64_t keys[kBlock / 64][64];
+  __shared__ uint64_t high[kBlock / 64][64];
+  __shared__ unsigned long long stage[kBlock / 64][NS][WORDS];
+  const uint32_t lane = threadIdx.x & 63;
+  const uint32_t wv = (uint32_t)__builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+  const uint32_t sub = lane / SUB, k = lane % SUB;
+  const uint32_t F = v.dims * (v.M + v.mbits) + 32, hdr = F - 32;  // bits besides the codes
+  const uint64_t q = ((uint64_t)blockIdx.x * (kBlock / 64) + wv) * NS + sub;
+  const bool valid = q < v.n_leaves;
+  uint64_t i = 0, op = 0, at = 0;
+  uint32_t m[3] = {0, 0, 0}, sm = 0, cnt = 0, nwd = 0;
+  unsigned long long* const st = stage[wv][sub];
+  if (valid) {
+    i = v.order[q];
+    const uint32_t mp = v.leaves[i].m;
+    m[0] = mp & 0xffu, m[1] = (mp >> 8) & 0xffu, m[2] = (mp >> 16) & 0xffu;
+    sm = m[0] + m[1] + m[2];
+    cnt = v.leaves[i].size - 1;
+    op = q * F + v.soff[q];
+    at = v.poff[i];
+    nwd = (uint32_t)(((op & 63) + F + (uint64_t)cnt * sm + 63) >> 6);
+    if (cnt > SUB) cnt = SUB;  // (never: the launch is chosen by the leaf size)
+    if (nwd > WORDS) nwd = WORDS;
+  }
+  for (uint32_t x = k; x < nwd; x += SUB) st[x] = 0;
+  const bool mine = k < cnt && sm > 0;
+  const uint64_t o0 = op & 63, c0 = o0 + hdr;  // the sequence's first bit, and its first code's, in the stage
+  uint32_t rank = 0;
+  if (__ballot(sm > 58) == 0) {
+    const uint64_t code = mine ? ro_read(v.pay, v.pwords, at + (uint64_t)k * sm, sm) : 0ull;
+    const uint64_t own = mine ? ro_rindex<uint64_t>(v, code, m) << 6 | k : ~0ull;
+    keys[wv][lane] = own;
+    wave_sync();
+    const ulonglong2* o = (const ulonglong2*)&keys[wv][sub * SUB];
+#pragma unroll 4
+    for (uint32_t t = 0; t < SUB / 2; ++t) {
+      const ulonglong2 x = o[t];
+      rank += (x.x < own ? 1u : 0u) + (x.y < own ? 1u : 0u);
+    }
+    if (mine) ro_write(st, c0 + (uint64_t)rank * sm, code, sm);
+  } else {
+    const u128 code = mine ? ro_code(v, at + (uint64_t)k * sm, sm) : (u128)0;
+    const u128 r = mine ? ro_rindex<u128>(v, code, m) : ~(u128)0;
+    keys[wv][lane] = (uint64_t)r;
+    high[wv][lane] = (uint64_t)(r >> 64);
+    wave_sync();
+    for (uint32_t t = 0; t < SUB; ++t) {
+      const u128 x = (u128)high[wv][sub * SUB + t] << 64 | keys[wv][sub * SUB + t];
+      rank += x < r || (x == r && t < k) ? 1u : 0u;
+    }
+    if (mine) ro_write128(st, c0 + (uint64_t)rank * sm, code, sm);
+  }
+  if (valid) {
+    ro_header(v, i, st, o0, k);
+    if (k == 0) ro_write(st, c0 + (uint64_t)cnt * sm, 0xffffffffull, 32);  // end mark
+  }
+  wave_sync();
+  for (uint32_t x = k; x < nwd; x += SUB) {
+    unsigned long long* const d = v.out + (op >> 6) + x;
+    if (x == 0 || x + 1 == nwd)
+      atomicOr(d, st[x]);
+    else
+      *d = st[x];
+  }
+}
+
+// A wavefront per sequence of any size.
+__global__ void __launch_bounds__(kBlock) k_ro_long(RoView v, const DevParams* P) {
   if (P->status != BBX_OK) return;
   __shared__ u128 rk[kBlock / 64][kRoLocal];
   __shared__ unsigned long long stg[kBlock / 64][kRoStage];
   const uint32_t lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-  const uint32_t ord[3] = {o0, o1, o2};
-  const uint64_t F = (uint64_t)dims * (M + mbits) + 32;  // a sequence's bits besides its codes
-  const uint32_t hdr = dims * (M + mbits);
+  const uint32_t hdr = v.dims * (v.M + v.mbits);
+  const uint64_t F = (uint64_t)hdr + 32;  // a sequence's bits besides its codes
   const uint64_t gw = ((uint64_t)blockIdx.x * kBlock + threadIdx.x) >> 6;
   const uint64_t nw = ((uint64_t)gridDim.x * kBlock) >> 6;
-  for (uint64_t q = gw; q < n_leaves; q += nw) {
-    const uint32_t i = order[q];
-    const LeafRec L = leaves[i];
-    const uint64_t in = (uint64_t)i * F + poff[i], op = q * F + soff[q];
+  for (uint64_t q = gw; q < v.n_leaves; q += nw) {
+    const uint32_t i = v.order[q];
+    const LeafRec L = v.leaves[i];
+    const uint64_t cin = v.poff[i], op = q * F + v.soff[q];
     const uint32_t m[3] = {L.m & 0xffu, (L.m >> 8) & 0xffu, (L.m >> 16) & 0xffu};
     const uint32_t sm = m[0] + m[1] + m[2];
     const uint32_t cnt = L.size - 1;
@@ -176,38 +309,29 @@ __global__ void __launch_bounds__(kBlock) k_ro_write(uint64_t n_leaves, uint32_t
     // into the output in place
     const uint64_t w0 = op >> 6, nwd = ((op + F + (uint64_t)cnt * sm - 1) >> 6) - w0 + 1;
     const bool staged = nwd <= kRoStage;
-    unsigned long long* dst = staged ? stg[wv] : out;
+    unsigned long long* dst = staged ? stg[wv] : v.out;
     const uint64_t dbase = staged ? w0 * 64 : 0;  // bit offset of dst[0] in the output
     if (staged) {
       for (uint32_t k = lane; k < kRoStage; k += 64) stg[wv][k] = 0;
       wave_sync();
     }
-    // centre and widths, 32 bits per lane-step
-    for (uint32_t b = lane * 32; b < hdr; b += 64 * 32) {
-      const uint32_t c = hdr - b < 32 ? hdr - b : 32;
-      ro_write(dst, op + b - dbase, ro_read(plain, plain_words, in + b, c), c);
-    }
-    const uint64_t cin = in + hdr, cout = op + hdr - dbase;
+    ro_header(v, i, dst, op - dbase, lane);
+    const uint64_t cout = op + hdr - dbase;
     if (sm > 0 && cnt > 0) {
       const bool local = cnt <= kRoLocal;
+      auto rindex = [&](uint32_t j) { return ro_rindex<u128>(v, ro_code(v, cin + (uint64_t)j * sm, sm), m); };
       if (local)
-        for (uint32_t j = lane; j < cnt; j += 64)
-          rk[wv][j] = ro_rindex(plain, plain_words, cin, j, m, sm, dims, ord);
+        for (uint32_t j = lane; j < cnt; j += 64) rk[wv][j] = rindex(j);
       wave_sync();
       for (uint32_t j = lane; j < cnt; j += 64) {
-        const u128 kj = local ? rk[wv][j] : ro_rindex(plain, plain_words, cin, j, m, sm, dims, ord);
+        const u128 kj = local ? rk[wv][j] : rindex(j);
         uint32_t rank = 0;
         for (uint32_t t = 0; t < cnt; ++t) {
-          const u128 kt = local ? rk[wv][t] : ro_rindex(plain, plain_words, cin, t, m, sm, dims, ord);
+          const u128 kt = local ? rk[wv][t] : rindex(t);
           rank += (kt < kj || (kt == kj && t < j)) ? 1u : 0u;
         }
         // the member's codes, in axis order, at its rank
-        uint64_t p = cin + (uint64_t)j * sm, o = cout + (uint64_t)rank * sm;
-        for (uint32_t d = 0; d < dims; ++d) {
-          ro_write(dst, o, ro_read(plain, plain_words, p, m[d]), m[d]);
-          p += m[d];
-          o += m[d];
-        }
+        ro_write128(dst, cout + (uint64_t)rank * sm, ro_code(v, cin + (uint64_t)j * sm, sm), sm);
       }
       wave_sync();  // rk is rewritten by the wavefront's next sequence
     }
@@ -215,11 +339,11 @@ __global__ void __launch_bounds__(kBlock) k_ro_write(uint64_t n_leaves, uint32_t
     if (staged) {
       wave_sync();
       for (uint32_t k = lane; k < nwd; k += 64) {
-        const unsigned long long v = stg[wv][k];
+        const unsigned long long x = stg[wv][k];
         if (k == 0 || k + 1 == nwd)
-          atomicOr(&out[w0 + k], v);
+          atomicOr(&v.out[w0 + k], x);
         else
-          out[w0 + k] = v;
+          v.out[w0 + k] = x;
       }
       wave_sync();  // stg is rewritten by the wavefront's next sequence
     }
@@ -235,23 +359,52 @@ hipError_t launch_reorder_hist(uint64_t n_leaves, uint32_t dims, const Decompres
   return hipGetLastError();
 }
 
+template <int SUB>
+static void launch_ro_write(const RoView& v, const DevParams* P, hipStream_t s) {
+  constexpr uint32_t per = kBlock / SUB;  // sequences per block
+  BBX_LAUNCH("reorder_write", k_ro_write<SUB>, (uint32_t)((v.n_leaves + per - 1) / per), kBlock, 0, s, v, P);
+}
+
 hipError_t launch_reorder_write(const DecompressPlan& p, const DecompressWs& w, const uint32_t ord[3],
-                                const uint8_t* plain, uint8_t* out, uint64_t out_words, uint8_t* key,
+                                const uint8_t* stream, uint8_t* out, uint64_t out_words, uint8_t* key,
                                 uint32_t* bcount, uint32_t* order, uint64_t* sbits, hipStream_t s) {
   const uint64_t nl = p.n_leaves, nblk = (nl + kBlock - 1) / kBlock;
   if (nl == 0) return hipGetLastError();
-  const uint32_t M = coord_bits(p.dtype);
-  BBX_LAUNCH("reorder_scan", k_ro_scan, 1, 1024, 0, s, bcount, (uint64_t)kRoKeys * nblk, w.params);
+  BBX_LAUNCH("reorder_scan", k_ro_scan, 1, 1024, 0, s, bcount, (uint64_t)kRoKeys * ro_stride(nblk), w.params);
   BBX_LAUNCH("reorder_place", k_ro_place, nblk, kBlock, 0, s, nl, key, bcount, w.leaves, order, sbits,
              w.params);
   hipError_t e = launch_dec_scan(nl, sbits, w.scan_part, w.params, p.payload_bits, s);
   if (e != hipSuccess) return e;
   BBX_LAUNCH("reorder_zero", k_ro_zero, (uint32_t)std::min<uint64_t>(out_words / kBlock + 1, 4096), kBlock, 0,
              s, (uint64_t*)out, out_words, w.params);
-  const uint64_t plain_words = out_words;  // both layouts have the same length
-  BBX_LAUNCH("reorder_write", k_ro_write, (uint32_t)std::min<uint64_t>((nl + 3) / 4, 65536), kBlock, 0, s,
-             nl, p.dims, M, p.mbits, ord[0], ord[1], ord[2], w.leaves, w.leaf_bits, order, sbits,
-             (const uint64_t*)plain, plain_words, (unsigned long long*)out, w.params);
+  RoView v;
+  v.n_leaves = nl;
+  v.leaves = w.leaves;
+  v.poff = w.leaf_bits;
+  v.order = order;
+  v.soff = sbits;
+  v.mwords = (p.meta_bits + 63) / 64;
+  v.pwords = (p.payload_bits + 63) / 64;
+  v.meta = (const uint64_t*)(stream + kHeaderBytes);
+  v.pay = v.meta + v.mwords;
+  v.out = (unsigned long long*)out;
+  v.dims = p.dims;
+  v.M = coord_bits(p.dtype);
+  v.mbits = p.mbits;
+  for (int d = 0; d < 3; ++d) v.ord[d] = ord[d];
+  // as many lanes per sequence as a leaf can have members besides its
+  // reference, at least the header's 8
+  if (p.r <= 9)
+    launch_ro_write<8>(v, w.params, s);
+  else if (p.r <= 17)
+    launch_ro_write<16>(v, w.params, s);
+  else if (p.r <= 33)
+    launch_ro_write<32>(v, w.params, s);
+  else if (p.r <= 65)
+    launch_ro_write<64>(v, w.params, s);
+  else
+    BBX_LAUNCH("reorder_write", k_ro_long, (uint32_t)std::min<uint64_t>((nl + 3) / 4, 65536), kBlock, 0, s, v,
+               w.params);
   return hipGetLastError();
 }
 

@@ -672,17 +672,23 @@ __global__ void __launch_bounds__(kBlock) k_export(uint64_t n_leaves, uint32_t d
   }
 }
 
+// Every leaf's record (w.leaves) and first payload bit (w.leaf_bits).
+hipError_t launch_records(const DecompressPlan& p, const DecompressWs& w, const uint8_t* stream, hipStream_t s) {
+  BBX_LAUNCH("dec_init", k_dec_init, 1, 64, 0, s, w.params, stream, p.header);
+  if (p.n == 0) return hipGetLastError();
+  uint64_t g = (p.n_leaves + kBlock - 1) / kBlock;
+  if (g > 65536) g = 65536;
+  BBX_LAUNCH("dec_meta", k_dec_meta, g, kBlock, 0, s, p.n_leaves, p.dims, p.mbits, p.G[0],
+             p.G[1], p.G[2], p.meta_bits, p.geom, stream, w.leaves, w.leaf_bits, w.params,
+             p.ref_mode, p.dtype, p.origin[0], p.origin[1], p.origin[2], p.inv_w);
+  return launch_dec_scan(p.n_leaves, w.leaf_bits, w.scan_part, w.params, p.payload_bits, s);
+}
+
 hipError_t launch_export(const DecompressPlan& p, const DecompressWs& w, const uint8_t* stream,
                          void* out, uint32_t* d_status, hipStream_t s) {
-  BBX_LAUNCH("dec_init", k_dec_init, 1, 64, 0, s, w.params, stream, p.header);
+  const hipError_t e = launch_records(p, w, stream, s);
+  if (e != hipSuccess) return e;
   if (p.n > 0) {
-    uint64_t g = (p.n_leaves + kBlock - 1) / kBlock;
-    if (g > 65536) g = 65536;
-    BBX_LAUNCH("dec_meta", k_dec_meta, g, kBlock, 0, s, p.n_leaves, p.dims, p.mbits, p.G[0],
-               p.G[1], p.G[2], p.meta_bits, p.geom, stream, w.leaves, w.leaf_bits, w.params,
-               p.ref_mode, p.dtype, p.origin[0], p.origin[1], p.origin[2], p.inv_w);
-    hipError_t e = launch_dec_scan(p.n_leaves, w.leaf_bits, w.scan_part, w.params, p.payload_bits, s);
-    if (e != hipSuccess) return e;
     const uint32_t M = coord_bits(p.dtype);
     const uint64_t F = (uint64_t)p.dims * (M + p.mbits) + 32;
     const uint64_t blocks = (p.n_leaves + kExportLeaves - 1) / kExportLeaves;
@@ -693,7 +699,7 @@ hipError_t launch_export(const DecompressPlan& p, const DecompressWs& w, const u
     BBX_LAUNCH("export", k_export, blocks, kBlock, 0, s, p.n_leaves, p.dims, p.mbits, M,
                p.meta_bits, p.payload_bits, w.leaf_bits, stream, (uint64_t*)out, w.params);
   }
-  BBX_LAUNCH("dec_finish", k_dec_finish, 1, 64, 0, s, w.params, d_status);
+  if (d_status) BBX_LAUNCH("dec_finish", k_dec_finish, 1, 64, 0, s, w.params, d_status);
   return hipGetLastError();
 }
 

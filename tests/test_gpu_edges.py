@@ -160,3 +160,17 @@ def test_decode_damaged(bbx, orc, ref_mode):
             assert got.tobytes() == np.ascontiguousarray(want).tobytes(), (trial, at)
         refused += want is None
     assert 0 < refused < 40
+
+
+# Reordered layout: lanes per sequence by leaf size (8, 16, 32, 64, a whole
+# wavefront and more), R-indices of one and two words, sets of few leaves.
+@pytest.mark.parametrize("n,r", [(1, 1), (40, 9), (5000, 9), (5000, 10), (5000, 17), (5000, 18), (5000, 33),
+                                 (9000, 34), (9000, 65), (9000, 66), (3000, 700), (270000, 1)])
+@pytest.mark.parametrize("dims,dtype,eb", [(3, np.float32, 1e-4), (2, np.float64, 1e-3), (3, np.float64, 1e-8)])
+def test_reordered_layout_shapes(bbx, orc, n, r, dims, dtype, eb):
+    pts = gen("cosmology", n, dims, dtype, seed=n + r)
+    s = orc.compress(pts, eb, "rel", r, ref_mode=1)
+    want, want_order = orc.export_sequences_reordered(s)
+    got, order = bbx.export_sequences_reordered(torch.from_numpy(np.frombuffer(s, np.uint8).copy()).cuda())
+    assert got.cpu().numpy().tobytes() == bytes(want)
+    assert list(order) == [int(a) for a in want_order][:dims]
