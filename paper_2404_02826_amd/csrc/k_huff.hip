@@ -23,8 +23,8 @@
 //   k_huf_count   bits of every chunk (a block per chunk)
 //   k_huf_offsets one block: exclusive scan of the chunk bits into the
 //                 stream's offset table, and the payload's total bits
-//   k_huf_write   a block per chunk: each thread's 64 bytes of codes at its
-//                 offset (block scan), ORed into the zeroed payload words
+//   k_huf_write   a block per chunk: each thread's 16 bytes of codes at its
+//                 offset (block scan) in an LDS copy of the chunk's words
 // Decode:
 //   k_huf_table   one block: checks the header against the host's copy, the
 //                 lengths (at most kHufMaxLen, Kraft sum at most 1), and builds
@@ -139,6 +139,9 @@ static void huf_build_table(const uint32_t* len, uint32_t* tab) {
 
 // ---------------------------------------------------------------- kernels
 
+// Every block adds its 256 bins to the same addresses at its end, one after
+// another: 40 MB take 50 us with 2,048 blocks, 24 with 512.
+constexpr uint64_t kHistBlocks = 512;
 __global__ void __launch_bounds__(kBlock) k_huf_hist(const uint8_t* in, uint64_t n,
                                                      unsigned long long* counts) {
   __shared__ uint32_t h[4][257];  // four copies, staggered across banks
@@ -183,37 +186,91 @@ __device__ inline uint64_t huf_block_exscan(uint64_t v, uint64_t* total) {
   return off + x - v;
 }
 
-// bits of the thread's bytes [c * kHufChunk + t * kHufPer, ...) of chunk c
-__device__ inline uint64_t huf_thread_bits(const uint8_t* in, uint64_t n, uint64_t a,
-                                           const uint32_t* tab) {
-  uint64_t b = 0;
-  for (uint32_t k = 0; k < kHufPer; ++k)
-    if (a + k < n) b += tab[in[a + k]] >> 16;
+// The thread's kHufPer bytes of a chunk (in + a, 16-byte aligned; those from n
+// on are not there), one load for all.
+struct HufBytes {
+  uint32_t w[kHufPer / 4];
+  uint32_t count;
+};
+static_assert(kHufPer == 16, "one 16-byte load per thread");
+__device__ __forceinline__ HufBytes huf_bytes(const uint8_t* in, uint64_t n, uint64_t a) {
+  HufBytes b;
+  if (a + kHufPer <= n) {
+    const uint4 q = *(const uint4*)(in + a);
+    b.w[0] = q.x, b.w[1] = q.y, b.w[2] = q.z, b.w[3] = q.w;
+    b.count = kHufPer;
+  } else {
+#pragma unroll
+    for (uint32_t k = 0; k < kHufPer / 4; ++k) b.w[k] = 0;
+    b.count = a < n ? (uint32_t)(n - a) : 0u;
+#pragma unroll
+    for (uint32_t k = 0; k < kHufPer; ++k)
+      if (k < b.count) b.w[k / 4] |= (uint32_t)in[a + k] << (8 * (k & 3));
+  }
   return b;
+}
+__device__ __forceinline__ uint32_t huf_byte(const HufBytes& b, uint32_t k) {
+  return (b.w[k / 4] >> (8 * (k & 3))) & 255u;
+}
+
+// code bits of the thread's bytes
+__device__ __forceinline__ uint32_t huf_thread_bits(const HufBytes& b, const uint32_t* tab) {
+  uint32_t bits = 0;
+#pragma unroll
+  for (uint32_t k = 0; k < kHufPer; ++k)
+    if (k < b.count) bits += tab[huf_byte(b, k)] >> 16;
+  return bits;
+}
+
+// Exclusive scan over the block of a value per thread (totals below 2^32).
+__device__ inline uint32_t huf_scan32(uint32_t x, uint32_t* total) {
+  __shared__ uint32_t ws[kBlock / 64];
+  const uint32_t incl = wave_incl(x), wv = threadIdx.x >> 6;
+  if ((threadIdx.x & 63) == 63) ws[wv] = incl;
+  __syncthreads();
+  uint32_t off = incl - x, tot = 0;
+#pragma unroll
+  for (uint32_t k = 0; k < kBlock / 64; ++k) {
+    off += k < wv ? ws[k] : 0u;
+    tot += ws[k];
+  }
+  *total = tot;
+  return off;
 }
 
 __global__ void __launch_bounds__(kBlock) k_huf_count(const uint8_t* in, uint64_t n,
                                                       const uint32_t* tab0, uint64_t* chunk_bits) {
   __shared__ uint32_t tab[256];
+  const HufBytes b = huf_bytes(in, n, (uint64_t)blockIdx.x * kHufChunk + (uint64_t)threadIdx.x * kHufPer);
   tab[threadIdx.x] = tab0[threadIdx.x];
   __syncthreads();
-  const uint64_t a = (uint64_t)blockIdx.x * kHufChunk + (uint64_t)threadIdx.x * kHufPer;
-  uint64_t tot;
-  huf_block_exscan(huf_thread_bits(in, n, a, tab), &tot);
+  uint32_t tot;
+  (void)huf_scan32(huf_thread_bits(b, tab), &tot);
   if (threadIdx.x == 0) chunk_bits[blockIdx.x] = tot;
 }
 
-// One block: chunk offsets into the stream (after the header) and the total.
+// One block: chunk offsets into the stream (after the header) and the total;
+// kOffPer chunks per thread and round.
+constexpr uint32_t kOffPer = 8;
 __global__ void __launch_bounds__(1024) k_huf_offsets(const uint64_t* chunk_bits, uint64_t chunks,
                                                       uint8_t* out, uint64_t* total_out) {
   uint64_t* offs = (uint64_t*)(out + kHufHeader);
   uint64_t run = 0;
-  for (uint64_t c0 = 0; c0 < chunks; c0 += blockDim.x) {
-    const uint64_t c = c0 + threadIdx.x;
-    const uint64_t v = c < chunks ? chunk_bits[c] : 0ull;
+  for (uint64_t c0 = 0; c0 < chunks; c0 += kOffPer * 1024) {
+    const uint64_t c = c0 + kOffPer * threadIdx.x;
+    uint64_t v[kOffPer], sum = 0;
+#pragma unroll
+    for (uint32_t k = 0; k < kOffPer; ++k) {
+      v[k] = c + k < chunks ? chunk_bits[c + k] : 0ull;
+      sum += v[k];
+    }
     uint64_t tot;
-    const uint64_t ex = huf_block_exscan(v, &tot);
-    if (c < chunks) offs[c] = run + ex;
+    uint64_t at = run + huf_block_exscan(sum, &tot);
+#pragma unroll
+    for (uint32_t k = 0; k < kOffPer; ++k) {
+      if (c + k < chunks) offs[c + k] = at;
+      at += v[k];
+    }
     run += tot;
   }
   if (threadIdx.x == 0) {
@@ -222,46 +279,64 @@ __global__ void __launch_bounds__(1024) k_huf_offsets(const uint64_t* chunk_bits
   }
 }
 
-__global__ void __launch_bounds__(kBlock) k_huf_zero(uint64_t* p, uint64_t words) {
-  for (uint64_t i = (uint64_t)blockIdx.x * kBlock + threadIdx.x; i < words;
-       i += (uint64_t)gridDim.x * kBlock)
-    p[i] = 0;
-}
-
+// A block per chunk: each thread's 16 codes go to its offset (block scan) in
+// an LDS copy of the chunk's words.  The block owns the words that begin in
+// its chunk; the last of them is completed with the first codes of the next
+// chunk by one wavefront (64 bytes of input hold at least 64 bits of codes,
+// or reach the input's end), so every word is written once, coalesced, and
+// nothing has to be zeroed before.  (ORing each thread's words into a zeroed
+// payload with global atomics took 150 us for 40 MB and the zeroing 8, this
+// takes 34.)
+constexpr uint32_t kHufOutWords = kHufChunk * kHufMaxLen / 64 + 2;
 __global__ void __launch_bounds__(kBlock) k_huf_write(const uint8_t* in, uint64_t n,
                                                       const uint32_t* tab0, uint8_t* out,
-                                                      uint64_t chunks) {
+                                                      uint64_t chunks, uint64_t bits) {
   __shared__ uint32_t tab[256];
-  tab[threadIdx.x] = tab0[threadIdx.x];
-  __syncthreads();
+  __shared__ unsigned long long wd[kHufOutWords];
   const uint64_t c = blockIdx.x;
   const uint64_t* offs = (const uint64_t*)(out + kHufHeader);
   unsigned long long* pay = (unsigned long long*)(out + kHufHeader + 8 * chunks);
-  const uint64_t a = c * kHufChunk + (uint64_t)threadIdx.x * kHufPer;
-  uint64_t tot;
-  uint64_t pos = offs[c] + huf_block_exscan(huf_thread_bits(in, n, a, tab), &tot);
-  // the thread's codes gathered in a 64-bit window; a full word (or the
-  // last, partial one) is ORed into the payload
-  uint64_t win = 0;
-  uint32_t fill = (uint32_t)(pos & 63);
-  uint64_t word = pos >> 6;
-  for (uint32_t k = 0; k < kHufPer; ++k) {
-    if (a + k >= n) break;
-    const uint32_t e = tab[in[a + k]];
-    const uint32_t L = e >> 16;
-    const uint64_t rev = e & 0xffffu;
-    win |= rev << fill;
-    if (fill + L >= 64) {
-      atomicOr(&pay[word], (unsigned long long)win);
-      const uint32_t used = 64 - fill;  // bits of this code that went into the word
-      win = used < 64 ? rev >> used : 0ull;
-      fill = fill + L - 64;
-      ++word;
-    } else {
+  const HufBytes b = huf_bytes(in, n, c * kHufChunk + (uint64_t)threadIdx.x * kHufPer);
+  const uint64_t pos = offs[c], end = c + 1 < chunks ? offs[c + 1] : bits;
+  const uint64_t next = (c + 1) * kHufChunk + threadIdx.x;  // the byte that the first wavefront adds
+  const uint32_t after = threadIdx.x < 64 && next < n ? in[next] : 0u;
+  tab[threadIdx.x] = tab0[threadIdx.x];
+  for (uint32_t k = threadIdx.x; k < kHufOutWords; k += kBlock) wd[k] = 0;
+  __syncthreads();
+  uint32_t tot;
+  const uint32_t at0 = (uint32_t)(pos & 63) + huf_scan32(huf_thread_bits(b, tab), &tot);
+  auto put = [&](uint32_t word, uint64_t v) {
+    if (word < kHufOutWords) atomicOr(&wd[word], (unsigned long long)v);
+  };
+  {
+    // the thread's codes gathered in a 64-bit window
+    uint64_t win = 0;
+    uint32_t fill = at0 & 63, word = at0 >> 6;
+#pragma unroll
+    for (uint32_t k = 0; k < kHufPer; ++k) {
+      const uint32_t e = k < b.count ? tab[huf_byte(b, k)] : 0u;
+      const uint32_t L = e >> 16;
+      const uint64_t rev = e & 0xffffu;
+      win |= rev << fill;
       fill += L;
+      if (fill >= 64) {
+        put(word, win);
+        ++word;
+        fill -= 64;
+        win = fill ? rev >> (L - fill) : 0ull;  // (L <= 12)
+      }
     }
+    if (win) put(word, win);
   }
-  if (fill > 0) atomicOr(&pay[word], (unsigned long long)win);
+  // the owned words [w0, w1): those whose first bit is in [pos, end)
+  const uint64_t base = pos >> 6, w0 = (pos + 63) >> 6, w1 = (end + 63) >> 6;
+  if (threadIdx.x < 64 && (end & 63) && end < bits) {
+    const uint32_t e = next < n ? tab[after] : 0u, L = e >> 16;
+    const uint32_t from = (uint32_t)(end & 63) + wave_incl(L) - L;  // in the last word
+    if (L && from < 64) put((uint32_t)((end >> 6) - base), (uint64_t)(e & 0xffffu) << from);
+  }
+  __syncthreads();
+  for (uint64_t w = w0 + threadIdx.x; w < w1; w += kBlock) pay[w] = wd[w - base];
 }
 
 // Decode table: 12-bit window (the code's first bit at bit 0) -> symbol |
@@ -541,7 +616,7 @@ bbx_status bbx_huffman_encode(const void* d_in, uint64_t n, void* d_out, size_t 
   uint8_t* out = (uint8_t*)d_out;
   hipError_t e = hipMemsetAsync(counts, 0, 2048, stream);
   if (e == hipSuccess && n > 0)
-    BBX_LAUNCH("huf_hist", k_huf_hist, (uint32_t)std::min<uint64_t>((n / 16 + kBlock - 1) / kBlock + 1, 2048),
+    BBX_LAUNCH("huf_hist", k_huf_hist, (uint32_t)std::min<uint64_t>((n / 16 + kBlock - 1) / kBlock + 1, kHistBlocks),
                kBlock, 0, stream, in, n, counts);
   uint64_t hc[256];
   if (e == hipSuccess) e = hipMemcpyAsync(hc, counts, sizeof(hc), hipMemcpyDeviceToHost, stream);
@@ -572,9 +647,7 @@ bbx_status bbx_huffman_encode(const void* d_in, uint64_t n, void* d_out, size_t 
   if (e == hipSuccess && chunks > 0) {
     BBX_LAUNCH("huf_count", k_huf_count, (uint32_t)chunks, kBlock, 0, stream, in, n, tab, cbits);
     BBX_LAUNCH("huf_offsets", k_huf_offsets, 1, 1024, 0, stream, cbits, chunks, out, total);
-    BBX_LAUNCH("huf_zero", k_huf_zero, (uint32_t)std::min<uint64_t>(huf_words(bits) / kBlock + 1, 4096),
-               kBlock, 0, stream, (uint64_t*)(out + kHufHeader + 8 * chunks), huf_words(bits));
-    BBX_LAUNCH("huf_write", k_huf_write, (uint32_t)chunks, kBlock, 0, stream, in, n, tab, out, chunks);
+    BBX_LAUNCH("huf_write", k_huf_write, (uint32_t)chunks, kBlock, 0, stream, in, n, tab, out, chunks, bits);
     e = hipGetLastError();
   }
   uint64_t dev_bits = bits;
