@@ -94,11 +94,12 @@ typedef enum { BBX_AOS = 0, BBX_SOA = 1 } bbx_layout;         /* [n][dims] or [d
  * exactly; the other members decode identically in both modes.  ref_mode 1
  * carries source indices through the partition (as a perm output does).
  * scatter_stage says how the partition levels that use global histograms
- * store a group of members: 1 = staged in on-chip memory in output order and
- * written with coalesced stores, 2 = stored straight from the ranks, 0 = the
- * library's choice by the level's chunk size (staged from 16,384 members per
- * block); like tile_override it never changes the stream, and all sets of a
- * batch share it.  level_blocks caps the number of blocks that each of the
+ * move a group of members: 0 = 16 bytes of consecutive codes per thread and
+ * axis, put into output order in on-chip memory and written four members at a
+ * time (the fastest at every size), 1 = rows of single codes, staged likewise
+ * and written one code at a time, 2 = rows of single codes stored straight
+ * from the ranks; like tile_override it never changes the stream, and all
+ * sets of a batch share it.  level_blocks caps the number of blocks that each of the
  * set's partition levels with global histograms is cut into (0 = the
  * library's choice: 1,024 for a set alone, the set's share of 4,096 by
  * particle count in a batch; otherwise 1..4096, the smaller of this and that
@@ -147,7 +148,7 @@ typedef struct {
   uint32_t tile_override; /* 0 (= 256), 256 or 512 */
   uint32_t ref_rule;      /* 0 (AABB centre) or 1 (fewest code bits) */
   uint32_t ref_mode;      /* 0 (reference code) or 1 (reference coordinates) */
-  uint32_t scatter_stage; /* 0 (by chunk size), 1 (always) or 2 (never) */
+  uint32_t scatter_stage; /* 0 (runs), 1 (staged rows) or 2 (direct rows) */
   uint32_t level_blocks;  /* 0 (library's choice) or 1..4096 */
   uint32_t reduce;        /* bit box reduction: 0 none, 1 (key: sum of widths), 2 (key: sum of lengths) */
   uint32_t split_rule;    /* 0 (median, axes in turn), 1 (widest axis), 2 (ceil(n/r) leaves), 3 (midpoint cells) */

@@ -607,8 +607,8 @@ def compress(pos: torch.Tensor, eb: float, eb_mode: str = "rel", leaf_size: int 
     ref_rule: 0 = leaf reference nearest the AABB centre (the paper's rule),
     1 = the member with the fewest code bits.  ref_mode: 0 = the reference
     stored as its codes, 1 = as its original coordinates (decoded exactly).
-    scatter_stage: how the global partition levels store their groups (0 =
-    by chunk size, 1 = staged, 2 = direct); level_blocks: cap on the blocks
+    scatter_stage: how the global partition levels move their groups (0 =
+    runs of codes, 1 = staged rows, 2 = direct rows); level_blocks: cap on the blocks
     per global partition level (0 = the library's choice); neither changes
     the stream.  reduce: the bit box reduction of Sec. 4.1 (1: key sum of
     widths, 2: key sum of box lengths), a version-2 stream.  split_rule: how

@@ -259,12 +259,12 @@ static void plan_batch(const SetIn* in, uint32_t nsets, BatchPlan* bp, std::vect
     }
     return cap ? std::min(b, cap) : b;
   };
+  bp->scatter_mode = in[0].prm.scatter_stage;
   bp->fold = 1;
   for (uint32_t s = 0; s < nsets; ++s)
     if (in[s].n > 0 && in[s].prm.level_pairs == 1 && !in[s].prm.split_rule) bp->fold = 0;
   std::vector<uint64_t> mm(nsets), qz(nsets), tl(nsets), bg(nsets), pm(nsets), pp(nsets);
   std::vector<uint64_t> rp(nsets, 0), rl(nsets, 0), rw(nsets, 0);
-  std::vector<uint8_t> stage_seen(kMaxDepth, 0);  // a set with global level k seen
   std::vector<std::vector<uint64_t>> lv(nsets), nd(nsets);
   std::vector<std::vector<uint8_t>> lk(nsets);  // per depth: the kernel family that handles it
   for (uint32_t s = 0; s < nsets; ++s) {
@@ -405,12 +405,7 @@ static void plan_batch(const SetIn* in, uint32_t nsets, BatchPlan* bp, std::vect
           if (!pair_second(D, k)) bp->sel_wide[k] = 1;
           if (pair_first(D, k)) bp->pair_wide[k] = 1;  // the second level's selects use these chunks
         }
-        if (fam == kFamGlobal) {  // by default staged only when every set's chunks are large
-          const uint32_t mode = in[0].prm.scatter_stage;
-          if (!stage_seen[k]) bp->scat_stage[k] = mode != 2;
-          stage_seen[k] = 1;
-          if (mode == 0 && sh.chunk_elems < kStageChunk) bp->scat_stage[k] = 0;
-        }
+        if (fam == kFamGlobal) bp->scat_stage[k] = bp->scatter_mode == 1;
         lv[s].push_back(sh.nodes * sh.chunks);
         nd[s].push_back(sh.nodes);
         if (kind == kLevelGlobal) {  // only these use selections and rows
@@ -677,8 +672,6 @@ static std::string check_plan(const SetIn* in, uint32_t nsets) {
       } else if (!pair_second(D, k) && !bp.lv_single[k]) {
         return where(s, k) + "scatter not launched";
       }
-      if (bp.scat_stage[k] && in[0].prm.scatter_stage == 0 && sh.chunk_elems < kStageChunk)
-        return where(s, k) + "staged scatter on short chunks";
       sel_need = std::max(sel_need, sh.nodes);
     }
     const uint64_t next_sel = s + 1 < nsets && descs[s + 1].n ? descs[s + 1].sel_off

@@ -25,7 +25,6 @@ constexpr int kGroup = kRows * kBlock;    // elements per streaming group
 constexpr uint64_t kLevelBlocks = 4096;   // most blocks per global level (cap of a target or share)
 constexpr uint64_t kSoloLevelBlocks = 1024;  // block target of a global level of a set alone
 constexpr uint64_t kLocalBlocks = 4096;   // levels of at least this many nodes run block-local
-constexpr uint32_t kStageChunk = 16384;   // the global scatter stages groups from this chunk size
 constexpr uint32_t kRedLdsBoxes = 4096;
 // Status of a set whose bound the grid cannot meet (eb_eff <= 0 or codes of
 // 30 bits or more): every later kernel skips it as it skips a failed set,
@@ -661,7 +660,8 @@ struct BatchPlan {
   uint8_t lv_local[kMaxDepth];   // some set handles level k one block per node
   uint8_t lv_global[kMaxDepth];  // some set handles level k with global histograms
   uint8_t sel_wide[kMaxDepth];   // some set's nodes have > 256 chunks at global level k
-  uint8_t scat_stage[kMaxDepth]; // every set's chunks at global level k hold >= kStageChunk codes
+  uint32_t scatter_mode;         // bbx_params.scatter_stage of the batch
+  uint8_t scat_stage[kMaxDepth]; // scatter_mode 1: some set has a global level k
   uint8_t lv_wave[kMaxDepth];    // some set handles level k one wavefront per node
   uint8_t lv_fused[kMaxDepth];   // some set handles levels k, k + 1 fused, a wavefront per node
   uint8_t lv_fused4[kMaxDepth];  // some set handles levels k, k + 1 fused, a block per node

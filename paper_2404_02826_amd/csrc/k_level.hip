@@ -29,10 +29,13 @@
 //   k_level_fused  two levels in one in-place pass with the node in
 //                  registers (the last four levels above the tile stage)
 //
-// Streaming kernels keep 8 loads in flight per thread (rows of 256 elements,
-// 8 rows per group) and synchronize once per 2048 elements.
+// The counting kernels keep 8 loads in flight per thread (rows of 256
+// elements, 8 rows per group) and synchronize once per 2048 elements; the
+// partition takes 16 bytes an axis per thread (part_range).
 // Nodes of <= r particles (possible only when r exceeds the tile capacity)
 // are leaves: they skip selection and are copied through.
+#include <type_traits>
+
 #include "bbx_internal.h"
 
 namespace bbx {
@@ -764,6 +767,211 @@ __device__ __forceinline__ uint32_t lh_slot(bool left, uint32_t bin) {
   return ((left ? 0u : kLhCopies) + (threadIdx.x & (kLhCopies - 1))) * kLhStride + bin;
 }
 
+// ---- the partition as it normally runs
+//
+// A thread takes R = 16 bytes of consecutive codes per axis (one load an
+// axis, of any element alignment), the block a group of kBlock R members.
+// Which go left and how many before them comes from per-thread counts and one
+// wavefront scan; each member's codes are put into LDS at its place in the
+// group's output order -- the left-goers, then from the next multiple of four
+// the right-goers, each one contiguous run of the node -- and four members a
+// thread go out with one 8- or 16-byte store per axis.  Rows of single codes
+// with a ballot per row, as in scatter_range below, issue about 100 vector
+// instructions per 64 members, which bounds them whatever the number of axes;
+// this moves its 12 bytes a member (three 16-bit axes, in and out) at the rate
+// of a copy.  The global levels of one set, rows before and runs now: 2^27
+// members 4772 and 4165 us (twelve levels, 4.6 TB/s), 2^24 499 and 430 (ten),
+// 33.6 million tracked 1345 and 1162, 13.1 million in two axes 388 and 336,
+// a million 133 and 122; 256 sets of 10^3 to 10^6 1110 and 877.
+template <typename KT>
+constexpr uint32_t kPartR = 16 / sizeof(KT);
+constexpr uint32_t kPartSlots = kGroup + 8;  // a group, the gap before its right run, slack for whole quads
+static_assert(kLhWords % 4 == 0 && kPartSlots % 8 == 0, "16-byte aligned arrays");
+
+struct __attribute__((packed, aligned(2))) Raw16 {
+  uint32_t x, y, z, w;
+};
+struct __attribute__((packed, aligned(2))) Raw8 {
+  uint32_t x, y;
+};
+
+// R consecutive elements from X on (16-bit ones two to a register)
+template <typename T, int R>
+struct PartRun {
+  uint32_t w[R * sizeof(T) / 4];
+  __device__ __forceinline__ uint32_t operator[](int i) const {
+    return sizeof(T) == 4 ? w[i] : ((i & 1) ? w[i >> 1] >> 16 : w[i >> 1] & 0xffffu);
+  }
+  __device__ __forceinline__ void load(const T* X) {
+#pragma unroll
+    for (int b = 0; b < (int)(R * sizeof(T) / 16); ++b) {
+      const Raw16 u = *(const Raw16*)((const uint8_t*)X + 16 * b);
+      w[4 * b] = u.x, w[4 * b + 1] = u.y, w[4 * b + 2] = u.z, w[4 * b + 3] = u.w;
+    }
+  }
+};
+
+// LDS of a group: 16-bit codes as (axis 0 | axis 1 << 16) words and halfwords
+// of the third axis; 32-bit codes (half as many members) a word per axis;
+// source indices a word each.
+template <bool TRACK>
+struct alignas(16) PartStage {
+  uint32_t a[kPartSlots];
+  uint32_t c[kPartSlots / 2];
+  uint32_t i[TRACK ? kPartSlots : 1];
+};
+
+template <typename KT, int NA, bool TRACK, typename Sel>
+__device__ __forceinline__ void part_range(uint32_t beg, uint32_t end, const KT* A0, const KT* A1, const KT* A2,
+                                           KT* B0, KT* B1, KT* B2, const uint32_t* is, uint32_t* id, uint32_t sz,
+                                           Sel&& select, bool cl, bool cr, uint32_t shn, uint32_t maskn,
+                                           uint32_t* lhist, PartStage<TRACK>& st, DevParams* P) {
+  constexpr int R = (int)kPartR<KT>;
+  constexpr uint32_t G = kBlock * R;  // members of a group
+  __shared__ __align__(16) uint32_t cnt[2][kBlock / 64];
+  const uint32_t lane = threadIdx.x & 63;
+  const uint32_t wv = (uint32_t)__builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+  const uint32_t t0 = threadIdx.x * R;  // the thread's first member in a group
+  PartRun<KT, R> k0, k1, k2, n0, n1, n2;
+  PartRun<uint32_t, TRACK ? R : 4> ki, ni;
+  // (a thread with a member of the chunk reads all R: the others lie in the
+  // axis's array or just behind it, in the workspace)
+  auto load = [&](uint32_t g, PartRun<KT, R>& x0, PartRun<KT, R>& x1, PartRun<KT, R>& x2, auto& xi) {
+    if (g + t0 >= end) return;
+    x0.load(A0 + g + t0);
+    x1.load(A1 + g + t0);
+    if (NA > 2) x2.load(A2 + g + t0);
+    if constexpr (TRACK)
+      if (is) xi.load(is + g + t0);
+  };
+  load(beg, k0, k1, k2, ki);
+  uint32_t v, jeq, lt_run, eq_run;
+  if (!select(&v, &jeq, &lt_run, &eq_run)) return;  // uniform
+  const uint32_t half = sz >> 1;
+  uint32_t* const hl = lhist + lh_slot(true, 0);
+  uint32_t* const hr = lhist + lh_slot(false, 0);
+  uint32_t buf = 0;
+  for (uint32_t g = beg; g < end; g += G, buf ^= 1) {
+    const uint32_t gsz = end - g < G ? end - g : G;
+    // members the thread holds; those past the chunk count as neither
+    const uint32_t mine = gsz == G ? R : (t0 >= gsz ? 0u : (gsz - t0 < (uint32_t)R ? gsz - t0 : R));
+    const bool full = gsz == G;
+    uint32_t x = 0;  // below the median | equal to it << 16
+    auto count = [&](auto whole) {
+#pragma unroll
+      for (int i = 0; i < R; ++i) {
+        const uint32_t k = k0[i];
+        const uint32_t one = k < v ? 1u : (k == v ? 0x10000u : 0u);
+        x += whole || (uint32_t)i < mine ? one : 0u;
+      }
+    };
+    if (full)
+      count(std::true_type());
+    else
+      count(std::false_type());
+    const uint32_t incl = wave_incl(x);
+    if (g + G < end) load(g + G, n0, n1, n2, ni);
+    if (lane == 63) cnt[buf][wv] = incl;
+    __syncthreads();
+    const uint4 c = *(const uint4*)&cnt[buf][0];
+    const uint32_t bw = (wv > 0 ? c.x : 0u) + (wv > 1 ? c.y : 0u) + (wv > 2 ? c.z : 0u) + incl - x;
+    const uint32_t all = c.x + c.y + c.z + c.w;
+    const uint32_t lbg = lt_run + umin32(eq_run, jeq);  // left-goers before the group
+    uint32_t E = eq_run + (bw >> 16);
+    const uint32_t lb = lt_run + (bw & 0xffffu) + umin32(E, jeq) - lbg;  // left-goers of the group before the thread's
+    lt_run = uniform32(lt_run + (all & 0xffffu));
+    eq_run = uniform32(eq_run + (all >> 16));
+    const uint32_t nl = uniform32(lt_run + umin32(eq_run, jeq) - lbg), rb = (nl + 3) & ~3u;
+    // places: consistent for any median, as the counts above follow the same rule
+    uint32_t sl = lb, sr = rb + (t0 - lb);
+    auto place = [&](auto whole, auto both) {  // both: both children split again
+#pragma unroll
+      for (int i = 0; i < R; ++i) {
+        if (!whole && (uint32_t)i >= mine) break;
+        const uint32_t k = k0[i];
+        const bool eq = k == v, left = k < v || (eq && E < jeq);
+        E += eq ? 1u : 0u;
+        const uint32_t at = left ? sl : sr;
+        sl += left ? 1u : 0u;
+        sr += left ? 0u : 1u;
+        if constexpr (sizeof(KT) == 2) {
+          st.a[at] = (k0.w[i >> 1] >> (16 * (i & 1)) & 0xffffu) | (k1[i] << 16);
+          if (NA > 2) ((uint16_t*)st.c)[at] = (uint16_t)k2[i];
+        } else {
+          st.a[at] = k;
+          st.a[kPartSlots / 2 + at] = k1[i];
+          if (NA > 2) st.c[at] = k2[i];
+        }
+        if constexpr (TRACK) st.i[at] = ki[i];
+        if (both || (left ? cl : cr)) atomicAdd((left ? hl : hr) + (k1[i] >> shn & maskn), 1u);
+      }
+    };
+    if (full && cl && cr)
+      place(std::true_type(), std::true_type());
+    else
+      place(std::false_type(), std::false_type());
+    __syncthreads();
+    // ---- out: quads of the left run, then of the right one
+    const uint32_t lq = rb / 4, nr = gsz - nl, rq = (nr + 3) / 4, rbase = half + (g - lbg);
+    for (uint32_t q = threadIdx.x; q < lq + rq; q += kBlock) {
+      const bool left = q < lq;
+      const uint32_t o = 4 * (left ? q : q - lq);  // in its run
+      const uint32_t num = umin32(4u, (left ? nl : nr) - o);
+      const uint32_t dest = (left ? lbg : rbase) + o;
+      if (dest + num > sz || dest + num < dest) {
+        check_failed(P, kChkScatterDrain);
+        continue;
+      }
+      uint32_t w[3][sizeof(KT)];  // four codes per axis
+      if constexpr (sizeof(KT) == 2) {
+        const uint4 a = *(const uint4*)&st.a[4 * q];
+        w[0][0] = (a.x & 0xffffu) | (a.y << 16), w[0][1] = (a.z & 0xffffu) | (a.w << 16);
+        w[1][0] = (a.x >> 16) | (a.y & 0xffff0000u), w[1][1] = (a.z >> 16) | (a.w & 0xffff0000u);
+        if (NA > 2) {
+          const uint2 b = *(const uint2*)&st.c[2 * q];
+          w[2][0] = b.x, w[2][1] = b.y;
+        }
+      } else {
+#pragma unroll
+        for (int d = 0; d < NA; ++d) {
+          const uint4 a = *(const uint4*)(d < 2 ? &st.a[d * (kPartSlots / 2) + 4 * q] : &st.c[4 * q]);
+          w[d][0] = a.x, w[d][1] = a.y, w[d][2] = a.z, w[d][3] = a.w;
+        }
+      }
+      KT* const B[3] = {B0 + dest, B1 + dest, B2 + dest};
+      if (num == 4) {
+#pragma unroll
+        for (int d = 0; d < NA; ++d) {
+          if constexpr (sizeof(KT) == 2)
+            *(Raw8*)B[d] = Raw8{w[d][0], w[d][1]};
+          else
+            *(Raw16*)B[d] = Raw16{w[d][0], w[d][1], w[d][2], w[d][3]};
+        }
+        if constexpr (TRACK)
+          if (id) {
+            const uint4 a = *(const uint4*)&st.i[4 * q];
+            *(Raw16*)(id + dest) = Raw16{a.x, a.y, a.z, a.w};
+          }
+      } else {
+#pragma unroll
+        for (uint32_t e = 0; e < 3; ++e)
+          if (e < num) {
+#pragma unroll
+            for (int d = 0; d < NA; ++d)
+              B[d][e] = sizeof(KT) == 2 ? (KT)(w[d][e >> 1] >> (16 * (e & 1))) : (KT)w[d][e & (sizeof(KT) - 1)];
+            if constexpr (TRACK)
+              if (id) id[dest + e] = st.i[4 * q + e];
+          }
+      }
+    }
+    k0 = n0, k1 = n1;
+    if (NA > 2) k2 = n2;
+    if constexpr (TRACK) ki = ni;
+  }
+}
+
+// ---- the partition with single-code rows (bbx_params.scatter_stage 1 and 2)
+//
 // Stable partition of a chunk in streaming groups of kGroup elements:
 // wavefront w of the block takes the 512 consecutive elements
 // [g + 512 w, g + 512 w + 512) of a group as 8 rows of 64.  Codes are handled
@@ -987,11 +1195,27 @@ __device__ __forceinline__ void scatter_range(uint32_t beg, uint32_t end, const 
   }
 }
 
-template <typename KT, bool TRACK, bool STAGE>
-__device__ void scatter_body(uint32_t depth, const SetDesc& S, DevParams* P, const LevelCtx& c,
-                             uint32_t v, uint32_t jeq, uint32_t lt_run, uint32_t eq_run,
-                             const uint8_t* src, uint8_t* dst, const uint32_t* isrc, uint32_t* idst,
-                             uint32_t* next_hist, uint32_t* lhist, uint32_t* stg) {
+// MODE: how a chunk is partitioned (kPartRuns, kPartStaged, kPartDirect).
+enum { kPartRuns = 0, kPartStaged = 1, kPartDirect = 2 };
+template <bool TRACK, int MODE>
+struct alignas(16) PartLds {
+  alignas(16) uint32_t lhist[kLhWords];
+  union {
+    PartStage<TRACK> runs;
+    uint32_t stg[MODE == kPartStaged ? (TRACK ? 4 : 3) * kGroup : 1];  // one staged group (codes, indices)
+  };
+  __device__ PartLds() {}
+};
+
+// select(v, jeq, lt_run, eq_run): the node's median, how many members equal
+// to it go left, and the members below and equal to it in the chunks before;
+// false when there is none (the chunk is left alone).  Called once the first
+// codes are on their way.
+template <typename KT, bool TRACK, int MODE, typename Sel>
+__device__ __forceinline__ void scatter_body(uint32_t depth, const SetDesc& S, DevParams* P, const LevelCtx& c,
+                                             Sel&& select, const uint8_t* src, uint8_t* dst,
+                                             const uint32_t* isrc, uint32_t* idst, uint32_t* next_hist,
+                                             PartLds<TRACK, MODE>& sm) {
   // next_hist: the bins of level depth + 1's nodes
   static_assert(kBlock == 256, "four wavefronts per block");
   const uint64_t n = S.n, kst = S.kst;
@@ -1007,7 +1231,7 @@ __device__ void scatter_body(uint32_t depth, const SetDesc& S, DevParams* P, con
   const uint32_t end = (uint32_t)(beg64 + c.sh.chunk_elems < sz64 ? beg64 + c.sh.chunk_elems : sz64);
   const uint32_t* is = isrc ? isrc + st : nullptr;
   uint32_t* id = idst ? idst + st : nullptr;
-  if (STAGE && !TRACK && is) {  // the staged path carries indices only with TRACK
+  if (MODE != kPartDirect && !TRACK && is) {  // only the direct path carries indices without TRACK
     if (threadIdx.x == 0) check_failed(P, kChkStageIdx);
     return;
   }
@@ -1032,6 +1256,7 @@ __device__ void scatter_body(uint32_t depth, const SetDesc& S, DevParams* P, con
                     !level_fused(S, depth + 1);
   const uint32_t wn = pn.width[0], shn = pn.shift[0], maskn = (1u << wn) - 1;
   const bool cl = fuse && half > r, cr = fuse && (sz - half) > r;  // children that split again
+  uint32_t* const lhist = sm.lhist;
   if (fuse)
     for (uint32_t i = threadIdx.x; i < kLhWords; i += kBlock) lhist[i] = 0;
   // axis order: split axis, next axis, third axis
@@ -1042,12 +1267,23 @@ __device__ void scatter_body(uint32_t depth, const SetDesc& S, DevParams* P, con
   KT* B0 = (KT*)dst + st + (uint64_t)d * kst;
   KT* B1 = (KT*)dst + st + (uint64_t)a1 * kst;
   KT* B2 = (KT*)dst + st + (uint64_t)a2 * kst;
-  if (dims == 3)
-    scatter_range<KT, 3, TRACK, STAGE>(beg, end, A0, A1, A2, B0, B1, B2, is, id, sz, v, jeq, lt_run,
-                                       eq_run, cl, cr, shn, maskn, lhist, stg, P);
-  else  // fewer axes: the missing ones repeat the split axis (same value, same slot)
-    scatter_range<KT, 3, TRACK, STAGE>(beg, end, A0, A1, A0, B0, B1, B0, is, id, sz, v, jeq, lt_run,
-                                       eq_run, cl, cr, shn, maskn, lhist, stg, P);
+  if constexpr (MODE == kPartRuns) {
+    // (the first barrier of the group loop comes between the bins' zeros and
+    // their first counts)
+    if (dims == 3)
+      part_range<KT, 3, TRACK>(beg, end, A0, A1, A2, B0, B1, B2, is, id, sz, select, cl, cr, shn, maskn, lhist,
+                               sm.runs, P);
+    else
+      part_range<KT, 2, TRACK>(beg, end, A0, A1, A1, B0, B1, B1, is, id, sz, select, cl, cr, shn, maskn, lhist,
+                               sm.runs, P);
+  } else {
+    uint32_t v, jeq, lt_run, eq_run;
+    if (!select(&v, &jeq, &lt_run, &eq_run)) return;
+    // fewer axes: the missing ones repeat the split axis (same value, same slot)
+    scatter_range<KT, 3, TRACK, MODE == kPartStaged>(beg, end, A0, A1, dims == 3 ? A2 : A0, B0, B1,
+                                                     dims == 3 ? B2 : B0, is, id, sz, v, jeq, lt_run, eq_run, cl,
+                                                     cr, shn, maskn, lhist, sm.stg, P);
+  }
   if (fuse) {
     __syncthreads();
     for (uint32_t child = 0; child < 2; ++child) {
@@ -1061,12 +1297,9 @@ __device__ void scatter_body(uint32_t depth, const SetDesc& S, DevParams* P, con
 }
 
 // TRACK: some set of the batch carries source indices (loaded with the codes).
-// STAGE: groups are staged in LDS before the stores (levels whose chunks hold
-// many groups; with one or two groups per block the extra barrier and LDS
-// round trip cost more than the coalesced stores save).
 // fold: the medians and chunk bases come from the histogram and rows of the
 // kernel before (fold_select); else from select launches (sel, cb).
-template <bool TRACK, bool STAGE>
+template <bool TRACK, int MODE>
 __global__ void __launch_bounds__(kBlock) k_scatter(uint32_t depth, uint32_t fold, uint32_t nsets,
                                                     const uint64_t* pre, const SetDesc* sets,
                                                     DevParams* params, const NodeSel* sel0,
@@ -1078,41 +1311,34 @@ __global__ void __launch_bounds__(kBlock) k_scatter(uint32_t depth, uint32_t fol
   DevParams* P = params + c.s;
   if (P->status != BBX_OK) return;
   if (level_is_local(S.n, depth) || pair_first(S, depth) || pair_second(S, depth)) return;
-  __shared__ uint32_t lhist[kLhWords];
-  __shared__ uint32_t stg[STAGE ? (TRACK ? 4 : 3) * kGroup : 1];  // one staged group (codes, indices)
+  __shared__ PartLds<TRACK, MODE> sm;
   level_bufs(S, depth, src0, dst0, isrc0, idst0);
   const uint32_t* isrc = S.track ? isrc0 + S.idx_off : nullptr;
   uint32_t* idst = S.track ? idst0 + S.idx_off : nullptr;
   uint32_t* const hist = hist0 + S.hist_off;
-  uint32_t v, jeq, lt_run, eq_run;
-  uint32_t* next_hist;
-  if (fold) {
-    const uint32_t t1 = hist_index(S, P->G, depth + 1);  // the next level's first histogram
-    next_hist = hist_region(S, t1, hist);
-    v = jeq = lt_run = eq_run = 0;
-    uint64_t st, sz;
-    node_span(S.n, depth, c.lb / c.sh.chunks, &st, &sz);
-    if (sz > S.r && !fold_select(depth, S, P, c, t1 - 1, sel0 + S.sel_off, hist, rows0 + S.rows_off, &v, &jeq,
-                                 &lt_run, &eq_run)) {
+  const uint32_t t1 = fold ? hist_index(S, P->G, depth + 1) : 0u;  // the next level's first histogram
+  uint32_t* const next_hist = fold ? hist_region(S, t1, hist) : hist_level(S, depth + 1, hist);
+  auto select = [&](uint32_t* v, uint32_t* jeq, uint32_t* lt_run, uint32_t* eq_run) -> bool {
+    if (fold) {
+      if (fold_select(depth, S, P, c, t1 - 1, sel0 + S.sel_off, hist, rows0 + S.rows_off, v, jeq, lt_run, eq_run))
+        return true;
       if (threadIdx.x == 0) check_failed(P, kChkLastDigit);
-      return;
+      return false;
     }
-  } else {
-    next_hist = hist_level(S, depth + 1, hist);
     const NodeSel ns = sel_level(S, depth, sel0)[c.lb / c.sh.chunks];
     const uint32_t* cb = cb_level(S, depth, cb0) + c.lb * 2;
-    v = ns.v, jeq = ns.jeq, lt_run = cb[0], eq_run = cb[1];
-  }
+    *v = uniform32(ns.v), *jeq = uniform32(ns.jeq), *lt_run = uniform32(cb[0]), *eq_run = uniform32(cb[1]);
+    return true;
+  };
   if (P->key16)
-    scatter_body<uint16_t, TRACK, STAGE>(depth, S, P, c, v, jeq, lt_run, eq_run, src0 + S.key_off,
-                                        dst0 + S.key_off, isrc, idst, next_hist, lhist, stg);
+    scatter_body<uint16_t, TRACK, MODE>(depth, S, P, c, select, src0 + S.key_off, dst0 + S.key_off, isrc, idst,
+                                        next_hist, sm);
   else
-    scatter_body<uint32_t, TRACK, STAGE>(depth, S, P, c, v, jeq, lt_run, eq_run, src0 + S.key_off,
-                                        dst0 + S.key_off, isrc, idst, next_hist, lhist, stg);
+    scatter_body<uint32_t, TRACK, MODE>(depth, S, P, c, select, src0 + S.key_off, dst0 + S.key_off, isrc, idst,
+                                        next_hist, sm);
   if (fold) {
     // the histogram after the one built here: the next level's second digit,
     // or (block-local) the level after it
-    const uint32_t t1 = hist_index(S, P->G, depth + 1);
     const uint64_t nblk = c.sh.nodes * c.sh.chunks;
     if (depth + 1 >= S.nglobal)
       hist_clear(S, t1 + 1, depth + 2, c.lb, nblk, hist);
@@ -1201,6 +1427,7 @@ __device__ void local_median(const KT* axis, uint64_t A, uint64_t B, uint32_t ra
 
 // A level whose nodes each fit one block: median and stable partition of
 // each node in one block, for every set whose level is local.
+template <bool TRACK>
 __global__ void __launch_bounds__(kBlock) k_level_local(uint32_t depth, uint32_t fold, uint32_t nsets,
                                                         const uint64_t* pre, const SetDesc* sets,
                                                         DevParams* params, uint8_t* src0,
@@ -1211,7 +1438,8 @@ __global__ void __launch_bounds__(kBlock) k_level_local(uint32_t depth, uint32_t
   DevParams* P = params + c.s;
   if (P->status != BBX_OK) return;
   if (level_kind(S.n, depth) != kLevelBlock || level_fused(S, depth)) return;
-  __shared__ uint32_t lhist[kLhWords];
+  __shared__ PartLds<TRACK, kPartRuns> sm;
+  uint32_t* const lhist = sm.lhist;
   __shared__ uint32_t red[16];
   level_bufs(S, depth, src0, dst0, isrc0, idst0);
   const uint32_t* isrc = S.track ? isrc0 + S.idx_off : nullptr;
@@ -1246,12 +1474,16 @@ __global__ void __launch_bounds__(kBlock) k_level_local(uint32_t depth, uint32_t
                    &jeq, lhist, red, h, pl);
     __syncthreads();  // lhist is reused by the partition
   }
+  auto select = [&](uint32_t* pv, uint32_t* pj, uint32_t* lt_run, uint32_t* eq_run) {
+    *pv = uniform32(v), *pj = uniform32(jeq), *lt_run = *eq_run = 0;
+    return true;
+  };
   if (P->key16)
-    scatter_body<uint16_t, false, false>(depth, S, P, c, v, jeq, 0, 0, src0 + S.key_off,
-                                         dst0 + S.key_off, isrc, idst, next_hist, lhist, nullptr);
+    scatter_body<uint16_t, TRACK, kPartRuns>(depth, S, P, c, select, src0 + S.key_off, dst0 + S.key_off, isrc,
+                                             idst, next_hist, sm);
   else
-    scatter_body<uint32_t, false, false>(depth, S, P, c, v, jeq, 0, 0, src0 + S.key_off,
-                                         dst0 + S.key_off, isrc, idst, next_hist, lhist, nullptr);
+    scatter_body<uint32_t, TRACK, kPartRuns>(depth, S, P, c, select, src0 + S.key_off, dst0 + S.key_off, isrc,
+                                             idst, next_hist, sm);
   if (fold) hist_clear(S, hist_index(S, P->G, depth) + 2, depth + 2, c.lb, c.sh.nodes, hist);
 }
 
@@ -2603,9 +2835,12 @@ hipError_t launch_pair(const BatchPlan& bp, const Ws& w, uint32_t k, hipStream_t
 }
 
 static void launch_scatter(const BatchPlan& bp, const Ws& w, uint32_t k, hipStream_t s) {
-  BBX_LAUNCH("level_scatter",
-             (bp.track ? (bp.scat_stage[k] ? k_scatter<true, true> : k_scatter<true, false>)
-                       : (bp.scat_stage[k] ? k_scatter<false, true> : k_scatter<false, false>)),
+  auto kern = bp.track ? k_scatter<true, kPartRuns> : k_scatter<false, kPartRuns>;
+  if (bp.scatter_mode == kPartStaged && bp.scat_stage[k])
+    kern = bp.track ? k_scatter<true, kPartStaged> : k_scatter<false, kPartStaged>;
+  else if (bp.scatter_mode != kPartRuns)
+    kern = bp.track ? k_scatter<true, kPartDirect> : k_scatter<false, kPartDirect>;
+  BBX_LAUNCH("level_scatter", kern,
              bp.g_lv[k], kBlock, 0, s, k, bp.fold, bp.nsets, w.pre + bp.o_lv[k], w.sets, w.params, w.sel,
              w.chunk_base, w.rows, w.keys[0], w.keys[1], w.idx[0], w.idx[1], w.hist);
 }
@@ -2625,8 +2860,8 @@ hipError_t launch_levels(const BatchPlan& bp, const Ws& w, hipStream_t s) {
     const uint64_t* plv = w.pre + bp.o_lv[k];
     const uint64_t* pnd = w.pre + bp.o_nd[k];
     if (bp.lv_local[k])
-      BBX_LAUNCH("level_local", k_level_local, bp.g_lc[k], kBlock, 0, s, k, bp.fold, bp.nsets,
-                 w.pre + bp.o_lc[k], w.sets, w.params, K0, K1, I0, I1, w.hist);
+      BBX_LAUNCH("level_local", bp.track ? k_level_local<true> : k_level_local<false>, bp.g_lc[k], kBlock, 0, s,
+                 k, bp.fold, bp.nsets, w.pre + bp.o_lc[k], w.sets, w.params, K0, K1, I0, I1, w.hist);
     if (bp.lv_wave[k])
       BBX_LAUNCH("level_wave", bp.track ? k_level_wave<true> : k_level_wave<false>,
                  (bp.g_wv[k] + kBlock / 64 - 1) / (kBlock / 64), kBlock, 0, s, k, bp.nsets,

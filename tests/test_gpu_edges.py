@@ -174,3 +174,17 @@ def test_reordered_layout_shapes(bbx, orc, n, r, dims, dtype, eb):
     got, order = bbx.export_sequences_reordered(torch.from_numpy(np.frombuffer(s, np.uint8).copy()).cuda())
     assert got.cpu().numpy().tobytes() == bytes(want)
     assert list(order) == [int(a) for a in want_order][:dims]
+
+
+# The partition by runs of codes: chunks that end inside a thread's run or a
+# group, starts off a 16-byte boundary, one group to several per chunk, two and
+# three axes, 16- and 32-bit codes, a median with many equal members.
+@pytest.mark.parametrize("n", [4097 * 4 - 1, 32771, 65536 + 2047, 4 * 65536 + 9, 300007])
+@pytest.mark.parametrize("kind,dims,dtype,eb", [("cosmology", 3, np.float32, 1e-4), ("uniform", 2, np.float32, 1e-3),
+                                                ("ties", 2, np.float64, 1e-7), ("ties", 3, np.float32, 1e-2),
+                                                ("cosmology", 3, np.float64, 1e-8), ("uniform", 2, np.float64, 1e-8)])
+def test_partition_runs(bbx, orc, n, kind, dims, dtype, eb):
+    pts = gen(kind, n, dims, dtype, seed=n % 997)
+    ref = orc.compress(pts, eb, "rel", 32, want_perm=True)
+    for blocks, perm in ((0, True), (0, False), (5, False)):
+        check_parity(orc, bbx, pts, eb, "rel", 32, level_blocks=blocks, want_perm=perm, ref=ref)
