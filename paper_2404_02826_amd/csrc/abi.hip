@@ -260,6 +260,7 @@ static void plan_batch(const SetIn* in, uint32_t nsets, BatchPlan* bp, std::vect
     return cap ? std::min(b, cap) : b;
   };
   bp->scatter_mode = in[0].prm.scatter_stage;
+  bp->tile_rows = bp->tile == 256;
   bp->fold = 1;
   for (uint32_t s = 0; s < nsets; ++s)
     if (in[s].n > 0 && in[s].prm.level_pairs == 1 && !in[s].prm.split_rule) bp->fold = 0;
@@ -329,6 +330,7 @@ static void plan_batch(const SetIn* in, uint32_t nsets, BatchPlan* bp, std::vect
         uint32_t K = 0;
         while (((n + (1ull << K) - 1) >> K) > bp->tile) ++K;
         D.gl = K;
+        if (!rows_tiles(n, K, D.r)) bp->tile_rows = 0;
       } else {
         D.tile_mode = 0;
         uint32_t K = 0;
@@ -680,6 +682,7 @@ static std::string check_plan(const SetIn* in, uint32_t nsets) {
     // the leaf stage below the partition levels
     const uint64_t leafsz = (n + (1ull << D.gl) - 1) >> D.gl;
     if (D.tile_mode ? leafsz > bp.tile : leafsz > D.r) return where(s, D.gl) + "leaf stage node too large";
+    if (D.tile_mode && bp.tile_rows && !rows_tiles(n, D.gl, D.r)) return where(s, D.gl) + "tile not for rows";
     if (D.gl > 0 && ((n + (1ull << (D.gl - 1)) - 1) >> (D.gl - 1)) <= (D.tile_mode ? bp.tile : D.r))
       return where(s, D.gl) + "a partition level above the leaf stage is not needed";
   }

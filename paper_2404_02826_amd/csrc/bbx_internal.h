@@ -380,6 +380,22 @@ __host__ __device__ inline uint64_t leaves_before_node(const TreeGeom& g, uint32
   return j * g.L[k][0] + big * (g.L[k][1] - g.L[k][0]);
 }
 
+// k_rows takes a tile of s members in rows of 64: four rows and three levels,
+// or for at most 128 members two rows and two levels, and leaves of at most 32
+// members.  rows_leaves: a node of s members is down to such leaves after lv
+// levels; rows_tiles: every tile of a set is (its tiles differ by one member).
+inline bool rows_leaves(uint64_t s, uint32_t r, uint32_t lv) {
+  if (lv == 0) return s <= r && s <= 32;
+  if (s <= r) return s <= 32;
+  return rows_leaves(s >> 1, r, lv - 1) && rows_leaves(s - (s >> 1), r, lv - 1);
+}
+inline bool rows_tiles(uint64_t n, uint32_t gl, uint32_t r) {
+  const uint64_t lo = n >> gl, hi = (n + (1ull << gl) - 1) >> gl;
+  for (uint64_t s = lo; s <= hi; ++s)
+    if (s > 256 || !rows_leaves(s, r, s > 128 ? 3 : 2)) return false;
+  return true;
+}
+
 // Radix-select digit plan for a code of G bits: the last pass takes the low
 // min(G, 8) bits; the bits above are split evenly into passes of <= 8 bits.
 struct DigitPlan {
@@ -605,6 +621,11 @@ __device__ inline uint32_t wave_max_dpp(uint32_t x) {
   return (uint32_t)__builtin_amdgcn_readlane((int)x, 63);
 }
 
+// a value that is the same in every lane, kept in a scalar register
+__device__ __forceinline__ uint32_t uniform32(uint32_t x) {
+  return (uint32_t)__builtin_amdgcn_readfirstlane((int)x);
+}
+
 // set bits of a wavefront mask in the lanes below this one
 __device__ inline uint32_t lanes_below(uint64_t m) {
   return __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
@@ -660,6 +681,7 @@ struct BatchPlan {
   uint8_t lv_local[kMaxDepth];   // some set handles level k one block per node
   uint8_t lv_global[kMaxDepth];  // some set handles level k with global histograms
   uint8_t sel_wide[kMaxDepth];   // some set's nodes have > 256 chunks at global level k
+  uint32_t tile_rows;            // every tile of the batch is one that k_rows takes
   uint32_t scatter_mode;         // bbx_params.scatter_stage of the batch
   uint8_t scat_stage[kMaxDepth]; // scatter_mode 1: some set has a global level k
   uint8_t lv_wave[kMaxDepth];    // some set handles level k one wavefront per node

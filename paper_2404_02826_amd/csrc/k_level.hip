@@ -554,11 +554,6 @@ __global__ void __launch_bounds__(kBlock) k_select_last_wide(uint32_t depth, uin
 
 // ---------------------------------------------------------------- selection without launches
 
-// a value that is the same in every lane, kept in a scalar register
-__device__ __forceinline__ uint32_t uniform32(uint32_t x) {
-  return (uint32_t)__builtin_amdgcn_readfirstlane((int)x);
-}
-
 // One wavefront: the digit of a 256-bin histogram that holds `rank`, and the
 // rank among that digit's members.  False when the bins hold fewer members
 // (inconsistent counts, never expected).

@@ -14,6 +14,9 @@
 // (0 when D_d = 0).  Finally the node is written back in output-slot order (reference
 // first in each leaf) with coalesced stores.
 //
+// k_rows: the same for tiles whose leaves hold at most 32 members, in rows of
+// registers; k_tile has the others.
+//
 // k_bigleaf: one workgroup per leaf when leaves exceed the tile capacity.
 #include <type_traits>
 
@@ -783,6 +786,583 @@ __global__ void __launch_bounds__(kBlock) k_bigleaf(uint32_t nsets, const uint64
                            S.perm, leaves0 + S.leaf_off, leaf_bits0 + S.leaf_off, S.ref_rule);
 }
 
+// ---------------------------------------------------------------- tiles by rows
+//
+// k_rows: one wavefront per tile, for sets whose tiles reach their leaves of
+// at most 32 members in three levels (two for tiles of at most 128), as sets
+// of r = 32 have at every size (rows_tiles).  Vector instructions bound this
+// stage: the radix passes of k_tile issue 1,370 of them per 256 members for
+// three levels and the boxes, whatever the members' bytes.  Here the tile's
+// members lie in R rows of 64, one per lane and row, and a node of level l in
+// its own R / 2^l rows, so a node's median is found bit by bit with one
+// compare and one scalar population count per row and bit, its prefix ranks
+// are counts of mask bits below the lane, and a member moves as one 8-byte
+// LDS word (codes minus the tile's minimum; 16 bytes in the pass for tiles
+// whose spans exceed 16 bits).  The last level leaves each leaf in its own 32
+// places, 32 / R lanes and R members a lane, so boxes are packed 16-bit
+// minima over a few DPP steps, and the node is written in output-slot order
+// straight from registers, R consecutive members per store.
+// 570 vector and 580 scalar instructions a whole tile.  2^27 members in whole
+// tiles 1,246 us (k_tile) and 652, 2^24 195 and 88, 33.6 million in tiles of
+// 128 642 and 326, 13.1 million in two axes 178 and 107, 256 sets 742 and 438;
+// vector and scalar issue are each about 70 % busy.  A capped grid whose
+// wavefronts loop over tiles: 108 registers for 43, 975 us at 2^27.
+template <bool WIDE, bool TRACK>
+struct RowTile {
+  typename std::conditional<WIDE, uint4, uint2>::type m[256];
+  uint32_t I[TRACK ? 256 : 1];  // source indices by position in the tile
+};
+
+typedef uint16_t u16x2 __attribute__((ext_vector_type(2)));
+__device__ __forceinline__ uint32_t pk_min(uint32_t a, uint32_t b) {
+  return __builtin_bit_cast(uint32_t, __builtin_elementwise_min(__builtin_bit_cast(u16x2, a),
+                                                                __builtin_bit_cast(u16x2, b)));
+}
+__device__ __forceinline__ uint32_t pk_max(uint32_t a, uint32_t b) {
+  return __builtin_bit_cast(uint32_t, __builtin_elementwise_max(__builtin_bit_cast(u16x2, a),
+                                                                __builtin_bit_cast(u16x2, b)));
+}
+// over the wavefront (ID: the operation's identity), uniform result
+template <uint32_t ID, typename F>
+__device__ __forceinline__ uint32_t wave_reduce(uint32_t x, F&& op) {
+  const int I = (int)ID;
+  x = op(x, (uint32_t)__builtin_amdgcn_update_dpp(I, (int)x, 0x111, 0xf, 0xf, false));
+  x = op(x, (uint32_t)__builtin_amdgcn_update_dpp(I, (int)x, 0x112, 0xf, 0xf, false));
+  x = op(x, (uint32_t)__builtin_amdgcn_update_dpp(I, (int)x, 0x114, 0xf, 0xf, false));
+  x = op(x, (uint32_t)__builtin_amdgcn_update_dpp(I, (int)x, 0x118, 0xf, 0xf, false));
+  x = op(x, (uint32_t)__builtin_amdgcn_update_dpp(I, (int)x, 0x142, 0xa, 0xf, false));
+  x = op(x, (uint32_t)__builtin_amdgcn_update_dpp(I, (int)x, 0x143, 0xc, 0xf, false));
+  return (uint32_t)__builtin_amdgcn_readlane((int)x, 63);
+}
+// the lane's partner in step i of a reduction over aligned groups of 8 or 16 lanes
+template <int STEP>
+__device__ __forceinline__ uint32_t group_partner(uint32_t v) {
+  constexpr int ctrl = STEP == 0 ? 0xB1 : STEP == 1 ? 0x4E : STEP == 2 ? 0x141 : 0x140;
+  return (uint32_t)__builtin_amdgcn_update_dpp((int)v, (int)v, ctrl, 0xf, 0xf, false);
+}
+template <int GS, typename F>
+__device__ __forceinline__ uint32_t group_reduce(uint32_t v, F&& op) {
+  v = op(v, group_partner<0>(v));
+  v = op(v, group_partner<1>(v));
+  v = op(v, group_partner<2>(v));
+  if constexpr (GS == 16) v = op(v, group_partner<3>(v));
+  return v;
+}
+// set bits of a mask in the lanes below this one, plus c
+__device__ __forceinline__ uint32_t lanes_below(uint64_t m, uint32_t c) {
+  return __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, c));
+}
+
+__device__ __forceinline__ uint64_t lane_mask(bool b) { return __builtin_amdgcn_ballot_w64(b); }
+__device__ __forceinline__ uint32_t bits_of(uint64_t m) { return (uint32_t)__builtin_popcountll(m); }
+
+// Medians of N nodes of R rows each (codes of G bits; places without a member
+// hold 0xffffffff): v the largest code that at most `rank` members are below,
+// lt the members below it, jeq how many of those equal to it go left.
+// rank = the node's size (a node that does not split) makes all go left.
+template <int N, int R>
+__device__ __forceinline__ void rows_median(const uint32_t (&k)[N * R], uint32_t G, const uint32_t (&rank)[N],
+                                            uint32_t (&v)[N], uint64_t (&lt)[N * R], uint32_t (&jeq)[N]) {
+#pragma unroll
+  for (int i = 0; i < N; ++i) v[i] = 0;
+  for (uint32_t bit = (1u << G) >> 1; bit; bit >>= 1) {
+#pragma unroll
+    for (int i = 0; i < N; ++i) {
+      const uint32_t t = v[i] | bit;
+      uint32_t c = 0;
+#pragma unroll
+      for (int j = 0; j < R; ++j) c += bits_of(lane_mask(k[i * R + j] < t));
+      v[i] = c <= rank[i] ? t : v[i];
+    }
+  }
+#pragma unroll
+  for (int i = 0; i < N; ++i) {
+    uint32_t c = 0;
+#pragma unroll
+    for (int j = 0; j < R; ++j) {
+      lt[i * R + j] = lane_mask(k[i * R + j] < v[i]);
+      c += bits_of(lt[i * R + j]);
+    }
+    jeq[i] = rank[i] - c;
+  }
+}
+
+template <int AX, typename M>
+__device__ __forceinline__ uint32_t row_code(const M& m) {
+  if constexpr (sizeof(M) == 8)
+    return AX == 0 ? m.x & 0xffffu : AX == 1 ? m.x >> 16 : m.y & 0xffffu;
+  else
+    return AX == 0 ? m.x : AX == 1 ? m.y : m.z;
+}
+
+template <typename M>
+__device__ __forceinline__ uint32_t row_slot(const M& m) {
+  if constexpr (sizeof(M) == 16) return m.w;
+  return 0;
+}
+// the value of the lane before in the row of 16 lanes
+__device__ __forceinline__ uint32_t row_prev(uint32_t v) {
+  return (uint32_t)__builtin_amdgcn_update_dpp((int)v, (int)v, 0x111, 0xf, 0xf, false);
+}
+
+// A level whose N nodes hold R >= 1 rows each: sz[i] their sizes, AX the split
+// axis.  Each half goes to its half of the node's places.  WHOLE: every place
+// holds a member and every node splits.
+template <int AX, int N, int R, bool WHOLE, typename M>
+__device__ __forceinline__ void rows_split(M* m, uint32_t G, const uint32_t (&sz)[N], uint32_t r) {
+  const uint32_t lane = threadIdx.x & 63;
+  M x[N * R];
+  uint32_t k[N * R], rank[N], v[N], jeq[N];
+  uint64_t lt[N * R];
+#pragma unroll
+  for (int i = 0; i < N * R; ++i) x[i] = m[64 * i + lane];
+#pragma unroll
+  for (int i = 0; i < N * R; ++i)
+    k[i] = WHOLE || lane + 64 * (i % R) < sz[i / R] ? row_code<AX>(x[i]) : 0xffffffffu;
+#pragma unroll
+  for (int i = 0; i < N; ++i) rank[i] = WHOLE || sz[i] > r ? sz[i] >> 1 : sz[i];
+  rows_median<N, R>(k, G, rank, v, lt, jeq);
+  wave_sync();
+#pragma unroll
+  for (int i = 0; i < N; ++i) {
+    if (jeq[i]) {  // uniform: members equal to the median, the first jeq of them to the left
+      uint32_t e = 0;
+#pragma unroll
+      for (int j = 0; j < R; ++j) {
+        const bool eq = k[i * R + j] == v[i];
+        const uint64_t em = lane_mask(eq);
+        lt[i * R + j] |= em & lane_mask(lanes_below(em, e) < jeq[i]);
+        e += bits_of(em);
+      }
+    }
+    uint32_t l = 0;
+#pragma unroll
+    for (int j = 0; j < R; ++j) {
+      const uint32_t p = lane + 64 * j, at = lanes_below(lt[i * R + j], l);
+      const bool left = __builtin_amdgcn_inverse_ballot_w64(lt[i * R + j]);
+      l += bits_of(lt[i * R + j]);
+      if (WHOLE || p < sz[i]) m[64 * R * i + (left ? at : 32 * R + p - at)] = x[i * R + j];
+    }
+  }
+  wave_sync();
+}
+
+template <int BYTES>
+struct __attribute__((packed, aligned(2))) RawWords {
+  uint32_t w[BYTES / 4];
+};
+
+// What a tile needs to know of its set (read before the first LDS access:
+// later reads would be vector loads in the way of the boxes).
+struct RowSet {
+  uint64_t kst, n_leaves;
+  uint32_t dims, r, gl, rule;
+  const uint32_t* idx;
+  uint32_t* perm;
+  LeafRec* leaves;
+  uint64_t* leaf_bits;
+};
+
+// One tile of at most 64 R members in R rows (WHOLE: exactly 64 R, which
+// split at every level); false: a span exceeds the 16 bits of the narrow words
+// (nothing was written).
+template <int R, bool WHOLE, bool WIDE, typename KT, bool TRACK>
+__device__ __forceinline__ bool rows_body(RowTile<WIDE, TRACK>& sm, uint32_t s_rt, uint64_t tst, uint64_t first_leaf,
+                                          const RowSet& S, DevParams* P, KT* keys) {
+  static_assert(R == 4 || R == 2, "three levels or two");
+  constexpr int LV = R == 4 ? 3 : 2, GS = 32 / R;  // levels; lanes per leaf
+  typedef typename std::remove_reference<decltype(sm.m[0])>::type M;
+  const uint32_t lane = threadIdx.x & 63;
+  const uint32_t s0 = WHOLE ? 64u * R : s_rt, dims = S.dims, r = S.r;
+  const uint32_t* const idx = S.idx;
+  const uint32_t d0 = S.gl % dims, d1 = d0 + 1 == dims ? 0 : d0 + 1, d2 = dims == 3 ? 3 - d0 - d1 : 2;
+  KT* const A0 = keys + (uint64_t)d0 * S.kst + tst;
+  KT* const A1 = keys + (uint64_t)d1 * S.kst + tst;
+  KT* const A2 = keys + (uint64_t)(dims == 3 ? d2 : d0) * S.kst + tst;
+  const bool track = TRACK && idx != nullptr;
+
+  // ---- the lane's R consecutive members (a lane with one member reads all R:
+  // the others lie in the axis's array or just behind it, in the workspace)
+  const uint32_t t0 = R * lane;
+  const uint32_t mine = t0 >= s0 ? 0u : umin32(s0 - t0, R);
+  RawWords<R * sizeof(KT)> w0 = {}, w1 = {}, w2 = {};
+  RawWords<4 * R> wi;
+  if (WHOLE || mine) {
+    w0 = *(const RawWords<R * sizeof(KT)>*)(A0 + t0);
+    w1 = *(const RawWords<R * sizeof(KT)>*)(A1 + t0);
+    if (dims == 3) w2 = *(const RawWords<R * sizeof(KT)>*)(A2 + t0);
+    if (track) wi = *(const RawWords<4 * R>*)(idx + tst + t0);
+  }
+  auto code = [](const RawWords<R * sizeof(KT)>& w, int i) -> uint32_t {
+    return sizeof(KT) == 4 ? w.w[i] : ((i & 1) ? w.w[i >> 1] >> 16 : w.w[i >> 1] & 0xffffu);
+  };
+  uint32_t c0[R], c1[R], c2[R];
+#pragma unroll
+  for (int i = 0; i < R; ++i) {
+    c0[i] = code(w0, i), c1[i] = code(w1, i), c2[i] = code(w2, i);
+    // a place without a member repeats the lane's first one
+    if (!WHOLE && (uint32_t)i >= mine) c0[i] = c0[0], c1[i] = c1[0], c2[i] = c2[0];
+  }
+
+  // ---- minima and spans per axis (of an empty lane: the identities)
+  uint32_t m0, m1, m2, G0, G1, G2;
+  if constexpr (sizeof(KT) == 2 && !WIDE) {
+    uint32_t lo = 0xffffffffu, hi = 0, lh = 0xffffffffu;  // axes 0 and 1; axis 2 and its complement
+    if (WHOLE || mine) {
+#pragma unroll
+      for (int i = 0; i < R; ++i) {
+        const uint32_t a = c0[i] | c1[i] << 16, c = c2[i] | ~c2[i] << 16;
+        lo = pk_min(lo, a), hi = pk_max(hi, a), lh = pk_min(lh, c);
+      }
+    }
+    lo = wave_reduce<0xffffffffu>(lo, pk_min);
+    hi = wave_reduce<0u>(hi, pk_max);
+    lh = wave_reduce<0xffffffffu>(lh, pk_min);
+    m0 = lo & 0xffffu, m1 = lo >> 16, m2 = lh & 0xffffu;
+    G0 = bitlen32((hi & 0xffffu) - m0), G1 = bitlen32((hi >> 16) - m1), G2 = bitlen32((~lh >> 16) - m2);
+  } else {
+    uint32_t lo[3] = {0xffffffffu, 0xffffffffu, 0xffffffffu}, hi[3] = {0, 0, 0};
+    if (WHOLE || mine) {
+#pragma unroll
+      for (int i = 0; i < R; ++i) {
+        lo[0] = umin32(lo[0], c0[i]), lo[1] = umin32(lo[1], c1[i]), lo[2] = umin32(lo[2], c2[i]);
+        hi[0] = umax32(hi[0], c0[i]), hi[1] = umax32(hi[1], c1[i]), hi[2] = umax32(hi[2], c2[i]);
+      }
+    }
+    m0 = wave_min_dpp(lo[0]), m1 = wave_min_dpp(lo[1]), m2 = wave_min_dpp(lo[2]);
+    G0 = bitlen32(wave_max_dpp(hi[0]) - m0), G1 = bitlen32(wave_max_dpp(hi[1]) - m1);
+    G2 = bitlen32(wave_max_dpp(hi[2]) - m2);
+    if (!WIDE && umax32(G0, umax32(G1, G2)) > 16) return false;
+  }
+
+  // ---- level 0, members in lane order
+  const uint32_t rank0 = WHOLE || s0 > r ? s0 >> 1 : s0;
+  {
+    uint32_t k[R];
+    const uint32_t rank[1] = {rank0};
+    uint32_t v[1], jeq[1];
+    uint64_t lt[R];
+#pragma unroll
+    for (int i = 0; i < R; ++i) k[i] = WHOLE || (uint32_t)i < mine ? c0[i] - m0 : 0xffffffffu;
+    rows_median<1, R>(k, G0, rank, v, lt, jeq);
+    if (jeq[0]) {
+      uint32_t e = 0;
+#pragma unroll
+      for (int i = 0; i < R; ++i) e = lanes_below(lane_mask(k[i] == v[0]), e);
+#pragma unroll
+      for (int i = 0; i < R; ++i) {
+        const bool eq = k[i] == v[0];
+        lt[i] |= lane_mask(eq) & lane_mask(e < jeq[0]);
+        e += eq ? 1u : 0u;
+      }
+    }
+    uint32_t at = 0;
+#pragma unroll
+    for (int i = 0; i < R; ++i) at = lanes_below(lt[i], at);
+#pragma unroll
+    for (int i = 0; i < R; ++i) {
+      const bool left = __builtin_amdgcn_inverse_ballot_w64(lt[i]);
+      const uint32_t p = t0 + i, dest = left ? at : 32 * R + p - at;
+      at += left ? 1u : 0u;
+      M x;
+      if constexpr (WIDE) {
+        x = M{c0[i] - m0, c1[i] - m1, c2[i] - m2, p};
+      } else {
+        const uint32_t q2 = c2[i] - m2;
+        x = M{(c0[i] - m0) | (c1[i] - m1) << 16, q2 | (TRACK ? p : ~q2) << 16};
+      }
+      if (WHOLE || (uint32_t)i < mine) {
+        sm.m[dest] = x;
+        if (track) sm.I[p] = wi.w[i];
+      }
+    }
+  }
+  wave_sync();
+
+  // ---- the levels below
+  const uint32_t s1[2] = {rank0, s0 - rank0};
+  rows_split<1, 2, R / 2, WHOLE>(sm.m, G1, s1, r);
+  if constexpr (R == 4) {
+    const uint32_t h0 = WHOLE || s1[0] > r ? s1[0] >> 1 : s1[0], h1 = WHOLE || s1[1] > r ? s1[1] >> 1 : s1[1];
+    const uint32_t s2[4] = {h0, s1[0] - h0, h1, s1[1] - h1};
+    if (dims == 3)
+      rows_split<2, 4, 1, WHOLE>(sm.m, G2, s2, r);
+    else
+      rows_split<0, 4, 1, WHOLE>(sm.m, G0, s2, r);
+  }
+
+  // ---- the leaf of the lane's group: its start and size in the tile (a node
+  // that did not split leaves its right half empty), its number
+  const uint32_t c = lane / GS, sub = lane & (GS - 1);
+  uint32_t ls = 32 * c, lz = 32, nth = c;
+  if (!WHOLE) {
+    ls = 0, lz = s0;
+#pragma unroll
+    for (int l = 0; l < LV; ++l) {
+      const uint32_t h = lz > r ? lz >> 1 : lz;
+      const bool right = c >> (LV - 1 - l) & 1;
+      ls += right ? h : 0u;
+      lz = right ? lz - h : h;
+    }
+    nth = lanes_below(lane_mask(lz > 0), 0u) / GS;
+  }
+  const uint64_t lid = first_leaf + nth;
+  const uint32_t l0 = 32 * c, o0 = R * sub;  // the leaf's places; the lane's first member
+  M x[R];
+#pragma unroll
+  for (int i = 0; i < R; ++i)  // (places without a member repeat the leaf's last one)
+    x[i] = sm.m[l0 + (WHOLE ? o0 + i : lz ? umin32(o0 + i, lz - 1) : 0u)];
+
+  // ---- bit box: per axis minimum and maximum, over the lane and its group
+  uint32_t mn[3], mx[3];
+  if constexpr (WIDE) {
+    mn[0] = mn[1] = mn[2] = 0xffffffffu, mx[0] = mx[1] = mx[2] = 0;
+#pragma unroll
+    for (int i = 0; i < R; ++i) {
+      mn[0] = umin32(mn[0], x[i].x), mn[1] = umin32(mn[1], x[i].y), mn[2] = umin32(mn[2], x[i].z);
+      mx[0] = umax32(mx[0], x[i].x), mx[1] = umax32(mx[1], x[i].y), mx[2] = umax32(mx[2], x[i].z);
+    }
+    mn[0] = group_reduce<GS>(mn[0], umin32), mx[0] = group_reduce<GS>(mx[0], umax32);
+    mn[1] = group_reduce<GS>(mn[1], umin32), mx[1] = group_reduce<GS>(mx[1], umax32);
+    mn[2] = group_reduce<GS>(mn[2], umin32), mx[2] = group_reduce<GS>(mx[2], umax32);
+  } else {
+    uint32_t lo = 0xffffffffu, hi = 0, lh = 0xffffffffu;
+#pragma unroll
+    for (int i = 0; i < R; ++i) {
+      lo = pk_min(lo, x[i].x), hi = pk_max(hi, x[i].x);
+      lh = pk_min(lh, TRACK ? (x[i].y & 0xffffu) | ~x[i].y << 16 : x[i].y);
+    }
+    lo = group_reduce<GS>(lo, pk_min);
+    hi = group_reduce<GS>(hi, pk_max);
+    lh = group_reduce<GS>(lh, pk_min);
+    mn[0] = lo & 0xffffu, mn[1] = lo >> 16, mn[2] = lh & 0xffffu;
+    mx[0] = hi & 0xffffu, mx[1] = hi >> 16, mx[2] = ~lh >> 16;
+  }
+
+  // ---- reference: the member nearest the box's centre (squared distance in
+  // doubled code space: at most three times the square of the largest span) or
+  // with the fewest code bits; the first one on ties (a repeated member comes
+  // after the one it repeats)
+  uint32_t ref = 0;
+  auto width = [](uint32_t q, uint32_t a, uint32_t b) { return width_of(umax32(q - a, b - q)); };
+  if (S.rule || umax32(G0, umax32(G1, G2)) <= 15) {
+    uint32_t dist[R];
+    if (S.rule) {
+#pragma unroll
+      for (int i = 0; i < R; ++i)
+        dist[i] = width(row_code<0>(x[i]), mn[0], mx[0]) + width(row_code<1>(x[i]), mn[1], mx[1]) +
+                  width(row_code<2>(x[i]), mn[2], mx[2]);
+    } else {  // (spans of 15 bits: products of 24 bits suffice)
+      const uint32_t a0 = mn[0] + mx[0], a1 = mn[1] + mx[1], a2 = mn[2] + mx[2];
+#pragma unroll
+      for (int i = 0; i < R; ++i) {
+        const int u0 = (int)(2 * row_code<0>(x[i]) - a0), u1 = (int)(2 * row_code<1>(x[i]) - a1);
+        const int u2 = (int)(2 * row_code<2>(x[i]) - a2);
+        dist[i] = (uint32_t)(u0 * u0) + (uint32_t)(u1 * u1) + (uint32_t)(u2 * u2);
+      }
+    }
+    uint32_t low = dist[0];
+    ref = o0;
+#pragma unroll
+    for (int i = 1; i < R; ++i) {
+      ref = dist[i] < low ? o0 + i : ref;
+      low = umin32(dist[i], low);
+    }
+    uint64_t best = (uint64_t)low << 32 | ref;  // (distance or bits, member)
+    auto take = [&](auto step) __attribute__((always_inline)) {
+      constexpr int st = decltype(step)::value;
+      const uint64_t u = (uint64_t)group_partner<st>((uint32_t)(best >> 32)) << 32 | group_partner<st>((uint32_t)best);
+      best = u < best ? u : best;
+    };
+    take(std::integral_constant<int, 0>{});
+    take(std::integral_constant<int, 1>{});
+    take(std::integral_constant<int, 2>{});
+    if constexpr (GS == 16) take(std::integral_constant<int, 3>{});
+    ref = (uint32_t)best;
+  } else {
+    uint64_t best = ~0ull;
+#pragma unroll
+    for (int i = 0; i < R; ++i) {
+      const int64_t u0 = 2 * (int64_t)row_code<0>(x[i]) - mn[0] - mx[0];
+      const int64_t u1 = 2 * (int64_t)row_code<1>(x[i]) - mn[1] - mx[1];
+      const int64_t u2 = 2 * (int64_t)row_code<2>(x[i]) - mn[2] - mx[2];
+      const uint64_t dist = (uint64_t)(u0 * u0) + (uint64_t)(u1 * u1) + (uint64_t)(u2 * u2);
+      if (dist < best) best = dist, ref = o0 + i;
+    }
+    auto take = [&](auto step) __attribute__((always_inline)) {
+      constexpr int st = decltype(step)::value;
+      const uint64_t u = (uint64_t)group_partner<st>((uint32_t)(best >> 32)) << 32 | group_partner<st>((uint32_t)best);
+      const uint32_t p = group_partner<st>(ref);
+      if (u < best || (u == best && p < ref)) best = u, ref = p;
+    };
+    take(std::integral_constant<int, 0>{});
+    take(std::integral_constant<int, 1>{});
+    take(std::integral_constant<int, 2>{});
+    if constexpr (GS == 16) take(std::integral_constant<int, 3>{});
+  }
+  const M xr = sm.m[l0 + ref];
+  const uint32_t rs = TRACK ? (WIDE ? row_slot(xr) : xr.y >> 16) : 0u;
+
+  // ---- the leaf's record and the members in output-slot order, the reference first
+  if (sub == 0 && lz) {
+    if (lid < S.n_leaves) {
+      const uint32_t q0 = row_code<0>(xr), q1 = row_code<1>(xr), q2 = row_code<2>(xr);
+      const uint32_t b0 = width(q0, mn[0], mx[0]), b1 = width(q1, mn[1], mx[1]), b2 = width(q2, mn[2], mx[2]);
+      const uint32_t f0 = q0 + m0, f1 = q1 + m1, f2 = q2 + m2;
+      LeafRec rec;
+      rec.start = (uint32_t)(tst + ls);
+      rec.size = lz;
+      rec.m = b0 << (8 * d0) | b1 << (8 * d1) | b2 << (8 * d2);
+      rec.qref[0] = d0 == 0 ? f0 : (d1 == 0 ? f1 : f2);
+      rec.qref[1] = d0 == 1 ? f0 : (d1 == 1 ? f1 : f2);
+      rec.qref[2] = d0 == 2 ? f0 : (d1 == 2 ? f1 : f2);
+      rec.ref_src = track ? sm.I[rs] : 0u;
+      S.leaves[lid] = rec;
+      S.leaf_bits[lid] = (uint64_t)((lz - 1) * (b0 + b1 + b2));
+    } else {
+      check_failed(P, kChkTileLeaves);  // leaf count mismatch: never expected
+    }
+  }
+  M y[R];
+  {
+    M prev;  // the member before the lane's first one
+    if constexpr (WIDE) {
+      prev = M{row_prev(x[R - 1].x), row_prev(x[R - 1].y), row_prev(x[R - 1].z), TRACK ? row_prev(x[R - 1].w) : 0u};
+    } else {
+      prev = M{row_prev(x[R - 1].x), row_prev(x[R - 1].y)};
+    }
+#pragma unroll
+    for (int i = 0; i < R; ++i) y[i] = o0 + i <= ref ? (i ? x[i ? i - 1 : 0] : prev) : x[i];
+    if (sub == 0) y[0] = xr;
+  }
+  const uint32_t num = lz > o0 ? umin32(lz - o0, R) : 0u;
+  auto put = [&](KT* A, auto ax_tag, uint32_t base) __attribute__((always_inline)) {
+    constexpr int AX = decltype(ax_tag)::value;
+    KT* const D = A + (ls + o0);
+    uint32_t q[R];
+#pragma unroll
+    for (int i = 0; i < R; ++i) q[i] = row_code<AX>(y[i]) + base;
+    if (num == R) {
+      RawWords<R * sizeof(KT)> w;
+#pragma unroll
+      for (int i = 0; i < (int)(R * sizeof(KT) / 4); ++i)
+        w.w[i] = sizeof(KT) == 4 ? q[i] : q[2 * i % R] | q[(2 * i + 1) % R] << 16;
+      *(RawWords<R * sizeof(KT)>*)D = w;
+    } else {
+#pragma unroll
+      for (int i = 0; i < R - 1; ++i)
+        if ((uint32_t)i < num) D[i] = (KT)q[i];
+    }
+  };
+  put(A0, std::integral_constant<int, 0>{}, m0);
+  put(A1, std::integral_constant<int, 1>{}, m1);
+  if (dims == 3) put(A2, std::integral_constant<int, 2>{}, m2);
+  if constexpr (TRACK) {
+    if (track && S.perm) {
+#pragma unroll
+      for (int i = 0; i < R; ++i)
+        if ((uint32_t)i < num) S.perm[tst + ls + o0 + i] = sm.I[WIDE ? row_slot(y[i]) : y[i].y >> 16];
+    }
+  }
+  return true;
+}
+
+template <bool WIDE, bool TRACK>
+__device__ __forceinline__ void rows_node(uint32_t nsets, const uint64_t* pre, const SetDesc* sets,
+                                          DevParams* params, uint8_t* keys0, uint8_t* keys1, uint32_t* idx0,
+                                          uint32_t* idx1, LeafRec* leaves0, uint64_t* leaf_bits0, uint32_t* defer,
+                                          uint32_t gtile, RowTile<WIDE, TRACK>& sm) {
+  const uint32_t s = find_set(pre, nsets, gtile);
+  const SetDesc& S = sets[s];
+  DevParams* P = params + s;
+  if (P->status != BBX_OK) return;
+  const uint64_t j = gtile - pre[s];
+  const uint32_t buf = key_buf(S, S.gl);  // the buffer holding the codes at the leaf stage
+  uint8_t* keys = (buf ? keys1 : keys0) + S.key_off;
+  const RowSet rs = {S.kst,
+                     S.n_leaves,
+                     S.dims,
+                     S.r,
+                     S.gl,
+                     S.ref_rule,
+                     TRACK && S.track ? (buf ? idx1 : idx0) + S.idx_off : nullptr,
+                     S.perm,
+                     leaves0 + S.leaf_off,
+                     leaf_bits0 + S.leaf_off};
+  uint64_t tst, s64;
+  node_span(S.n, S.gl, j, &tst, &s64);
+  if (s64 > 256) {  // launch plan violated: never expected
+    if ((threadIdx.x & 63) == 0) check_failed(P, kChkTileRange);
+    return;
+  }
+  const uint32_t s0 = (uint32_t)s64;
+  const uint64_t first = leaves_before_node(S.geom, S.gl, j, tst);
+  bool ok;
+  if (P->key16) {
+    uint16_t* K = (uint16_t*)keys;
+    if constexpr (!WIDE) {
+      if (s0 == 256)
+        ok = rows_body<4, true, WIDE, uint16_t, TRACK>(sm, s0, tst, first, rs, P, K);
+      else if (s0 == 128)
+        ok = rows_body<2, true, WIDE, uint16_t, TRACK>(sm, s0, tst, first, rs, P, K);
+      else
+        ok = s0 > 128 ? rows_body<4, false, WIDE, uint16_t, TRACK>(sm, s0, tst, first, rs, P, K)
+                      : rows_body<2, false, WIDE, uint16_t, TRACK>(sm, s0, tst, first, rs, P, K);
+    } else {
+      ok = s0 > 128 ? rows_body<4, false, WIDE, uint16_t, TRACK>(sm, s0, tst, first, rs, P, K)
+                    : rows_body<2, false, WIDE, uint16_t, TRACK>(sm, s0, tst, first, rs, P, K);
+    }
+  } else {
+    uint32_t* K = (uint32_t*)keys;
+    ok = s0 > 128 ? rows_body<4, false, WIDE, uint32_t, TRACK>(sm, s0, tst, first, rs, P, K)
+                  : rows_body<2, false, WIDE, uint32_t, TRACK>(sm, s0, tst, first, rs, P, K);
+  }
+  if (!ok && (threadIdx.x & 63) == 0) defer[1 + atomicAdd(&defer[0], 1u)] = gtile;  // the wide pass takes it
+}
+
+// first pass: every tile, 16-bit tile codes
+template <bool TRACK>
+__global__ void __launch_bounds__(kBlock) k_rows(uint32_t ntiles, uint32_t nsets, const uint64_t* pre,
+                                                 const SetDesc* sets, DevParams* params, uint8_t* keys0,
+                                                 uint8_t* keys1, uint32_t* idx0, uint32_t* idx1, LeafRec* leaves0,
+                                                 uint64_t* leaf_bits0, uint32_t* defer) {
+  __shared__ RowTile<false, TRACK> sm[kBlock / 64];
+  const uint32_t wv = uniform32(threadIdx.x >> 6), gtile = blockIdx.x * (kBlock / 64) + wv;
+  if (gtile < ntiles)
+    rows_node<false, TRACK>(nsets, pre, sets, params, keys0, keys1, idx0, idx1, leaves0, leaf_bits0, defer, gtile,
+                            sm[wv]);
+}
+
+// second pass and only pass of grids of few tiles, as k_tile_wide
+template <bool TRACK>
+__global__ void __launch_bounds__(64) k_rows_wide(uint32_t nsets, const uint64_t* pre, const SetDesc* sets,
+                                                  DevParams* params, uint8_t* keys0, uint8_t* keys1,
+                                                  uint32_t* idx0, uint32_t* idx1, LeafRec* leaves0,
+                                                  uint64_t* leaf_bits0, const uint32_t* defer) {
+  __shared__ RowTile<true, TRACK> sm;
+  const uint32_t count = defer ? defer[0] : gridDim.x;
+  for (uint32_t q = blockIdx.x; q < count; q += gridDim.x) {
+    rows_node<true, TRACK>(nsets, pre, sets, params, keys0, keys1, idx0, idx1, leaves0, leaf_bits0, nullptr,
+                           defer ? defer[1 + q] : q, sm);
+    wave_sync();  // the next tile reuses the LDS
+  }
+}
+
+template <bool TRACK>
+static void launch_rows(const BatchPlan& bp, const Ws& w, hipStream_t s) {
+  if (bp.g_tile <= kTileOnce) {
+    BBX_LAUNCH("tile", k_rows_wide<TRACK>, bp.g_tile, 64, 0, s, bp.nsets, w.pre + bp.o_tile, w.sets, w.params,
+               w.keys[0], w.keys[1], w.idx[0], w.idx[1], w.leaves, w.leaf_bits, (const uint32_t*)nullptr);
+    return;
+  }
+  BBX_LAUNCH("tile", k_rows<TRACK>, (bp.g_tile + kBlock / 64 - 1) / (kBlock / 64), kBlock, 0, s,
+             (uint32_t)bp.g_tile, bp.nsets, w.pre + bp.o_tile, w.sets, w.params, w.keys[0], w.keys[1], w.idx[0],
+             w.idx[1], w.leaves, w.leaf_bits, w.tile_defer);
+  const uint64_t gw = bp.g_tile < 4096 ? bp.g_tile : 4096;
+  BBX_LAUNCH("tile_wide", k_rows_wide<TRACK>, gw, 64, 0, s, bp.nsets, w.pre + bp.o_tile, w.sets, w.params,
+             w.keys[0], w.keys[1], w.idx[0], w.idx[1], w.leaves, w.leaf_bits, w.tile_defer);
+}
+
 template <int TILE, bool TRACK>
 static void launch_tiles(const BatchPlan& bp, const Ws& w, hipStream_t s) {
   if (bp.g_tile <= kTileOnce) {
@@ -802,7 +1382,9 @@ static void launch_tiles(const BatchPlan& bp, const Ws& w, hipStream_t s) {
 
 hipError_t launch_leaves(const BatchPlan& bp, const Ws& w, hipStream_t s) {
   if (bp.g_tile > 0) {
-    if (bp.tile == 256)
+    if (bp.tile_rows)
+      bp.track ? launch_rows<true>(bp, w, s) : launch_rows<false>(bp, w, s);
+    else if (bp.tile == 256)
       bp.track ? launch_tiles<256, true>(bp, w, s) : launch_tiles<256, false>(bp, w, s);
     else
       bp.track ? launch_tiles<512, true>(bp, w, s) : launch_tiles<512, false>(bp, w, s);

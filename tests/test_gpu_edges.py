@@ -188,3 +188,29 @@ def test_partition_runs(bbx, orc, n, kind, dims, dtype, eb):
     ref = orc.compress(pts, eb, "rel", 32, want_perm=True)
     for blocks, perm in ((0, True), (0, False), (5, False)):
         check_parity(orc, bbx, pts, eb, "rel", 32, level_blocks=blocks, want_perm=perm, ref=ref)
+
+
+# Tiles by rows: whole and ragged ones of four rows and of two, the pass of
+# few tiles and that of many with tiles left to the wide one (spans above 16
+# bits), boxes of spans above 15 bits, leaf sizes for which every tile, some or
+# none qualify, equal codes, both reference rules, source indices.
+@pytest.mark.parametrize("n", [1, 2, 31, 33, 65, 127, 128, 129, 255, 256, 257, 65536, 65536 + 3])
+@pytest.mark.parametrize("r", [16, 17, 24, 31, 32, 33, 48, 63])
+def test_row_tiles_small(bbx, orc, n, r):
+    for kind, dims, dtype, eb, rule in (("cosmology", 3, np.float32, 1e-4, 0), ("ties", 2, np.float32, 1e-2, 1),
+                                        ("uniform", 3, np.float64, 1e-8, r & 1)):
+        pts = gen(kind, n, dims, dtype, seed=n + r)
+        check_parity(orc, bbx, pts, eb, "rel", r, want_perm=bool(n & 1), ref_rule=rule)
+
+
+@pytest.mark.parametrize("n", [2 ** 19 + 5, 2 ** 20, 786431, 1000003])
+@pytest.mark.parametrize("kind,dims,dtype,eb,r,rule", [("cosmology", 3, np.float32, 1e-4, 32, 0),
+                                                       ("ties", 3, np.float32, 1e-3, 32, 1),
+                                                       ("uniform", 2, np.float32, 1e-5, 40, 0),
+                                                       ("uniform", 3, np.float64, 1e-8, 32, 0),
+                                                       ("cosmology", 3, np.float64, 5e-9, 24, 1)])
+def test_row_tiles_many(bbx, orc, n, kind, dims, dtype, eb, r, rule):
+    pts = gen(kind, n, dims, dtype, seed=n % 991)
+    ref = orc.compress(pts, eb, "rel", r, want_perm=True, ref_rule=rule)
+    for perm in (True, False):
+        check_parity(orc, bbx, pts, eb, "rel", r, ref_rule=rule, want_perm=perm, ref=ref)
