@@ -631,6 +631,39 @@ __device__ inline uint32_t lanes_below(uint64_t m) {
   return __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
 }
 
+// find_set and node_span by a whole wavefront for uniform arguments, where
+// their loops are a chain of dependent loads (find_set: eight for 256 sets) or
+// of some fourteen scalar operations a level (node_span of an n that 2^k does
+// not divide: 260 at depth 18, half a tile's scalar work).
+__device__ __forceinline__ uint32_t wave_find_set(const uint64_t* pre, uint32_t nsets, uint64_t b) {
+  uint32_t lo = 0, cnt = nsets;  // the last entry <= b is among cnt entries from lo on
+  while (cnt > 1) {
+    const uint32_t step = (cnt + 63) >> 6, at = (threadIdx.x & 63) * step;
+    const uint64_t m = __builtin_amdgcn_ballot_w64(at < cnt && pre[lo + (at < cnt ? at : 0u)] <= b);
+    const uint32_t i = (uint32_t)__builtin_popcountll(m) - 1;
+    lo += i * step;
+    cnt = cnt - i * step < step ? cnt - i * step : step;
+  }
+  return lo;
+}
+// With R the k bits of j in reverse order (bit l says whether level l + 1 went
+// right), the size after l halvings is (n + R mod 2^l) >> l, as the left child
+// takes the floor: lane l adds the left sibling that a right turn at level
+// l + 1 passes by.
+__device__ __forceinline__ void wave_node_span(uint64_t n, uint32_t k, uint64_t j, uint64_t* start,
+                                               uint64_t* size) {
+  if ((n & ((1ull << k) - 1)) == 0 || n >> 31) {
+    node_span(n, k, j, start, size);
+    return;
+  }
+  const uint32_t n32 = (uint32_t)n, R = __brev((uint32_t)j) >> (32 - k);  // (k > 0: 2^0 divides n)
+  const uint32_t l = threadIdx.x & 63;
+  const bool on = l < k && (R >> (l & 31) & 1u);
+  const uint32_t left = (n32 + (R & ((1u << (l & 31)) - 1u))) >> (l & 31) >> 1;
+  *start = (uint32_t)__builtin_amdgcn_readlane((int)wave_incl(on ? left : 0u), 63);
+  *size = (n32 + R) >> k;
+}
+
 // ---------------------------------------------------------------- launch plumbing
 
 // Kernel timing hook (bbx_profile_*): records HIP events around a launch.

@@ -101,7 +101,7 @@ struct LevelCtx {
 __device__ inline LevelCtx level_ctx(uint32_t nsets, const uint64_t* pre, const SetDesc* sets,
                                      uint32_t depth, uint64_t vb) {
   LevelCtx c;
-  c.s = find_set(pre, nsets, vb);
+  c.s = wave_find_set(pre, nsets, vb);
   c.lb = vb - pre[c.s];
   c.sh = level_shape(sets[c.s].n, depth, sets[c.s].level_blocks);
   return c;
@@ -176,7 +176,7 @@ __device__ void hist_mid_body(uint32_t depth, uint32_t pass, const SetDesc& S, c
   const DigitPlan pl = digit_plan(P->G[d]);
   const uint64_t j = c.lb / c.sh.chunks, ch = c.lb % c.sh.chunks;
   uint64_t st, sz;
-  node_span(n, depth, j, &st, &sz);
+  wave_node_span(n, depth, j, &st, &sz);
   if (sz <= S.r) return;
   const uint32_t w = dp_width(pl, pass), sh = dp_shift(pl, pass), hs = sh + w;
   const uint32_t prefix = sel[j].prefix;
@@ -599,7 +599,7 @@ __device__ void fold_hist_body(uint32_t depth, uint32_t pass, const SetDesc& S, 
   const uint64_t nblk = c.sh.nodes * c.sh.chunks;
   const uint64_t j = c.lb / c.sh.chunks, ch = c.lb % c.sh.chunks;
   uint64_t st, sz;
-  node_span(n, depth, j, &st, &sz);
+  wave_node_span(n, depth, j, &st, &sz);
   if (sz <= S.r) {
     hist_clear(S, t + 1, LAST ? depth + 1 : depth, c.lb, nblk, hist);
     return;
@@ -1218,7 +1218,7 @@ __device__ __forceinline__ void scatter_body(uint32_t depth, const SetDesc& S, D
   const uint32_t d = depth % dims;
   const uint64_t j = c.lb / c.sh.chunks, ch = c.lb % c.sh.chunks;
   uint64_t st, sz64;
-  node_span(n, depth, j, &st, &sz64);
+  wave_node_span(n, depth, j, &st, &sz64);
   const uint64_t beg64 = ch * (uint64_t)c.sh.chunk_elems;
   if (beg64 >= sz64) return;
   // positions inside the node fit 32 bits (n < 2^32)
@@ -1440,7 +1440,7 @@ __global__ void __launch_bounds__(kBlock) k_level_local(uint32_t depth, uint32_t
   const uint32_t* isrc = S.track ? isrc0 + S.idx_off : nullptr;
   uint32_t* idst = S.track ? idst0 + S.idx_off : nullptr;
   uint64_t st, sz;
-  node_span(S.n, depth, c.lb, &st, &sz);
+  wave_node_span(S.n, depth, c.lb, &st, &sz);
   uint32_t v = 0, jeq = 0;
   const uint32_t d = depth % S.dims;
   const uint8_t* keys = src0 + S.key_off;
@@ -1649,7 +1649,7 @@ __device__ void level_wave_body(uint32_t depth, const SetDesc& S, DevParams* P, 
                                 const uint8_t* src, uint8_t* dst, const uint32_t* isrc,
                                 uint32_t* idst, uint32_t* bins) {
   uint64_t st, sz64;
-  node_span(S.n, depth, j, &st, &sz64);
+  wave_node_span(S.n, depth, j, &st, &sz64);
   const uint32_t sz = (uint32_t)sz64;
   const uint32_t dims = S.dims, d = depth % dims;
   const uint64_t kst = S.kst;
@@ -1684,7 +1684,7 @@ __global__ void __launch_bounds__(kBlock) k_level_wave(uint32_t depth, uint32_t 
   const uint32_t wv = threadIdx.x >> 6;
   const uint64_t gn = (uint64_t)blockIdx.x * (kBlock / 64) + wv;
   if (gn >= pre[nsets]) return;  // whole wavefront
-  const uint32_t s = find_set(pre, nsets, gn);
+  const uint32_t s = wave_find_set(pre, nsets, gn);
   const SetDesc& S = sets[s];
   DevParams* P = params + s;
   if (P->status != BBX_OK) return;
@@ -2244,7 +2244,7 @@ __device__ __forceinline__ void level_fused_body(uint32_t depth, const SetDesc& 
                                                  uint64_t j, uint8_t* keys, uint32_t* idx,
                                                  uint32_t* lds, uint32_t* red, uint32_t (*xs)[W][4]) {
   uint64_t st, sz;
-  node_span(S.n, depth, j, &st, &sz);
+  wave_node_span(S.n, depth, j, &st, &sz);
   if (sz > (uint64_t)W * kFuseNode || sz <= S.r) {  // launch plan violated: never expected
     if (threadIdx.x == 0) check_failed(P, kChkFusedIdx);
     return;
@@ -2278,7 +2278,7 @@ __global__ void __launch_bounds__(fused_threads<W>(), 4) k_level_fused(uint32_t 
   const uint32_t wv = (uint32_t)__builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
   const uint64_t gn = W == 1 ? (uint64_t)blockIdx.x * (kBlock / 64) + wv : blockIdx.x;
   if (gn >= pre[nsets]) return;  // whole wavefront (W = 1) or block
-  const uint32_t s = find_set(pre, nsets, gn);
+  const uint32_t s = wave_find_set(pre, nsets, gn);
   const SetDesc& S = sets[s];
   DevParams* P = params + s;
   if (P->status != BBX_OK) return;

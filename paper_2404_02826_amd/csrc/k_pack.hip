@@ -293,7 +293,7 @@ __device__ inline uint64_t ref_coord_bits(const SetDesc& S, uint32_t src, uint32
 // its uniform values in vector registers)
 __device__ __forceinline__ void pack_meta(uint32_t nsets, const uint64_t* pre, uint64_t vb, const SetDesc* sets,
                           const DevParams* params, const LeafRec* leaves0) {
-  const uint32_t s = find_set(pre, nsets, vb);
+  const uint32_t s = wave_find_set(pre, nsets, vb);
   const SetDesc& S = sets[s];
   const DevParams* P = params + s;
   if (P->status != BBX_OK) return;
@@ -640,7 +640,7 @@ __device__ __forceinline__ void pack_payload(uint32_t nsets, const uint64_t* pre
                              const DevParams* params, const LeafRec* leaves0, const uint64_t* off0,
                              const uint8_t* keys0, const uint8_t* keys1, LeafRec* s_rec, uint64_t* s_off,
                              unsigned long long* s_w) {
-  const uint32_t s = find_set(pre, nsets, vb);
+  const uint32_t s = wave_find_set(pre, nsets, vb);
   const SetDesc& S = sets[s];
   const DevParams* P = params + s;
   if (P->status != BBX_OK) return;

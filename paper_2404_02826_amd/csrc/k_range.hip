@@ -134,7 +134,7 @@ __global__ void __launch_bounds__(kBlock) k_minmax(uint32_t nsets, const uint64_
                                                    const SetDesc* sets, double* partials,
                                                    uint32_t* pass_need, uint32_t* lossless,
                                                    uint32_t* tile_defer) {
-  const uint32_t s = find_set(pre, nsets, blockIdx.x);
+  const uint32_t s = wave_find_set(pre, nsets, blockIdx.x);
   minmax_set(sets[s], blockIdx.x - pre[s], partials);
   minmax_clear(pass_need, lossless, tile_defer);
 }
@@ -366,7 +366,7 @@ __global__ void __launch_bounds__(kBlock) k_quantize(uint32_t nsets, const uint6
                                                      const SetDesc* sets, const DevParams* params,
                                                      uint8_t* keys0, uint32_t* idx0,
                                                      uint32_t* hist0) {
-  const uint32_t s = find_set(pre, nsets, blockIdx.x);
+  const uint32_t s = wave_find_set(pre, nsets, blockIdx.x);
   const SetDesc& S = sets[s];
   const DevParams* P = params + s;
   if (P->status != BBX_OK) return;

@@ -269,7 +269,7 @@ __device__ void tile_body(WaveTile<TILE, KL, TRACK>& sm, uint64_t j, uint32_t K0
   constexpr int E = TILE / 64;
   const uint32_t lane = threadIdx.x & 63;
   uint64_t tst, s0_64;
-  node_span(n, K0, j, &tst, &s0_64);
+  wave_node_span(n, K0, j, &tst, &s0_64);
   if (s0_64 > (uint64_t)TILE) {  // launch plan violated: never expected
     if (lane == 0) check_failed(P, kChkTileRange);
     return;
@@ -617,7 +617,7 @@ __device__ void tile_node(uint32_t nsets, const uint64_t* pre, const SetDesc* se
                           DevParams* params, uint8_t* keys0, uint8_t* keys1, uint32_t* idx0,
                           uint32_t* idx1, LeafRec* leaves0, uint64_t* leaf_bits0, uint32_t* defer,
                           uint32_t gtile, WaveTile<TILE, KL, TRACK>& sm) {
-  const uint32_t s = find_set(pre, nsets, gtile);
+  const uint32_t s = wave_find_set(pre, nsets, gtile);
   const SetDesc& S = sets[s];
   DevParams* P = params + s;
   if (P->status != BBX_OK) return;
@@ -1272,7 +1272,7 @@ __device__ __forceinline__ void rows_node(uint32_t nsets, const uint64_t* pre, c
                                           DevParams* params, uint8_t* keys0, uint8_t* keys1, uint32_t* idx0,
                                           uint32_t* idx1, LeafRec* leaves0, uint64_t* leaf_bits0, uint32_t* defer,
                                           uint32_t gtile, RowTile<WIDE, TRACK>& sm) {
-  const uint32_t s = find_set(pre, nsets, gtile);
+  const uint32_t s = wave_find_set(pre, nsets, gtile);
   const SetDesc& S = sets[s];
   DevParams* P = params + s;
   if (P->status != BBX_OK) return;
@@ -1290,7 +1290,7 @@ __device__ __forceinline__ void rows_node(uint32_t nsets, const uint64_t* pre, c
                      leaves0 + S.leaf_off,
                      leaf_bits0 + S.leaf_off};
   uint64_t tst, s64;
-  node_span(S.n, S.gl, j, &tst, &s64);
+  wave_node_span(S.n, S.gl, j, &tst, &s64);
   if (s64 > 256) {  // launch plan violated: never expected
     if ((threadIdx.x & 63) == 0) check_failed(P, kChkTileRange);
     return;
