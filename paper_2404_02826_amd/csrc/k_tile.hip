@@ -807,9 +807,14 @@ __global__ void __launch_bounds__(kBlock) k_bigleaf(uint32_t nsets, const uint64
 // 128 642 and 326, 13.1 million in two axes 178 and 107, 256 sets 742 and 438;
 // vector and scalar issue are each about 70 % busy.  A capped grid whose
 // wavefronts loop over tiles: 108 registers for 43, 975 us at 2^27.
+// x, y: axes 0 and 1 of the level order, axis 2 and its complement or (TRACK)
+// the member's position; wide: an axis each, the position (vectors: arrays of
+// structs went through scratch memory, 21 us a launch for 6)
+typedef uint32_t RowM2 __attribute__((ext_vector_type(2)));
+typedef uint32_t RowM4 __attribute__((ext_vector_type(4)));
 template <bool WIDE, bool TRACK>
 struct RowTile {
-  typename std::conditional<WIDE, uint4, uint2>::type m[256];
+  typename std::conditional<WIDE, RowM4, RowM2>::type m[256];
   uint32_t I[TRACK ? 256 : 1];  // source indices by position in the tile
 };
 
@@ -1006,7 +1011,7 @@ __device__ __forceinline__ bool rows_body(RowTile<WIDE, TRACK>& sm, uint32_t s_r
 
   // ---- minima and spans per axis (of an empty lane: the identities)
   uint32_t m0, m1, m2, G0, G1, G2;
-  if constexpr (sizeof(KT) == 2 && !WIDE) {
+  if constexpr (sizeof(KT) == 2) {
     uint32_t lo = 0xffffffffu, hi = 0, lh = 0xffffffffu;  // axes 0 and 1; axis 2 and its complement
     if (WHOLE || mine) {
 #pragma unroll
@@ -1298,20 +1303,16 @@ __device__ __forceinline__ void rows_node(uint32_t nsets, const uint64_t* pre, c
   const uint32_t s0 = (uint32_t)s64;
   const uint64_t first = leaves_before_node(S.geom, S.gl, j, tst);
   bool ok;
-  if (P->key16) {
+  if (P->key16) {  // spans within 16 bits
     uint16_t* K = (uint16_t*)keys;
-    if constexpr (!WIDE) {
-      if (s0 == 256)
-        ok = rows_body<4, true, WIDE, uint16_t, TRACK>(sm, s0, tst, first, rs, P, K);
-      else if (s0 == 128)
-        ok = rows_body<2, true, WIDE, uint16_t, TRACK>(sm, s0, tst, first, rs, P, K);
-      else
-        ok = s0 > 128 ? rows_body<4, false, WIDE, uint16_t, TRACK>(sm, s0, tst, first, rs, P, K)
-                      : rows_body<2, false, WIDE, uint16_t, TRACK>(sm, s0, tst, first, rs, P, K);
-    } else {
-      ok = s0 > 128 ? rows_body<4, false, WIDE, uint16_t, TRACK>(sm, s0, tst, first, rs, P, K)
-                    : rows_body<2, false, WIDE, uint16_t, TRACK>(sm, s0, tst, first, rs, P, K);
-    }
+    RowTile<false, TRACK>& nm = (RowTile<false, TRACK>&)sm;
+    if (s0 == 256)
+      ok = rows_body<4, true, false, uint16_t, TRACK>(nm, s0, tst, first, rs, P, K);
+    else if (s0 == 128)
+      ok = rows_body<2, true, false, uint16_t, TRACK>(nm, s0, tst, first, rs, P, K);
+    else
+      ok = s0 > 128 ? rows_body<4, false, false, uint16_t, TRACK>(nm, s0, tst, first, rs, P, K)
+                    : rows_body<2, false, false, uint16_t, TRACK>(nm, s0, tst, first, rs, P, K);
   } else {
     uint32_t* K = (uint32_t*)keys;
     ok = s0 > 128 ? rows_body<4, false, WIDE, uint32_t, TRACK>(sm, s0, tst, first, rs, P, K)
