@@ -582,7 +582,7 @@ def main():
                          "1 widest axis, 2 ceil(n/r) proportional leaves, 3 midpoint cells "
                          "(ablations, version-2 streams)")
     ap.add_argument("--scatter-stage", type=int, default=0, choices=(0, 1, 2),
-                    help="global partition group stores: 0 by chunk size, 1 staged, 2 direct")
+                    help="global partition groups: 0 runs of codes, 1 staged rows, 2 direct rows")
     ap.add_argument("--nsets", type=int, default=4096)
     ap.add_argument("--requests", type=int, default=2000, help="served workload: requests")
     ap.add_argument("--qps", type=float, default=400.0, help="served workload: arrival rate")
