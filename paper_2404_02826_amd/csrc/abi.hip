@@ -437,7 +437,7 @@ static void plan_batch(const SetIn* in, uint32_t nsets, BatchPlan* bp, std::vect
       key_bytes += align_up((uint64_t)D.dims * D.kst * 4);
       if (I.need_idx || D.track) idx_n += (n + 63) & ~63ull;
       if (D.reduce && !(I.need_idx || D.track)) idx_n += (n + 63) & ~63ull;
-      hist_n += 3 * bin_nodes * kHistBins;
+      hist_n += (bp->fold ? 3 : 2) * bin_nodes * kHistBins;
       sel_n += 2 * max_nodes;
       rows_n += (bp->fold ? 1 : 2) * max_blocks;
       cb_n += 2 * D.cb_half;
