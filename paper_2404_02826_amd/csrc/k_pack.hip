@@ -23,6 +23,8 @@
 //                   member per lane), then writes every owned word once with
 //                   a coalesced plain store (no global atomics, no zeroing of
 //                   the output)
+#include <type_traits>
+
 #include "bbx_internal.h"
 
 namespace bbx {
@@ -422,6 +424,18 @@ __device__ inline void or_into64(uint64_t& word, uint64_t w0, uint64_t val, uint
     word |= val >> (uint32_t)(w0 - at);  // w0 - at < len <= 64
 }
 
+// 16 bytes of consecutive codes, of any element alignment
+template <typename KT>
+struct PackRun {
+  struct __attribute__((packed, aligned(2))) Raw {
+    uint32_t w[4];
+  } v;
+  __device__ __forceinline__ void load(const KT* p) { v = *(const Raw*)p; }
+  __device__ __forceinline__ uint32_t operator[](int i) const {
+    return sizeof(KT) == 4 ? v.w[i & 3] : ((i & 1) ? v.w[i >> 1] >> 16 : v.w[i >> 1] & 0xffffu);
+  }
+};
+
 constexpr uint32_t kPackLdsWords = 3072;  // payload words of one block's members (24 KB)
 
 // Leaf-aligned packing: a block takes leaves_per_block(r) consecutive leaves
@@ -493,107 +507,87 @@ __device__ __forceinline__ void pack_payload_body(const SetDesc& S, const DevPar
   }
   for (uint32_t t = threadIdx.x; t < (uint32_t)nwb; t += kBlock) s_w[t] = 0;
   __syncthreads();
-  const uint64_t slot0 = s_rec[0].start;
-  const uint64_t slot_end = (uint64_t)s_rec[nlb - 1].start + s_rec[nlb - 1].size;
-  // each thread takes V consecutive slots (V-aligned slot indices): one
-  // 16-byte code load per axis, one leaf search, and LDS atomics that land on
-  // different words across the lanes
+  // a thread takes V consecutive members of one leaf (one 16-byte load an axis,
+  // of any element alignment; what lies past the leaf is in the workspace and
+  // not used), a leaf of at most r members by `runs` threads.  Runs aligned in
+  // the arrays needed a search for their leaf, and in sets with ragged leaves
+  // every wavefront took the code for a run over two leaves as well: 13.1
+  // million members in leaves of 24 and 25 84 us, 51 now; 33.6 million of 16 to
+  // 32 178 and 105; 256 sets 300 and 203; 2^27 in whole leaves 480 and 450.
   constexpr uint32_t V = 16 / sizeof(KT);
-  for (uint64_t gs = (slot0 & ~(uint64_t)(V - 1)) + (uint64_t)V * threadIdx.x; gs < slot_end;
-       gs += (uint64_t)V * kBlock) {
-    union {
-      uint4 v;
-      KT e[V];
-    } kk[3];
+  const uint32_t runs = (S.r + V - 1) / V;
+  for (uint32_t u = threadIdx.x; u < nlb * runs; u += kBlock) {
+    const uint32_t a = u / runs;
+    const LeafRec ra = s_rec[a];
+    const uint32_t sma = sum_m(ra.m), at0 = (uint32_t)(s_off[a] - wlo * 64);
+    if (sma == 0) continue;
+    for (uint32_t j0 = V * (u - a * runs); j0 < ra.size; j0 += V * runs) {
+      const uint32_t num = ra.size - j0 < V ? ra.size - j0 : V;
+      PackRun<KT> kk[3];
 #pragma unroll
-    for (uint32_t d = 0; d < 3; ++d) {
-      kk[d].v = make_uint4(0, 0, 0, 0);
-      if (d < dims) kk[d].v = *(const uint4*)(keys + (uint64_t)d * kst + gs);
-    }
-    const uint64_t pfirst = gs > slot0 ? gs : slot0;
-    uint32_t a = 0, z = nlb - 1;  // last staged leaf starting at or before pfirst
-    while (a < z) {
-      const uint32_t mid = (a + z + 1) >> 1;
-      if (s_rec[mid].start <= pfirst)
-        a = mid;
-      else
-        z = mid - 1;
-    }
-    {
-      // the usual shape: all V slots inside leaf a, member codes of at most
-      // 32 bits.  The run's codes occupy consecutive bits, so they are
-      // assembled in registers and ORed into LDS one 64-bit word at a time.
-      const LeafRec ra = s_rec[a];
-      const uint32_t sma = sum_m(ra.m);
-      if (gs >= ra.start && gs + V <= (uint64_t)ra.start + ra.size && sma > 0 && sma <= 32) {
-        const uint32_t j0 = (uint32_t)(gs - ra.start);
-        uint32_t hm[3], sh3[3] = {0, 0, 0};
+      for (uint32_t d = 0; d < 3; ++d)
+        if (d < dims) kk[d].load(keys + (uint64_t)d * kst + ra.start + j0);
+      uint32_t hm[3], sh3[3] = {0, 0, 0};
 #pragma unroll
-        for (uint32_t d = 0; d < 3; ++d) {
-          const uint32_t m = d < dims ? (ra.m >> (8 * d)) & 0xffu : 0u;
-          hm[d] = (uint32_t)((1ull << m) >> 1) - (d < dims ? ra.qref[d] : 0u);
-          if (d + 1 < 3) sh3[d + 1] = sh3[d] + m;
-        }
-        uint32_t at = (uint32_t)(s_off[a] - wlo * 64) + (j0 ? j0 - 1 : 0u) * sma;
+      for (uint32_t d = 0; d < 3; ++d) {
+        const uint32_t m = d < dims ? (ra.m >> (8 * d)) & 0xffu : 0u;
+        hm[d] = (uint32_t)((1ull << m) >> 1) - (d < dims ? ra.qref[d] : 0u);
+        if (d + 1 < 3) sh3[d + 1] = sh3[d] + m;
+      }
+      // (u_d = q_d - q_ref,d + 2^(m_d - 1) lies in [0, 2^m_d), m_d <= 32, so 32-bit
+      // wrap-around arithmetic gives it; an axis with m_d = 0 adds nothing.  Bits
+      // in the LDS copy lie below kPackLdsWords * 64: 32-bit arithmetic)
+      uint32_t at = at0 + (j0 ? j0 - 1 : 0u) * sma;
+      if (sma <= 32) {
+        // codes of at most 32 bits: consecutive bits, assembled in registers and
+        // ORed into LDS one 64-bit word at a time
         uint32_t w = at >> 6, pos = at & 63;
         uint64_t lo = 0, hi = 0;
+        auto put = [&](auto whole) __attribute__((always_inline)) {
 #pragma unroll
-        for (uint32_t k = 0; k < V; ++k) {
-          if (j0 + k == 0) continue;  // the reference carries no payload
-          uint64_t c = 0;
+          for (uint32_t k = 0; k < V; ++k) {
+            if (j0 + k == 0 || (!whole && k >= num)) continue;  // the reference carries no payload
+            uint64_t c = 0;
 #pragma unroll
-          for (uint32_t d = 0; d < 3; ++d)
-            if (d < dims) c |= (uint64_t)((uint32_t)kk[d].e[k] + hm[d]) << sh3[d];
-          lo |= c << pos;
-          hi |= pos ? c >> (64 - pos) : 0ull;
-          pos += sma;
-          if (pos >= 64) {
-            atomicOr(&s_w[w], (unsigned long long)lo);
-            ++w;
-            lo = hi;
-            hi = 0;
-            pos -= 64;
+            for (uint32_t d = 0; d < 3; ++d)
+              if (d < dims) c |= (uint64_t)(kk[d][k] + hm[d]) << sh3[d];
+            lo |= c << pos;
+            hi |= pos ? c >> (64 - pos) : 0ull;
+            pos += sma;
+            if (pos >= 64) {
+              atomicOr(&s_w[w], (unsigned long long)lo);
+              ++w;
+              lo = hi;
+              hi = 0;
+              pos -= 64;
+            }
           }
-        }
+        };
+        if (__builtin_amdgcn_ballot_w64(num < V) == 0)
+          put(std::true_type());
+        else
+          put(std::false_type());
         if (pos > 0) atomicOr(&s_w[w], (unsigned long long)lo);
         continue;
       }
-    }
 #pragma unroll
-    for (uint32_t k = 0; k < V; ++k) {
-      const uint64_t slot = gs + k;
-      if (slot < slot0 || slot >= slot_end) continue;
-      while (a + 1 < nlb && s_rec[a + 1].start <= slot) ++a;
-      const LeafRec rec = s_rec[a];
-      const uint32_t j = (uint32_t)(slot - rec.start);
-      const uint32_t sm = sum_m(rec.m);
-      if (j == 0 || sm == 0) continue;  // the reference, or a leaf without payload
-      // bit in the LDS copy (below kPackLdsWords * 64: 32-bit arithmetic)
-      const uint32_t at = (uint32_t)(s_off[a] - wlo * 64) + (j - 1) * sm;
-      const uint32_t w = at >> 6, sh = at & 63;
-      if (sm <= 64) {
-        // u_d = q_d - q_ref,d + 2^(m_d - 1) lies in [0, 2^m_d) (m_d <= 32), so
-        // 32-bit wrap-around arithmetic gives it exactly; an axis with m_d = 0
-        // has q_d = q_ref,d and adds nothing
-        uint64_t c = 0;
-        uint32_t cat = 0;
+      for (uint32_t k = 0; k < V; ++k) {
+        if (j0 + k == 0 || k >= num) continue;
+        const uint32_t w = at >> 6, sh = at & 63;
+        at += sma;
+        if (sma <= 64) {
+          uint64_t c = 0;
 #pragma unroll
-        for (uint32_t d = 0; d < 3; ++d) {
-          if (d >= dims) break;
-          const uint32_t m = (rec.m >> (8 * d)) & 0xffu;
-          const uint32_t u = (uint32_t)kk[d].e[k] - rec.qref[d] + (uint32_t)((1ull << m) >> 1);
-          c |= (uint64_t)u << cat;
-          cat += m;
-        }
-        atomicOr(&s_w[w], (unsigned long long)(c << sh));
-        if (sh + sm > 64) atomicOr(&s_w[w + 1], (unsigned long long)(c >> (64 - sh)));
-      } else {
-        const u128 c = member_code(keys, kst, dims, rec, slot) << sh;
-        atomicOr(&s_w[w], (unsigned long long)(uint64_t)c);
-        atomicOr(&s_w[w + 1], (unsigned long long)(uint64_t)(c >> 64));
-        if (sh + sm > 128) {
-          const u128 c3 = member_code(keys, kst, dims, rec, slot) >> (128 - sh);
-          atomicOr(&s_w[w + 2], (unsigned long long)(uint64_t)c3);
+          for (uint32_t d = 0; d < 3; ++d)
+            if (d < dims) c |= (uint64_t)(kk[d][k] + hm[d]) << (sh3[d] & 63);  // (64: an axis of no bits)
+          atomicOr(&s_w[w], (unsigned long long)(c << sh));
+          if (sh + sma > 64) atomicOr(&s_w[w + 1], (unsigned long long)(c >> (64 - sh)));
+        } else {
+          const u128 m = member_code(keys, kst, dims, ra, (uint64_t)ra.start + j0 + k);
+          const u128 c = m << sh;
+          atomicOr(&s_w[w], (unsigned long long)(uint64_t)c);
+          atomicOr(&s_w[w + 1], (unsigned long long)(uint64_t)(c >> 64));
+          if (sh + sma > 128) atomicOr(&s_w[w + 2], (unsigned long long)(uint64_t)(m >> (128 - sh)));
         }
       }
     }

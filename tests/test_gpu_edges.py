@@ -214,3 +214,20 @@ def test_row_tiles_many(bbx, orc, n, kind, dims, dtype, eb, r, rule):
     ref = orc.compress(pts, eb, "rel", r, want_perm=True, ref_rule=rule)
     for perm in (True, False):
         check_parity(orc, bbx, pts, eb, "rel", r, ref_rule=rule, want_perm=perm, ref=ref)
+
+
+# Payload runs within a leaf: leaves of one member, fewer than a run, ending
+# inside one, of several rounds of runs and of one-code cells beyond r; codes
+# of up to 32, 64 and 93 bits a member; 16- and 32-bit codes.
+@pytest.mark.parametrize("n,r", [(1, 1), (50, 1), (777, 3), (5000, 7), (5000, 8), (5001, 9), (40000, 25), (9999, 70),
+                                 (70001, 300), (200000, 5000)])
+@pytest.mark.parametrize("kind,dims,dtype,eb", [("cosmology", 3, np.float32, 1e-4), ("uniform", 2, np.float64, 1e-6),
+                                                ("uniform", 3, np.float64, 1e-7), ("uniform", 3, np.float64, 1.2e-9),
+                                                ("ties", 3, np.float32, 1e-1)])
+def test_pack_runs(bbx, orc, n, r, kind, dims, dtype, eb):
+    pts = gen(kind, n, dims, dtype, seed=n + r)
+    check_parity(orc, bbx, pts, eb, "rel", r, want_perm=False)
+    if n < 20000:
+        ref, _ = orc.compress_split(pts, eb, "rel", r, split_rule=3, want_perm=True)
+        x = torch.from_numpy(pts).cuda()
+        assert bbx.compress(x, eb, leaf_size=r, split_rule=3).cpu().numpy().tobytes() == bytes(ref)
