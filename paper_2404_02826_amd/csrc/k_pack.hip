@@ -439,8 +439,8 @@ struct PackRun {
 constexpr uint32_t kPackLdsWords = 3072;  // payload words of one block's members (24 KB)
 
 // Leaf-aligned packing: a block takes leaves_per_block(r) consecutive leaves
-// and stages their records and bit offsets.  Every member (thread per slot,
-// coalesced code loads) ORs its code into an LDS copy of the payload words its
+// and stages their records and bit offsets.  Every thread ORs the codes
+// of a run of a leaf's members into an LDS copy of the payload words the
 // leaves' bits touch (LDS atomics), and the block stores the words whose first
 // bit lies in its leaves' bit range with coalesced plain stores.  The last such
 // word can also hold the first bits of the next block's leaves: one thread
