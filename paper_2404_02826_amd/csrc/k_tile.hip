@@ -804,8 +804,9 @@ __global__ void __launch_bounds__(kBlock) k_bigleaf(uint32_t nsets, const uint64
 // straight from registers, R consecutive members per store.
 // 570 vector and 580 scalar instructions a whole tile.  2^27 members in whole
 // tiles 1,246 us (k_tile) and 652, 2^24 195 and 88, 33.6 million in tiles of
-// 128 642 and 326, 13.1 million in two axes 178 and 107, 256 sets 742 and 438;
-// vector and scalar issue are each about 70 % busy.  A capped grid whose
+// 128 642 and 209, 13.1 million in two axes 178 and 91, 256 sets 742 and 378
+// (the ragged ones 326, 107 and 438 before wave_node_span and wave_find_set);
+// vector and scalar issue are each about 80 % busy.  A capped grid whose
 // wavefronts loop over tiles: 108 registers for 43, 975 us at 2^27.
 // x, y: axes 0 and 1 of the level order, axis 2 and its complement or (TRACK)
 // the member's position; wide: an axis each, the position (vectors: arrays of
@@ -1334,7 +1335,8 @@ __global__ void __launch_bounds__(kBlock) k_rows(uint32_t ntiles, uint32_t nsets
                             sm[wv]);
 }
 
-// second pass and only pass of grids of few tiles, as k_tile_wide
+// second pass and only pass of grids of few tiles, as k_tile_wide (65,536
+// members: 6.1 us, against 5.8 and a second launch)
 template <bool TRACK>
 __global__ void __launch_bounds__(64) k_rows_wide(uint32_t nsets, const uint64_t* pre, const SetDesc* sets,
                                                   DevParams* params, uint8_t* keys0, uint8_t* keys1,
