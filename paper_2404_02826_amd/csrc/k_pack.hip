@@ -514,8 +514,10 @@ __device__ __forceinline__ void pack_payload_body(const SetDesc& S, const DevPar
   // every wavefront took the code for a run over two leaves as well: 13.1
   // million members in leaves of 24 and 25 84 us, 51 now; 33.6 million of 16 to
   // 32 178 and 105; 256 sets 300 and 203; 2^27 in whole leaves 480 and 450.
+  // (runs: of the leaf itself when the block has one, as r may be any 32-bit
+  // number, far above the set; r is at most 1,024 where a block has more)
   constexpr uint32_t V = 16 / sizeof(KT);
-  const uint32_t runs = (S.r + V - 1) / V;
+  const uint32_t runs = ((nlb == 1 ? s_rec[0].size : S.r) + V - 1) / V;
   for (uint32_t u = threadIdx.x; u < nlb * runs; u += kBlock) {
     const uint32_t a = u / runs;
     const LeafRec ra = s_rec[a];

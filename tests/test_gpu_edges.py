@@ -231,3 +231,12 @@ def test_pack_runs(bbx, orc, n, r, kind, dims, dtype, eb):
         ref, _ = orc.compress_split(pts, eb, "rel", r, split_rule=3, want_perm=True)
         x = torch.from_numpy(pts).cuda()
         assert bbx.compress(x, eb, leaf_size=r, split_rule=3).cpu().numpy().tobytes() == bytes(ref)
+
+
+# Leaf sizes far above the set, up to the largest number a caller can give
+# ("one leaf"): the set's one leaf is packed whatever the leaf size.
+@pytest.mark.parametrize("r", [1 << 30, 0xfffffff9, 0xfffffffd, 0xffffffff])
+@pytest.mark.parametrize("n", [1, 1000, 3001])
+@pytest.mark.parametrize("dtype,eb", [(np.float32, 1e-3), (np.float64, 1e-7)])
+def test_pack_one_leaf(bbx, orc, n, r, dtype, eb):
+    check_parity(orc, bbx, gen("uniform", n, 3, dtype, seed=n), eb, "rel", r)
