@@ -1167,6 +1167,7 @@ bbx_status bbx_decompress(const void* d_stream, size_t stream_size, const void* 
     e = hipMemcpyAsync(&hp, w.params, sizeof(hp), hipMemcpyDeviceToHost, stream);
     if (e == hipSuccess) e = hipStreamSynchronize(stream);
     if (e != hipSuccess) return fail(BBX_EHIP, std::string("synchronize failed: ") + hipGetErrorString(e));
+    if (hp.damage) hp.status = BBX_ECORRUPT;
     if (hp.status != BBX_OK) return fail((bbx_status)hp.status, "stream payload fails validation");
   }
   return BBX_OK;

@@ -47,7 +47,7 @@ struct DevParams {
   uint64_t payload_base;  // global payload-bit offset of the set's first leaf
   uint64_t nseq;          // sequences of the version-2 stream (reduce or split-rule sets)
   uint64_t nleaves;       // leaves the partition made (split-rule sets; found on the device)
-  uint64_t pad1[1];
+  uint64_t damage;        // decoding: k_unpack found a code that no stream has (it does not read this word)
 };
 
 // Shape of the k-d tree, which depends on (n, r) only: at depth k every node

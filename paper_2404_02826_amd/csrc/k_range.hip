@@ -213,7 +213,7 @@ __global__ void __launch_bounds__(kBlock) k_epilogue(const SetDesc* sets, const 
   p.meta_bits = p.payload_bits = p.total_bytes = p.payload_base = 0;
   p.nseq = 0;
   p.nleaves = 0;
-  p.pad1[0] = 0;
+  p.damage = 0;
   if (n == 0) {
     p.eb_abs = S.eb_mode == BBX_EB_ABS ? eb : 0.0;
     *P = p;

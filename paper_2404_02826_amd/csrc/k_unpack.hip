@@ -223,6 +223,7 @@ __global__ void __launch_bounds__(1024) k_dec_top(uint64_t blocks, uint64_t* par
   }
   if (threadIdx.x == 0) {
     P->status = bad || total != expect ? BBX_ECORRUPT : BBX_OK;
+    P->damage = 0;
     P->payload_bits = total;
   }
 }
@@ -461,7 +462,11 @@ __device__ __forceinline__ void unpack_body(const MetaView& V, uint64_t n, uint3
       for (uint32_t i = 0; i < 4 * DIMS * sizeof(T) / 16; ++i) dst[i] = o.v[i];
     }
   }
-  if (corrupt) P->status = BBX_ECORRUPT;
+  // not P->status: every wavefront reads that when it starts, and one that
+  // left alone would leave its leaves' spans unwritten, by which the others
+  // of its block store (a barrier in front of that read takes the
+  // 2^27-particle decode from 637 us to 663)
+  if (corrupt) P->damage = 1;
   // ref_mode 1: each leaf's first slot (its reference, where its code's bin
   // centre was written) receives the stored original coordinates, bit for bit
   if (V.ref_mode) {
@@ -481,7 +486,7 @@ template <typename T>
 __global__ void __launch_bounds__(kBlock) k_unpack(MetaView V, uint64_t n, uint32_t layout, const uint64_t* part,
                                                    const uint8_t* stream, uint64_t pay_bits, T* out,
                                                    DevParams* P) {
-  if (P->status != BBX_OK) return;
+  if (P->status != BBX_OK) return;  // (set by earlier kernels only)
   __shared__ UnpackStage sm;
   const uint64_t* meta = (const uint64_t*)(stream + kHeaderBytes);
   const uint64_t* pay = meta + (V.meta_bits + 63) / 64;
@@ -499,12 +504,13 @@ __global__ void k_dec_init(DevParams* P, const uint8_t* stream, HeaderCopy h) {
   const uint64_t any = __ballot(diff);
   if (lane == 0) {
     P->status = any ? BBX_ECORRUPT : BBX_OK;
+    P->damage = 0;
     P->payload_bits = 0;
   }
 }
 
 __global__ void k_dec_finish(const DevParams* P, uint32_t* d_status) {
-  if (threadIdx.x == 0 && d_status) *d_status = P->status;
+  if (threadIdx.x == 0 && d_status) *d_status = P->damage ? (uint32_t)BBX_ECORRUPT : P->status;
 }
 
 // A lossless stream: the stored bits of every coordinate, in input order.

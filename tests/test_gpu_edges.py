@@ -5,6 +5,7 @@ from __future__ import annotations
 import numpy as np
 import pytest
 
+import props
 from oracle import Oracle
 from test_gpu_parity import check_parity, gen
 
@@ -240,3 +241,31 @@ def test_pack_runs(bbx, orc, n, r, kind, dims, dtype, eb):
 @pytest.mark.parametrize("dtype,eb", [(np.float32, 1e-3), (np.float64, 1e-7)])
 def test_pack_one_leaf(bbx, orc, n, r, dtype, eb):
     check_parity(orc, bbx, gen("uniform", n, 3, dtype, seed=n), eb, "rel", r)
+
+
+# Damaged streams of some hundred decode blocks, where blocks start while
+# others report damage: refused, nothing written outside the output, and the
+# same decoder reads the undamaged stream afterwards.
+@pytest.mark.parametrize("layout", ["aos", "soa"])
+@pytest.mark.parametrize("ref_mode", [0, 1])
+def test_decode_damaged_blocks(bbx, orc, ref_mode, layout):
+    n, guard = 2048 * 300 + 77, 1 << 16
+    x = torch.from_numpy(gen("uniform", n, 3, np.float32, seed=4)).cuda()
+    good = bbx.compress(x, 1e-3, ref_mode=ref_mode)
+    h = props.parse_header(good[:128].cpu().numpy().tobytes())
+    codes = 128 + (h["meta_bits"] + 63) // 64 * 8  # the payload's first byte
+    want = bbx.decompress(good, layout).clone()
+    dec = bbx.Decompressor(good[:128].cpu().numpy().tobytes(), layout)
+    buf = torch.full((3 * n + 2 * guard,), 7.5, device="cuda")
+    dec.pos = buf[guard: guard + 3 * n].view(dec.pos.shape)
+    rng = np.random.default_rng(ref_mode)
+    for trial in range(12):
+        bad = good.clone()
+        for at in rng.integers(codes, len(good) - 32, 1 + 3 * trial):  # codes of 0
+            bad[int(at): int(at) + 24] = 0
+        with pytest.raises(bbx.BitboxError, match="ECORRUPT"):
+            dec(bad)
+        dec.launch(bad)
+        assert int(dec.d_status) == 3  # ECORRUPT
+        assert bool((buf[:guard] == 7.5).all()) and bool((buf[guard + 3 * n:] == 7.5).all()), trial
+    assert torch.equal(dec(good), want)
