@@ -2,8 +2,9 @@
 // centre origin + q*w, FP64 multiply then add, then rounding to the type).
 //
 //   k_dec_sums   payload bits of each unpack block: a thread per leaf reads
-//                and checks its record's widths; its span follows from (n, r)
-//                alone (the tree's leaf sizes depend on n and r only)
+//                and checks its record (widths, with ref_mode 1 the reference's
+//                coordinates); its span follows from (n, r) alone (the tree's
+//                leaf sizes depend on n and r only)
 //   k_dec_top    (up to kDecTop blocks, else k_dec_init and the scan kernels)
 //                their exclusive scan, total checked against the header
 //   k_unpack     a block takes leaves_per_block(r) leaves: their records, a
@@ -151,7 +152,8 @@ __device__ inline bool record_widths(const MetaView& v, u128 bits, uint32_t* m, 
 }
 
 // Payload bits of each unpack block (leaves_per_block leaves), a thread per
-// leaf.  A record with a bad width makes the stream corrupt: reported in P,
+// leaf.  A record with a bad width or a reference coordinate outside the grid
+// makes the stream corrupt before anything is decoded: reported in P,
 // or (P null) as a total of all ones for k_dec_top.
 __global__ void __launch_bounds__(kBlock) k_dec_sums(MetaView v, const uint8_t* stream, uint64_t blocks,
                                                      uint64_t* part, DevParams* P) {
@@ -167,7 +169,17 @@ __global__ void __launch_bounds__(kBlock) k_dec_sums(MetaView v, const uint8_t* 
     const uint64_t* meta = (const uint64_t*)(stream + kHeaderBytes);
     const u128 bits = read_bits(meta, (v.meta_bits + 63) / 64, i * record_bits(v), v.dims * v.mbits);
     uint32_t m, summ;
-    if (!record_widths(v, bits, &m, &summ)) {
+    bool ok = record_widths(v, bits, &m, &summ);
+    if (v.ref_mode) {
+#pragma unroll
+      for (uint32_t d = 0; d < 3; ++d) {
+        if (d >= v.dims) break;
+        const uint64_t at = i * record_bits(v) + v.dims * v.mbits + d * coord_bits(v.dtype);
+        uint32_t q;
+        ok &= ref_code_from_coord(meta, (v.meta_bits + 63) / 64, at, v.dtype, v.origin[d], v.inv_w, v.G[d], &q);
+      }
+    }
+    if (!ok) {
       bad[x] = 1;
     } else {
       uint64_t st, sz;
@@ -279,14 +291,14 @@ __device__ __forceinline__ void unpack_body(const MetaView& V, uint64_t n, uint3
       const uint64_t i = L0 + t;
       u128 v = read_bits(meta, mwords, i * rb, V.ref_mode ? dims * V.mbits : rb);
       uint32_t m, summ;
-      if (!record_widths(V, v, &m, &summ)) corrupt = true, m = summ = 0;  // (found before: not reached)
+      if (!record_widths(V, v, &m, &summ)) m = summ = 0;  // (found before: not reached)
       v >>= dims * V.mbits;
 #pragma unroll
       for (uint32_t d = 0; d < DIMS; ++d) {
         uint32_t q = 0;
         if (V.ref_mode) {
           const uint64_t at = i * rb + dims * V.mbits + d * coord_bits(V.dtype);
-          if (!ref_code_from_coord(meta, mwords, at, V.dtype, V.origin[d], V.inv_w, V.G[d], &q)) corrupt = true;
+          (void)ref_code_from_coord(meta, mwords, at, V.dtype, V.origin[d], V.inv_w, V.G[d], &q);
         } else {
           q = (uint32_t)v & ((1u << V.G[d]) - 1);
           v >>= V.G[d];

@@ -6,7 +6,7 @@ import numpy as np
 import pytest
 
 import props
-from oracle import Oracle
+from oracle import Oracle, OracleError
 from test_gpu_parity import check_parity, gen
 
 torch = pytest.importorskip("torch")
@@ -269,3 +269,34 @@ def test_decode_damaged_blocks(bbx, orc, ref_mode, layout):
         assert int(dec.d_status) == 3  # ECORRUPT
         assert bool((buf[:guard] == 7.5).all()) and bool((buf[guard + 3 * n:] == 7.5).all()), trial
     assert torch.equal(dec(good), want)
+
+
+# A reference coordinate that is no number or lies outside the grid: refused
+# before anything is decoded.  (The grid of a single point has one bin, in which
+# the oracle takes every number.)
+@pytest.mark.parametrize("dtype", [np.float32, np.float64])
+@pytest.mark.parametrize("n", [1, 300, 2048 * 40 + 5])
+def test_decode_bad_reference(bbx, orc, n, dtype):
+    x = torch.from_numpy(gen("uniform", n, 3, dtype, seed=6) + dtype(1)).cuda()
+    good = bbx.compress(x, 1e-3, eb_mode="abs", ref_mode=1)
+    h = props.parse_header(good[:128].cpu().numpy().tobytes())
+    dec = bbx.Decompressor(good[:128].cpu().numpy().tobytes())
+    bits, rec = 8 * np.dtype(dtype).itemsize, 3 * (h["mbits"] + 8 * np.dtype(dtype).itemsize)
+    raw = int.from_bytes(good.cpu().numpy().tobytes(), "little")
+    for leaf in {0, h["n_leaves"] // 2, h["n_leaves"] - 1}:
+        for axis in range(3):
+            for value in (np.nan, np.inf, -5.0):
+                at = 8 * 128 + leaf * rec + 3 * h["mbits"] + axis * bits
+                field = int.from_bytes(np.array(value, dtype).tobytes(), "little")
+                bad = ((raw & ~(((1 << bits) - 1) << at)) | (field << at)).to_bytes(len(good), "little")
+                y = torch.from_numpy(np.frombuffer(bad, np.uint8).copy()).cuda()
+                dec.pos.fill_(7.5)
+                if n == 1 and np.isfinite(value):
+                    assert np.array_equal(dec(y).cpu().numpy(), orc.decompress(bad))
+                    continue
+                with pytest.raises(OracleError):
+                    orc.decompress(bad)
+                with pytest.raises(bbx.BitboxError, match="ECORRUPT"):
+                    dec(y)
+                assert bool((dec.pos == 7.5).all()), (leaf, axis, value)
+    assert np.array_equal(dec(good).cpu().numpy(), orc.decompress(good.cpu().numpy().tobytes()))
