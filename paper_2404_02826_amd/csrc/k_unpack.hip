@@ -154,9 +154,13 @@ __device__ inline bool record_widths(const MetaView& v, u128 bits, uint32_t* m, 
 // Payload bits of each unpack block (leaves_per_block leaves), a thread per
 // leaf.  A record with a bad width or a reference coordinate outside the grid
 // makes the stream corrupt before anything is decoded: reported in P,
-// or (P null) as a total of all ones for k_dec_top.
+// or (P null) as a total of all ones for k_dec_top.  starts: each leaf's first
+// slot, when the leaves are not all equal.  (Where the threads of k_unpack
+// walked the tree for their leaves' spans, some twenty levels each, their
+// blocks waited for them: 67,108,941 particles at r = 128 470 us a decode and
+// 385 with the starts from here, 100,000,007 in 2-D 614 and 441.)
 __global__ void __launch_bounds__(kBlock) k_dec_sums(MetaView v, const uint8_t* stream, uint64_t blocks,
-                                                     uint64_t* part, DevParams* P) {
+                                                     uint64_t* part, uint32_t* starts, DevParams* P) {
   __shared__ unsigned long long sum[kBlock];
   __shared__ uint32_t bad[kBlock];
   const uint32_t lpb = leaves_per_block(v.r), nbk = kBlock / lpb;  // unpack blocks per block
@@ -179,13 +183,13 @@ __global__ void __launch_bounds__(kBlock) k_dec_sums(MetaView v, const uint8_t* 
         ok &= ref_code_from_coord(meta, (v.meta_bits + 63) / 64, at, v.dtype, v.origin[d], v.inv_w, v.G[d], &q);
       }
     }
-    if (!ok) {
-      bad[x] = 1;
-    } else {
-      uint64_t st, sz;
-      view_span(v, i, &st, &sz);
+    uint64_t st, sz;
+    view_span(v, i, &st, &sz);
+    if (!v.even) starts[i] = (uint32_t)st;
+    if (ok)
       atomicAdd(&sum[x], (unsigned long long)((sz - 1) * summ));
-    }
+    else
+      bad[x] = 1;
   }
   __syncthreads();
   const uint64_t b = (uint64_t)blockIdx.x * nbk + threadIdx.x;
@@ -272,8 +276,8 @@ struct UnpackStage {
 // (615) change little.
 template <typename T, int DIMS>
 __device__ __forceinline__ void unpack_body(const MetaView& V, uint64_t n, uint32_t layout, const uint64_t* meta,
-                                            const uint64_t* pay, uint64_t pbits, const uint64_t* part, T* out,
-                                            DevParams* P, UnpackStage& sm) {
+                                            const uint64_t* pay, uint64_t pbits, const uint64_t* part,
+                                            const uint32_t* starts, T* out, DevParams* P, UnpackStage& sm) {
   constexpr uint32_t dims = DIMS;
   const uint32_t lpb = leaves_per_block(V.r);
   const uint64_t nl = V.n_leaves;
@@ -305,12 +309,12 @@ __device__ __forceinline__ void unpack_body(const MetaView& V, uint64_t n, uint3
         }
         sm.q[d][t] = q;
       }
-      uint64_t st, sz;
-      view_span(V, i, &st, &sz);
-      sm.start[t] = (uint32_t)st;
-      if (t == nlb - 1) sm.start[nlb] = (uint32_t)(st + sz);
+      const uint32_t st = V.even ? (uint32_t)i * V.even : starts[i];
+      const uint32_t en = V.even ? st + V.even : i + 1 < nl ? starts[i + 1] : (uint32_t)n;
+      sm.start[t] = st;
+      if (t == nlb - 1) sm.start[nlb] = en;
       sm.m[t] = m;
-      bits = (sz - 1) * summ;
+      bits = (uint64_t)(en - st - 1) * summ;
     }
     // exclusive scan over the block's leaves
     const uint32_t lane = t & 63, wv = t >> 6;
@@ -371,7 +375,7 @@ __device__ __forceinline__ void unpack_body(const MetaView& V, uint64_t n, uint3
     } o;
     const uint32_t pfirst = (uint32_t)(gs > slot0 ? gs : slot0);
     uint32_t a = 0;  // last staged leaf starting at or before pfirst
-    if (mapped && full) {
+    if (mapped && gs >= slot0) {
       a = sm.map[((uint32_t)gs - mbase) >> 2];
     } else {
       uint32_t z = nlb - 1;
@@ -496,16 +500,16 @@ __device__ __forceinline__ void unpack_body(const MetaView& V, uint64_t n, uint3
 
 template <typename T>
 __global__ void __launch_bounds__(kBlock) k_unpack(MetaView V, uint64_t n, uint32_t layout, const uint64_t* part,
-                                                   const uint8_t* stream, uint64_t pay_bits, T* out,
-                                                   DevParams* P) {
+                                                   const uint32_t* starts, const uint8_t* stream,
+                                                   uint64_t pay_bits, T* out, DevParams* P) {
   if (P->status != BBX_OK) return;  // (set by earlier kernels only)
   __shared__ UnpackStage sm;
   const uint64_t* meta = (const uint64_t*)(stream + kHeaderBytes);
   const uint64_t* pay = meta + (V.meta_bits + 63) / 64;
   if (V.dims == 3)
-    unpack_body<T, 3>(V, n, layout, meta, pay, pay_bits, part, out, P, sm);
+    unpack_body<T, 3>(V, n, layout, meta, pay, pay_bits, part, starts, out, P, sm);
   else
-    unpack_body<T, 2>(V, n, layout, meta, pay, pay_bits, part, out, P, sm);
+    unpack_body<T, 2>(V, n, layout, meta, pay, pay_bits, part, starts, out, P, sm);
 }
 
 // Starts a decode: clears the status and checks that the stream's own
@@ -572,8 +576,9 @@ hipError_t launch_decompress(const DecompressPlan& p, const DecompressWs& w, con
     v.even = (p.n_leaves & (p.n_leaves - 1)) == 0 && p.n % p.n_leaves == 0 ? (uint32_t)(p.n / p.n_leaves) : 0u;
     const uint64_t per = (kBlock / lpb);  // unpack blocks per block of k_dec_sums
     uint64_t* part = w.leaf_bits;         // the unpack blocks' payload bits, then their first ones
+    uint32_t* starts = (uint32_t*)w.leaves;
     BBX_LAUNCH("dec_meta", k_dec_sums, (blocks + per - 1) / per, kBlock, 0, s, v, stream, blocks, part,
-               top ? (DevParams*)nullptr : w.params);
+               starts, top ? (DevParams*)nullptr : w.params);
     if (top) {
       BBX_LAUNCH("dec_top", k_dec_top, 1, 1024, 0, s, blocks, part, w.params, stream, p.header, p.payload_bits);
     } else {
@@ -581,10 +586,10 @@ hipError_t launch_decompress(const DecompressPlan& p, const DecompressWs& w, con
       if (e != hipSuccess) return e;
     }
     if (p.dtype == BBX_F32)
-      BBX_LAUNCH("unpack", k_unpack<float>, blocks, kBlock, 0, s, v, p.n, p.layout, part, stream,
+      BBX_LAUNCH("unpack", k_unpack<float>, blocks, kBlock, 0, s, v, p.n, p.layout, part, starts, stream,
                  p.payload_bits, (float*)pos, w.params);
     else
-      BBX_LAUNCH("unpack", k_unpack<double>, blocks, kBlock, 0, s, v, p.n, p.layout, part, stream,
+      BBX_LAUNCH("unpack", k_unpack<double>, blocks, kBlock, 0, s, v, p.n, p.layout, part, starts, stream,
                  p.payload_bits, (double*)pos, w.params);
   }
   if (d_status) BBX_LAUNCH("dec_finish", k_dec_finish, 1, 64, 0, s, w.params, d_status);

@@ -300,3 +300,14 @@ def test_decode_bad_reference(bbx, orc, n, dtype):
                     dec(y)
                 assert bool((dec.pos == 7.5).all()), (leaf, axis, value)
     assert np.array_equal(dec(good).cpu().numpy(), orc.decompress(good.cpu().numpy().tobytes()))
+
+
+# Leaves of unequal sizes (two sizes, and leaves of two depths just above a
+# power of two times r), their starts read by several decode blocks, and more
+# blocks than the one-block scan takes.
+@pytest.mark.parametrize("n,r", [(65537, 32), (2 ** 17 + 77, 64), (2 ** 15 * 5 + 1, 5), (100003, 128), (60000, 255),
+                                 (256 * 16384 + 5, 1)])
+@pytest.mark.parametrize("dims,layout,ref_mode", [(3, "aos", 0), (2, "soa", 0), (2, "aos", 1)])
+def test_decode_leaf_starts(bbx, orc, n, r, dims, layout, ref_mode):
+    pts = gen("uniform", n, dims, np.float32, seed=r)
+    check_parity(orc, bbx, pts, 1e-3, "rel", r, layout=layout, ref_mode=ref_mode, want_perm=False)
