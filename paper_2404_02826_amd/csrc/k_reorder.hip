@@ -32,7 +32,7 @@ typedef unsigned __int128 u128;
 constexpr uint32_t kRoKeys = 94;        // sums of widths 0 .. 3 * 31
 // counts per key: one per block of leaves, rounded up to 16 bytes
 __host__ __device__ inline uint64_t ro_stride(uint64_t blocks) { return (blocks + 3) & ~3ull; }
-constexpr uint32_t kRoLocal = 256;      // members ranked from LDS (more: from the layout)
+constexpr uint32_t kRoLocal = 256;      // members ranked from LDS (more: from the stream)
 constexpr uint32_t kRoStage = 64;       // words of a sequence staged in LDS (longer: written in place)
 
 __device__ inline uint64_t ro_read(const uint64_t* sec, uint64_t nwords, uint64_t at, uint32_t len) {
@@ -287,7 +287,12 @@ __global__ void __launch_bounds__(kBlock) k_ro_write(RoView v, const DevParams* 
   }
 }
 
-// A wavefront per sequence of any size.
+// A wavefront per sequence of any size: up to 256 other members are ranked by
+// keys in LDS, of one word up to R-indices of 56 bits (a position takes 8);
+// longer sequences read their codes again for every comparison.  Bound by the
+// comparisons: 30,000,001 particles in 2-D, 262,144 leaves of 114 and 115, 617
+// us (2,291 with two-word keys whatever the R-index); 13,000,001 in 3-D, 32,768
+// leaves of 396 and 397, 19.9 ms.
 __global__ void __launch_bounds__(kBlock) k_ro_long(RoView v, const DevParams* P) {
   if (P->status != BBX_OK) return;
   __shared__ u128 rk[kBlock / 64][kRoLocal];
@@ -318,20 +323,42 @@ __global__ void __launch_bounds__(kBlock) k_ro_long(RoView v, const DevParams* P
     ro_header(v, i, dst, op - dbase, lane);
     const uint64_t cout = op + hdr - dbase;
     if (sm > 0 && cnt > 0) {
-      const bool local = cnt <= kRoLocal;
       auto rindex = [&](uint32_t j) { return ro_rindex<u128>(v, ro_code(v, cin + (uint64_t)j * sm, sm), m); };
-      if (local)
-        for (uint32_t j = lane; j < cnt; j += 64) rk[wv][j] = rindex(j);
-      wave_sync();
-      for (uint32_t j = lane; j < cnt; j += 64) {
-        const u128 kj = local ? rk[wv][j] : rindex(j);
-        uint32_t rank = 0;
-        for (uint32_t t = 0; t < cnt; ++t) {
-          const u128 kt = local ? rk[wv][t] : rindex(t);
-          rank += (kt < kj || (kt == kj && t < j)) ? 1u : 0u;
+      // the members' codes, in axis order, at their ranks by key(j)
+      auto place = [&](auto&& key) {
+        for (uint32_t j = lane; j < cnt; j += 64) {
+          const u128 kj = key(j);
+          uint32_t rank = 0;
+          for (uint32_t t = 0; t < cnt; ++t) {
+            const u128 kt = key(t);
+            rank += (kt < kj || (kt == kj && t < j)) ? 1u : 0u;
+          }
+          ro_write128(dst, cout + (uint64_t)rank * sm, ro_code(v, cin + (uint64_t)j * sm, sm), sm);
         }
-        // the member's codes, in axis order, at its rank
-        ro_write128(dst, cout + (uint64_t)rank * sm, ro_code(v, cin + (uint64_t)j * sm, sm), sm);
+      };
+      if (cnt <= kRoLocal && sm <= 56) {  // (R-index, position) in one word
+        uint64_t* const keys = (uint64_t*)rk[wv];
+        for (uint32_t j = lane; j < ((cnt + 1) & ~1u); j += 64)
+          keys[j] = j < cnt ? ro_rindex<uint64_t>(v, ro_read(v.pay, v.pwords, cin + (uint64_t)j * sm, sm), m) << 8 | j
+                            : ~0ull;
+        wave_sync();
+        const ulonglong2* const o = (const ulonglong2*)keys;
+        for (uint32_t j = lane; j < cnt; j += 64) {
+          const uint64_t own = keys[j];
+          uint32_t rank = 0;
+#pragma unroll 4
+          for (uint32_t t = 0; t < (cnt + 1) / 2; ++t) {
+            const ulonglong2 x = o[t];
+            rank += (x.x < own ? 1u : 0u) + (x.y < own ? 1u : 0u);
+          }
+          ro_write(dst, cout + (uint64_t)rank * sm, ro_read(v.pay, v.pwords, cin + (uint64_t)j * sm, sm), sm);
+        }
+      } else if (cnt <= kRoLocal) {
+        for (uint32_t j = lane; j < cnt; j += 64) rk[wv][j] = rindex(j);
+        wave_sync();
+        place([&](uint32_t j) { return rk[wv][j]; });
+      } else {
+        place(rindex);
       }
       wave_sync();  // rk is rewritten by the wavefront's next sequence
     }

@@ -311,3 +311,19 @@ def test_decode_bad_reference(bbx, orc, n, dtype):
 def test_decode_leaf_starts(bbx, orc, n, r, dims, layout, ref_mode):
     pts = gen("uniform", n, dims, np.float32, seed=r)
     check_parity(orc, bbx, pts, 1e-3, "rel", r, layout=layout, ref_mode=ref_mode, want_perm=False)
+
+
+# Sequences of a wavefront: odd and even member counts up to and just past the
+# most that are ranked from LDS, R-indices on both sides of 56 bits (keys of one
+# word), two and three axes, equal codes.
+@pytest.mark.parametrize("n,r", [(8 * 67, 67), (8 * 130 + 3, 131), (8 * 256, 256), (8 * 257, 257), (4 * 258 + 1, 259),
+                                 (1, 100), (66, 66), (20011, 200)])
+@pytest.mark.parametrize("kind,dims,dtype,eb", [("uniform", 3, np.float32, 1e-3), ("uniform", 3, np.float64, 2e-6),
+                                                ("uniform", 3, np.float64, 9e-7), ("uniform", 2, np.float64, 1.9e-9),
+                                                ("ties", 3, np.float32, 1e-2)])
+def test_reordered_long_sequences(bbx, orc, n, r, kind, dims, dtype, eb):
+    s = orc.compress(gen(kind, n, dims, dtype, seed=n + r), eb, "rel", r, ref_mode=1)
+    want, want_order = orc.export_sequences_reordered(s)
+    got, order = bbx.export_sequences_reordered(torch.from_numpy(np.frombuffer(s, np.uint8).copy()).cuda())
+    assert got.cpu().numpy().tobytes() == bytes(want)
+    assert list(order) == [int(a) for a in want_order][:dims]
