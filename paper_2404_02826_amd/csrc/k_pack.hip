@@ -513,84 +513,84 @@ __device__ __forceinline__ void pack_payload_body(const SetDesc& S, const DevPar
   // the arrays needed a search for their leaf, and in sets with ragged leaves
   // every wavefront took the code for a run over two leaves as well: 13.1
   // million members in leaves of 24 and 25 84 us, 51 now; 33.6 million of 16 to
-  // 32 178 and 105; 256 sets 300 and 203; 2^27 in whole leaves 480 and 450.
-  // (runs: of the leaf itself when the block has one, as r may be any 32-bit
-  // number, far above the set; r is at most 1,024 where a block has more)
+  // 32 178 and 105; 256 sets 300 and 198; 2^27 in whole leaves 480 and 434.
+  // (r may be any 32-bit number, far above the set, but no leaf has more than
+  // n.  With a count of runs from the block's leaf sizes, which are not in
+  // scalar registers, 2^27 took 467 us)
   constexpr uint32_t V = 16 / sizeof(KT);
-  const uint32_t runs = ((nlb == 1 ? s_rec[0].size : S.r) + V - 1) / V;
+  const uint32_t runs = (uint32_t)(((S.r < S.n ? S.r : S.n) + V - 1) / V);
   for (uint32_t u = threadIdx.x; u < nlb * runs; u += kBlock) {
     const uint32_t a = u / runs;
     const LeafRec ra = s_rec[a];
     const uint32_t sma = sum_m(ra.m), at0 = (uint32_t)(s_off[a] - wlo * 64);
-    if (sma == 0) continue;
-    for (uint32_t j0 = V * (u - a * runs); j0 < ra.size; j0 += V * runs) {
-      const uint32_t num = ra.size - j0 < V ? ra.size - j0 : V;
-      PackRun<KT> kk[3];
+    const uint32_t j0 = V * (u - a * runs);  // (one run: a leaf has at most r members, and at most n)
+    if (sma == 0 || j0 >= ra.size) continue;
+    const uint32_t num = ra.size - j0 < V ? ra.size - j0 : V;
+    PackRun<KT> kk[3];
 #pragma unroll
-      for (uint32_t d = 0; d < 3; ++d)
-        if (d < dims) kk[d].load(keys + (uint64_t)d * kst + ra.start + j0);
-      uint32_t hm[3], sh3[3] = {0, 0, 0};
+    for (uint32_t d = 0; d < 3; ++d)
+      if (d < dims) kk[d].load(keys + (uint64_t)d * kst + ra.start + j0);
+    uint32_t hm[3], sh3[3] = {0, 0, 0};
 #pragma unroll
-      for (uint32_t d = 0; d < 3; ++d) {
-        const uint32_t m = d < dims ? (ra.m >> (8 * d)) & 0xffu : 0u;
-        hm[d] = (uint32_t)((1ull << m) >> 1) - (d < dims ? ra.qref[d] : 0u);
-        if (d + 1 < 3) sh3[d + 1] = sh3[d] + m;
-      }
-      // (u_d = q_d - q_ref,d + 2^(m_d - 1) lies in [0, 2^m_d), m_d <= 32, so 32-bit
-      // wrap-around arithmetic gives it; an axis with m_d = 0 adds nothing.  Bits
-      // in the LDS copy lie below kPackLdsWords * 64: 32-bit arithmetic)
-      uint32_t at = at0 + (j0 ? j0 - 1 : 0u) * sma;
-      if (sma <= 32) {
-        // codes of at most 32 bits: consecutive bits, assembled in registers and
-        // ORed into LDS one 64-bit word at a time
-        uint32_t w = at >> 6, pos = at & 63;
-        uint64_t lo = 0, hi = 0;
-        auto put = [&](auto whole) __attribute__((always_inline)) {
+    for (uint32_t d = 0; d < 3; ++d) {
+      const uint32_t m = d < dims ? (ra.m >> (8 * d)) & 0xffu : 0u;
+      hm[d] = (uint32_t)((1ull << m) >> 1) - (d < dims ? ra.qref[d] : 0u);
+      if (d + 1 < 3) sh3[d + 1] = sh3[d] + m;
+    }
+    // (u_d = q_d - q_ref,d + 2^(m_d - 1) lies in [0, 2^m_d), m_d <= 32, so 32-bit
+    // wrap-around arithmetic gives it; an axis with m_d = 0 adds nothing.  Bits
+    // in the LDS copy lie below kPackLdsWords * 64: 32-bit arithmetic)
+    uint32_t at = at0 + (j0 ? j0 - 1 : 0u) * sma;
+    if (sma <= 32) {
+      // codes of at most 32 bits: consecutive bits, assembled in registers and
+      // ORed into LDS one 64-bit word at a time
+      uint32_t w = at >> 6, pos = at & 63;
+      uint64_t lo = 0, hi = 0;
+      auto put = [&](auto whole) __attribute__((always_inline)) {
 #pragma unroll
-          for (uint32_t k = 0; k < V; ++k) {
-            if (j0 + k == 0 || (!whole && k >= num)) continue;  // the reference carries no payload
-            uint64_t c = 0;
-#pragma unroll
-            for (uint32_t d = 0; d < 3; ++d)
-              if (d < dims) c |= (uint64_t)(kk[d][k] + hm[d]) << sh3[d];
-            lo |= c << pos;
-            hi |= pos ? c >> (64 - pos) : 0ull;
-            pos += sma;
-            if (pos >= 64) {
-              atomicOr(&s_w[w], (unsigned long long)lo);
-              ++w;
-              lo = hi;
-              hi = 0;
-              pos -= 64;
-            }
-          }
-        };
-        if (__builtin_amdgcn_ballot_w64(num < V) == 0)
-          put(std::true_type());
-        else
-          put(std::false_type());
-        if (pos > 0) atomicOr(&s_w[w], (unsigned long long)lo);
-        continue;
-      }
-#pragma unroll
-      for (uint32_t k = 0; k < V; ++k) {
-        if (j0 + k == 0 || k >= num) continue;
-        const uint32_t w = at >> 6, sh = at & 63;
-        at += sma;
-        if (sma <= 64) {
+        for (uint32_t k = 0; k < V; ++k) {
+          if (j0 + k == 0 || (!whole && k >= num)) continue;  // the reference carries no payload
           uint64_t c = 0;
 #pragma unroll
           for (uint32_t d = 0; d < 3; ++d)
-            if (d < dims) c |= (uint64_t)(kk[d][k] + hm[d]) << (sh3[d] & 63);  // (64: an axis of no bits)
-          atomicOr(&s_w[w], (unsigned long long)(c << sh));
-          if (sh + sma > 64) atomicOr(&s_w[w + 1], (unsigned long long)(c >> (64 - sh)));
-        } else {
-          const u128 m = member_code(keys, kst, dims, ra, (uint64_t)ra.start + j0 + k);
-          const u128 c = m << sh;
-          atomicOr(&s_w[w], (unsigned long long)(uint64_t)c);
-          atomicOr(&s_w[w + 1], (unsigned long long)(uint64_t)(c >> 64));
-          if (sh + sma > 128) atomicOr(&s_w[w + 2], (unsigned long long)(uint64_t)(m >> (128 - sh)));
+            if (d < dims) c |= (uint64_t)(kk[d][k] + hm[d]) << sh3[d];
+          lo |= c << pos;
+          hi |= pos ? c >> (64 - pos) : 0ull;
+          pos += sma;
+          if (pos >= 64) {
+            atomicOr(&s_w[w], (unsigned long long)lo);
+            ++w;
+            lo = hi;
+            hi = 0;
+            pos -= 64;
+          }
         }
+      };
+      if (__builtin_amdgcn_ballot_w64(num < V) == 0)
+        put(std::true_type());
+      else
+        put(std::false_type());
+      if (pos > 0) atomicOr(&s_w[w], (unsigned long long)lo);
+      continue;
+    }
+#pragma unroll
+    for (uint32_t k = 0; k < V; ++k) {
+      if (j0 + k == 0 || k >= num) continue;
+      const uint32_t w = at >> 6, sh = at & 63;
+      at += sma;
+      if (sma <= 64) {
+        uint64_t c = 0;
+#pragma unroll
+        for (uint32_t d = 0; d < 3; ++d)
+          if (d < dims) c |= (uint64_t)(kk[d][k] + hm[d]) << (sh3[d] & 63);  // (64: an axis of no bits)
+        atomicOr(&s_w[w], (unsigned long long)(c << sh));
+        if (sh + sma > 64) atomicOr(&s_w[w + 1], (unsigned long long)(c >> (64 - sh)));
+      } else {
+        const u128 m = member_code(keys, kst, dims, ra, (uint64_t)ra.start + j0 + k);
+        const u128 c = m << sh;
+        atomicOr(&s_w[w], (unsigned long long)(uint64_t)c);
+        atomicOr(&s_w[w + 1], (unsigned long long)(uint64_t)(c >> 64));
+        if (sh + sma > 128) atomicOr(&s_w[w + 2], (unsigned long long)(uint64_t)(m >> (128 - sh)));
       }
     }
   }
