@@ -413,16 +413,17 @@ static void plan_batch(const SetIn* in, uint32_t nsets, BatchPlan* bp, std::vect
         if (kind == kLevelGlobal) {  // only these use selections and rows
           max_nodes = std::max(max_nodes, sh.nodes);
           max_blocks = std::max(max_blocks, sh.nodes * sh.chunks);
-          max_lab = std::max(max_lab, sh.nodes * sh.chunks * (uint64_t)(sh.chunk_elems / 64));
         }
-        if (kind != kLevelWave) bin_nodes = std::max(bin_nodes, sh.nodes);  // radix bins
+        if (pair_first(D, k))  // only these use labels
+          max_lab = std::max(max_lab, sh.nodes * sh.chunks * (uint64_t)(sh.chunk_elems / 64));
+        if (k < D.nbins) bin_nodes = sh.nodes;  // radix bins
       }
       bp->max_gl = std::max(bp->max_gl, D.gl);
       D.mm_blocks = (uint32_t)mm[s];
       D.key_off = key_bytes;
       D.idx_off = idx_n;
       D.hist_off = hist_n;
-      D.hist_half = bin_nodes * kHistBins;
+      D.hist_half = bp->fold ? (D.nglobal ? (uint64_t)kHistBins << (D.nglobal - 1) : 0) : bin_nodes * kHistBins;
       D.sel_off = sel_n;
       D.sel_half = max_nodes;
       D.rows_off = rows_n * kRowStride;
@@ -437,7 +438,7 @@ static void plan_batch(const SetIn* in, uint32_t nsets, BatchPlan* bp, std::vect
       key_bytes += align_up((uint64_t)D.dims * D.kst * 4);
       if (I.need_idx || D.track) idx_n += (n + 63) & ~63ull;
       if (D.reduce && !(I.need_idx || D.track)) idx_n += (n + 63) & ~63ull;
-      hist_n += (bp->fold ? 3 : 2) * bin_nodes * kHistBins;
+      hist_n += bp->fold ? hist_entries(D) : 2 * D.hist_half;
       sel_n += 2 * max_nodes;
       rows_n += (bp->fold ? 1 : 2) * max_blocks;
       cb_n += 2 * D.cb_half;
@@ -597,7 +598,10 @@ static std::string check_plan(const SetIn* in, uint32_t nsets) {
     const uint64_t next_rows = s + 1 < nsets && descs[s + 1].n ? descs[s + 1].rows_off / kRowStride
                                                                : rows_total;
     const uint64_t rows_cap = next_rows - D.rows_off / kRowStride;
-    const uint64_t bin_nodes = D.hist_half / kHistBins;
+    const uint64_t next_bins = s + 1 < nsets && descs[s + 1].n && !descs[s + 1].split ? descs[s + 1].hist_off
+                                                                                     : bp.hist_entries;
+    if (next_bins - D.hist_off < (bp.fold ? hist_entries(D) : 2 * D.hist_half))
+      return where(s, 0) + "radix bins too few";
     int prev_kind = kLevelGlobal;
     uint64_t sel_need = 0;
     // set s's share of a family's grid at level k (the family's array must exist)
@@ -642,7 +646,9 @@ static std::string check_plan(const SetIn* in, uint32_t nsets) {
         continue;
       }
       // block-local and global levels count radix bins of their nodes
-      if (sh.nodes > bin_nodes || k >= D.nbins) return where(s, k) + "radix bins too few";
+      if (k >= D.nbins) return where(s, k) + "radix bins too few";
+      if ((!bp.fold || kind == kLevelGlobal) && sh.nodes * kHistBins > D.hist_half)
+        return where(s, k) + "radix bins too few";
       if ((kind == kLevelGlobal) != (k < D.nglobal)) return where(s, k) + "global level count";
       if (bp.fold && kind == kLevelGlobal && k < D.mid_depth && !bp.lv_mid[k])
         return where(s, k) + "middle digits not launched";

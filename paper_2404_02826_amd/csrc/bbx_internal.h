@@ -110,7 +110,7 @@ struct SetDesc {
   uint64_t key_off;       // byte offset into each key buffer (capacity dims*n*4)
   uint64_t idx_off;       // u32 offset into each index buffer
   uint64_t hist_off;      // u32 offset into the histogram bins
-  uint64_t hist_half;     // u32 entries of each of the set's three bin regions
+  uint64_t hist_half;     // u32 entries of each of the set's two bin regions, or (no paired levels) of each global level's
   uint64_t sel_off;       // NodeSel offset
   uint64_t sel_half;      // NodeSel entries of each of the set's two selection regions (by depth, or histogram, parity)
   uint64_t rows_off;      // u32 offset into the chunk rows
@@ -485,40 +485,52 @@ __device__ inline uint32_t* hist_level(const SetDesc& S, uint32_t depth, uint32_
 
 // Without paired levels no kernel is launched for a selection: whoever needs
 // a digit of a median finds it itself in the histogram that the kernel before
-// it built.  The histograms of a set follow each other through its three
-// regions: histogram t lies in region t mod 3, kernel by kernel one is read
-// (t - 1), one is built (t), and the next one's region (t + 1) is cleared.
-// A global level of np digits builds np of them (the first in the partition of
-// the level above, or in quantization), or at most two from mid_depth on; a
-// block-local level one.
+// it built.  Kernel by kernel one histogram is read (t - 1), one is built (t),
+// and the next one's bins (t + 1) are cleared.  A global level of np digits
+// builds np of them (the first in the partition of the level above, or in
+// quantization), or at most two from mid_depth on, histogram t in region t mod
+// 3 of the set's three (of at most 2 MB each: a global level has at most 2,048
+// nodes); a block-local level one, in one of two further regions, the last such
+// level's of its own nodes, the other of half as many.
 __host__ __device__ inline uint32_t digit_passes(uint32_t G) { return G > 8 ? 1 + (G - 1) / 8 : 1; }
-// histogram index of level `depth`'s first digit
+// histogram index of level `depth`'s first digit (depth at most nglobal)
 __device__ inline uint32_t hist_index(const SetDesc& S, const uint32_t* G, uint32_t depth) {
   const uint32_t np[3] = {digit_passes(G[0]), digit_passes(G[1]), digit_passes(G[2])};
   uint32_t t = 0, a = 0;
   for (uint32_t k = 0; k < depth; ++k) {
     const uint32_t x = a == 0 ? np[0] : (a == 1 ? np[1] : np[2]);
-    t += k >= S.nglobal ? 1u : (k >= S.mid_depth && x > 2 ? 2u : x);
+    t += k >= S.mid_depth && x > 2 ? 2u : x;
     a = a + 1 == S.dims ? 0u : a + 1;
   }
   return t;
 }
-__device__ inline uint32_t* hist_region(const SetDesc& S, uint32_t t, uint32_t* hist) {
+// the bins of a global level's histogram t
+__device__ inline uint32_t* hist_global(const SetDesc& S, uint32_t t, uint32_t* hist) {
   return hist + (t % 3) * S.hist_half;
+}
+// the bins of level `depth`, for a global one of its histogram t
+__device__ inline uint32_t* hist_region(const SetDesc& S, uint32_t t, uint32_t depth, uint32_t* hist) {
+  if (depth < S.nglobal) return hist_global(S, t, hist);
+  return hist + 3 * S.hist_half + ((S.nbins - 1 - depth) & 1u ? 128ull << S.nbins : 0ull);
+}
+// entries of a set's bins
+__host__ __device__ inline uint64_t hist_entries(const SetDesc& S) {
+  const uint32_t nl = S.nbins - S.nglobal;  // block-local levels
+  return 3 * S.hist_half + (nl > 0 ? 128ull << S.nbins : 0ull) + (nl > 1 ? 64ull << S.nbins : 0ull);
 }
 // nodes whose bins level `depth` uses (0: none)
 __device__ inline uint64_t hist_nodes(const SetDesc& S, uint32_t depth) {
   return depth < S.nbins ? 1ull << depth : 0ull;
 }
-// Block lb of nblk of a set's launch clears its share of histogram t's
-// region, for the nodes of level `depth`.
-__device__ inline void hist_clear(const SetDesc& S, uint32_t t, uint32_t depth, uint64_t lb, uint64_t nblk,
-                                  uint32_t* hist) {
-  const uint64_t entries = hist_nodes(S, depth) << 8;
-  if (!entries) return;
-  const uint64_t per = (entries + nblk - 1) / nblk, a = lb * per;
+// Block lb of nblk of a set's launch clears its share of level `depth`'s bins
+// (of a global one's histogram t), those of the nodes from `from` on.
+__device__ inline void hist_clear(const SetDesc& S, uint32_t t, uint32_t depth, uint64_t from, uint64_t lb,
+                                  uint64_t nblk, uint32_t* hist) {
+  const uint64_t entries = hist_nodes(S, depth) << 8, first = from << 8;
+  if (entries <= first) return;
+  const uint64_t per = (entries - first + nblk - 1) / nblk, a = first + lb * per;
   const uint64_t b = a + per < entries ? a + per : entries;
-  uint32_t* h = hist_region(S, t, hist);
+  uint32_t* h = hist_region(S, t, depth, hist);
   for (uint64_t i = a + threadIdx.x; i < b; i += blockDim.x) h[i] = 0;
 }
 

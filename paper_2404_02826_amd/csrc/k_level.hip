@@ -601,7 +601,7 @@ __device__ void fold_hist_body(uint32_t depth, uint32_t pass, const SetDesc& S, 
   uint64_t st, sz;
   wave_node_span(n, depth, j, &st, &sz);
   if (sz <= S.r) {
-    hist_clear(S, t + 1, LAST ? depth + 1 : depth, c.lb, nblk, hist);
+    hist_clear(S, t + 1, LAST ? depth + 1 : depth, 0, c.lb, nblk, hist);
     return;
   }
   const KT* q = (const KT*)keys + (uint64_t)d * S.kst;
@@ -614,7 +614,7 @@ __device__ void fold_hist_body(uint32_t depth, uint32_t pass, const SetDesc& S, 
       const NodeSel ns = sel[((t - 1) & 1) * S.sel_half + j];
       prefix = uniform32(ns.prefix), rank = uniform32(ns.rank);
     }
-    ok = wave_digit(hist_region(S, t - 1, hist) + (j << 8), rank, &b, &rest);
+    ok = wave_digit(hist_global(S, t - 1, hist) + (j << 8), rank, &b, &rest);
     prefix = (prefix << dp_width(pl, p0)) | b;
     rank = rest;
   }
@@ -635,7 +635,7 @@ __device__ void fold_hist_body(uint32_t depth, uint32_t pass, const SetDesc& S, 
       lh[threadIdx.x] = 0;
       __syncthreads();
     }
-  uint32_t* const bins = hist_region(S, t, hist) + (j << 8);
+  uint32_t* const bins = hist_global(S, t, hist) + (j << 8);
   const uint32_t w = dp_width(pl, pass), sh = dp_shift(pl, pass), hs = sh + w;
   const uint32_t nb = 1u << w, mask = nb - 1;
   const uint64_t beg64 = ch * (uint64_t)c.sh.chunk_elems;
@@ -669,7 +669,7 @@ __device__ void fold_hist_body(uint32_t depth, uint32_t pass, const SetDesc& S, 
     ns.jeq = 0;
     sel[(t & 1) * S.sel_half + j] = ns;
   }
-  hist_clear(S, t + 1, LAST ? depth + 1 : depth, c.lb, nblk, hist);
+  hist_clear(S, t + 1, LAST ? depth + 1 : depth, 0, c.lb, nblk, hist);
 }
 
 template <bool LAST>
@@ -726,7 +726,7 @@ __device__ inline bool fold_select(uint32_t depth, const SetDesc& S, const DevPa
   const DigitPlan pl = digit_plan(P->G[depth % S.dims]);
   const NodeSel ns = sel[(t & 1) * S.sel_half + j];
   uint32_t b = 0, rest = 0;
-  const bool ok = wave_digit(hist_region(S, t, hist) + (j << 8), uniform32(ns.rank), &b, &rest);
+  const bool ok = wave_digit(hist_global(S, t, hist) + (j << 8), uniform32(ns.rank), &b, &rest);
   *v = (uniform32(ns.prefix) << dp_width(pl, pl.npass - 1)) | b;
   *jeq = rest;
   uint32_t lt = 0, eq = 0;
@@ -1312,7 +1312,7 @@ __global__ void __launch_bounds__(kBlock) k_scatter(uint32_t depth, uint32_t fol
   uint32_t* idst = S.track ? idst0 + S.idx_off : nullptr;
   uint32_t* const hist = hist0 + S.hist_off;
   const uint32_t t1 = fold ? hist_index(S, P->G, depth + 1) : 0u;  // the next level's first histogram
-  uint32_t* const next_hist = fold ? hist_region(S, t1, hist) : hist_level(S, depth + 1, hist);
+  uint32_t* const next_hist = fold ? hist_region(S, t1, depth + 1, hist) : hist_level(S, depth + 1, hist);
   auto select = [&](uint32_t* v, uint32_t* jeq, uint32_t* lt_run, uint32_t* eq_run) -> bool {
     if (fold) {
       if (fold_select(depth, S, P, c, t1 - 1, sel0 + S.sel_off, hist, rows0 + S.rows_off, v, jeq, lt_run, eq_run))
@@ -1336,9 +1336,9 @@ __global__ void __launch_bounds__(kBlock) k_scatter(uint32_t depth, uint32_t fol
     // or (block-local) the level after it
     const uint64_t nblk = c.sh.nodes * c.sh.chunks;
     if (depth + 1 >= S.nglobal)
-      hist_clear(S, t1 + 1, depth + 2, c.lb, nblk, hist);
+      hist_clear(S, t1 + 1, depth + 2, 0, c.lb, nblk, hist);
     else if (digit_passes(P->G[(depth + 1) % S.dims]) > 1)
-      hist_clear(S, t1 + 1, depth + 1, c.lb, nblk, hist);
+      hist_clear(S, t1 + 1, depth + 1, 0, c.lb, nblk, hist);
   }
 }
 
@@ -1445,16 +1445,8 @@ __global__ void __launch_bounds__(kBlock) k_level_local(uint32_t depth, uint32_t
   const uint32_t d = depth % S.dims;
   const uint8_t* keys = src0 + S.key_off;
   uint32_t* const hist = hist0 + S.hist_off;
-  uint32_t* this_hist = nullptr;
-  uint32_t* next_hist = nullptr;
-  if (fold) {
-    const uint32_t t = hist_index(S, P->G, depth);
-    this_hist = hist_region(S, t, hist);
-    next_hist = hist_region(S, t + 1, hist);
-  } else {
-    this_hist = hist_level(S, depth, hist);
-    next_hist = hist_level(S, depth + 1, hist);
-  }
+  uint32_t* const this_hist = fold ? hist_region(S, 0, depth, hist) : hist_level(S, depth, hist);
+  uint32_t* const next_hist = fold ? hist_region(S, 0, depth + 1, hist) : hist_level(S, depth + 1, hist);
   if (sz > S.r) {
     const DigitPlan pl = digit_plan(P->G[d]);
     // the level above built this node's first-digit histogram when the code
@@ -1479,7 +1471,9 @@ __global__ void __launch_bounds__(kBlock) k_level_local(uint32_t depth, uint32_t
   else
     scatter_body<uint32_t, TRACK, kPartRuns>(depth, S, P, c, select, src0 + S.key_off, dst0 + S.key_off, isrc,
                                              idst, next_hist, sm);
-  if (fold) hist_clear(S, hist_index(S, P->G, depth) + 2, depth + 2, c.lb, c.sh.nodes, hist);
+  // the level after the next has this one's region; this level's nodes have
+  // cleared their own bins (local_median)
+  if (fold) hist_clear(S, 0, depth + 2, c.sh.nodes, c.lb, c.sh.nodes, hist);
 }
 
 // Median of a node's axis codes by one wavefront (nodes of at most kWaveNode

@@ -161,7 +161,7 @@ __global__ void __launch_bounds__(kBlock) k_epilogue(const SetDesc* sets, const 
   const SetDesc& S = sets[blockIdx.x];
   DevParams* P = params + blockIdx.x;
   if (fold && S.nbins > 0)
-    for (uint32_t t = 0; t < 2; ++t) hist_region(S, t, hist0 + S.hist_off)[threadIdx.x] = 0;
+    for (uint32_t t = 0; t < 2; ++t) hist_global(S, t, hist0 + S.hist_off)[threadIdx.x] = 0;
   __shared__ double red[7][kBlock / 64];
   double v[7];
 #pragma unroll

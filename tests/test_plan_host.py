@@ -66,3 +66,25 @@ def test_plan_check_rejects_bad_arguments():
         bbx.plan_check([dict(n=5000, level_blocks=5000)])
     with pytest.raises(bbx.BitboxError, match="level_pairs"):
         bbx.plan_check([dict(n=5000, level_pairs=2)])
+
+
+# Workspace bytes that callers may have reserved for good (those of the library
+# before levels found their own medians): never more.
+@pytest.mark.parametrize("n,dims,r,ref_mode,most", [
+    (4096, 3, 32, 0, 139520), (65537, 3, 8, 0, 2548992), (1000003, 3, 32, 1, 34703872),
+    (16777217, 3, 32, 0, 571711232), (16777217, 2, 2000, 0, 418682624), (33554433, 2, 300, 0, 835950592),
+    (134217728, 3, 32, 0, 4502827264), (134217729, 3, 32, 0, 4539005696), (1073741825, 2, 2000, 0, 26483597056),
+    (2147483649, 2, 2000, 0, 52962240256)])
+def test_workspace_not_larger(n, dims, r, ref_mode, most):
+    assert bbx.compress_workspace_size(n, dims, leaf_size=r, ref_mode=ref_mode) <= most
+
+
+def test_plan_shares_of_all_blocks():
+    # as above with the 4,096 blocks a level that sets share: the shapes of
+    # shares above a set alone's 1,024, and block-local levels at every depth
+    for n in _sizes()[::3] + [(1 << 30) + 1, (1 << 32) - 1]:
+        for share in (1025, 1500, 2048, 3000, 4095, 4096):
+            m = max(1, round(n * (4096 / share - 1)))
+            m = min(m, (1 << 32) - 1)
+            bbx.plan_check([dict(n=n, leaf_size=32), dict(n=m, leaf_size=32)])
+            bbx.plan_check([dict(n=n, leaf_size=2000, want_perm=True), dict(n=m, leaf_size=300)])
