@@ -1236,7 +1236,7 @@ static ReorderLayout reorder_layout(const HostHeader& h) {
   L.dec = c.take(carve_decompress(h, nullptr, &w));
   L.whist = c.take(3 * 64 * 4);
   L.key = c.take((size_t)h.n_leaves);
-  L.bcount = c.take(4 * 94 * (((size_t)((h.n_leaves + kBlock - 1) / kBlock) + 3) & ~(size_t)3));
+  L.bcount = c.take(4 * 94 * (((size_t)((h.n_leaves + kBlock - 1) / kBlock) + 1) & ~(size_t)1));
   L.order = c.take(4 * (size_t)h.n_leaves);
   L.sbits = c.take(8 * (size_t)h.n_leaves);
   L.total = c.off;

@@ -30,8 +30,9 @@ namespace bbx {
 typedef unsigned __int128 u128;
 
 constexpr uint32_t kRoKeys = 94;        // sums of widths 0 .. 3 * 31
-// counts per key: one per block of leaves, rounded up to 16 bytes
-__host__ __device__ inline uint64_t ro_stride(uint64_t blocks) { return (blocks + 3) & ~3ull; }
+// counts per key: one per block of leaves, an even number (94 keys: a multiple of
+// four entries in all)
+__host__ __device__ inline uint64_t ro_stride(uint64_t blocks) { return (blocks + 1) & ~1ull; }
 constexpr uint32_t kRoLocal = 256;      // members ranked from LDS (more: from the stream)
 constexpr uint32_t kRoStage = 64;       // words of a sequence staged in LDS (longer: written in place)
 

@@ -88,3 +88,14 @@ def test_plan_shares_of_all_blocks():
             m = min(m, (1 << 32) - 1)
             bbx.plan_check([dict(n=n, leaf_size=32), dict(n=m, leaf_size=32)])
             bbx.plan_check([dict(n=n, leaf_size=2000, want_perm=True), dict(n=m, leaf_size=300)])
+
+
+# The same of the reordered export's workspace, of few leaves and of many.
+@pytest.mark.parametrize("n,r,dims,dtype,most", [
+    (1, 1, 3, np.float32, 3328), (33, 8, 2, np.float64, 3328), (257, 1, 2, np.float32, 19456),
+    (513, 1, 3, np.float32, 38144), (2049, 2, 3, np.float64, 87808), (100000, 32, 3, np.float32, 488192)])
+def test_reordered_workspace_not_larger(n, r, dims, dtype, most):
+    from oracle import Oracle
+    from synth import uniform_cube
+    s = Oracle().compress(uniform_cube(n, seed=4, dims=dims, dtype=dtype), 1e-3, "rel", r, ref_mode=1)
+    assert 0 < bbx.load().bbx_export_reordered_workspace_size(s[:128], 128) <= most
