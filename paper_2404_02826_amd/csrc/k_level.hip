@@ -846,8 +846,10 @@ __device__ __forceinline__ void part_range(uint32_t beg, uint32_t end, const KT*
   uint32_t* const hl = lhist + lh_slot(true, 0);
   uint32_t* const hr = lhist + lh_slot(false, 0);
   uint32_t buf = 0;
-  for (uint32_t g = beg; g < end; g += G, buf ^= 1) {
-    const uint32_t gsz = end - g < G ? end - g : G;
+  // (by what is left, not by where the next group starts, which for a node of
+  // nearly 2^32 members does not fit 32 bits)
+  for (uint32_t g = beg, rest = end - beg; rest > 0; g += G, rest = rest > G ? rest - G : 0, buf ^= 1) {
+    const uint32_t gsz = rest < G ? rest : G;
     // members the thread holds; those past the chunk count as neither
     const uint32_t mine = gsz == G ? R : (t0 >= gsz ? 0u : (gsz - t0 < (uint32_t)R ? gsz - t0 : R));
     const bool full = gsz == G;
@@ -865,7 +867,7 @@ __device__ __forceinline__ void part_range(uint32_t beg, uint32_t end, const KT*
     else
       count(std::false_type());
     const uint32_t incl = wave_incl(x);
-    if (g + G < end) load(g + G, n0, n1, n2, ni);
+    if (rest > G) load(g + G, n0, n1, n2, ni);
     if (lane == 63) cnt[buf][wv] = incl;
     __syncthreads();
     const uint4 c = *(const uint4*)&cnt[buf][0];
