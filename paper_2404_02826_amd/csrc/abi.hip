@@ -337,7 +337,7 @@ static void plan_batch(const SetIn* in, uint32_t nsets, BatchPlan* bp, std::vect
         while ((n >> K) > D.r) ++K;
         D.gl = ((n + (1ull << K) - 1) >> K) <= D.r ? K : K + 1;
       }
-      // paired global levels (k_pair.hip): depths 2p and 2p + 1 while both
+      // paired global levels (launch_pair): depths 2p and 2p + 1 while both
       // use global histograms and every node of the second still splits
       if (I.prm.level_pairs == 1)
         while (2 * D.npairs + 1 < D.gl && level_kind(n, 2 * D.npairs) == kLevelGlobal &&
@@ -407,7 +407,6 @@ static void plan_batch(const SetIn* in, uint32_t nsets, BatchPlan* bp, std::vect
           if (!pair_second(D, k)) bp->sel_wide[k] = 1;
           if (pair_first(D, k)) bp->pair_wide[k] = 1;  // the second level's selects use these chunks
         }
-        if (fam == kFamGlobal) bp->scat_stage[k] = bp->scatter_mode == 1;
         lv[s].push_back(sh.nodes * sh.chunks);
         nd[s].push_back(sh.nodes);
         if (kind == kLevelGlobal) {  // only these use selections and rows

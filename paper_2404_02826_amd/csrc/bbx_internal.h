@@ -164,7 +164,7 @@ struct Ws {
 __host__ __device__ inline bool seq_stream(const SetDesc& S) { return S.reduce != 0 || S.split != 0; }
 
 // Paired global levels: depths 2p and 2p + 1 (p < npairs) partition the
-// codes with one data movement (k_pair.hip), so the key buffer that holds a
+// codes with one data movement (launch_pair), so the key buffer that holds a
 // level's codes is the depth minus the pairs before it, mod 2.
 __host__ __device__ inline bool pair_first(const SetDesc& S, uint32_t depth) {
   return (depth & 1u) == 0 && depth / 2 < S.npairs;
@@ -728,13 +728,12 @@ struct BatchPlan {
   uint8_t sel_wide[kMaxDepth];   // some set's nodes have > 256 chunks at global level k
   uint32_t tile_rows;            // every tile of the batch is one that k_rows takes
   uint32_t scatter_mode;         // bbx_params.scatter_stage of the batch
-  uint8_t scat_stage[kMaxDepth]; // scatter_mode 1: some set has a global level k
   uint8_t lv_wave[kMaxDepth];    // some set handles level k one wavefront per node
   uint8_t lv_fused[kMaxDepth];   // some set handles levels k, k + 1 fused, a wavefront per node
   uint8_t lv_fused4[kMaxDepth];  // some set handles levels k, k + 1 fused, a block per node
   uint8_t lv_fused16[kMaxDepth]; // the same with a block of 16 wavefronts per node
   uint8_t lv_single[kMaxDepth];  // some set partitions global level k alone (k_scatter)
-  uint8_t lv_pair[kMaxDepth];    // some set partitions global levels k, k + 1 together (k_pair.hip)
+  uint8_t lv_pair[kMaxDepth];    // some set partitions global levels k, k + 1 together (launch_pair)
   uint8_t pair_wide[kMaxDepth];  // some paired set's nodes have > 256 chunks at level k
   uint32_t reduce;               // some set runs the bit box reduction
   uint32_t red_chip32, red_chip64;  // LDS bytes of the reduce sets that keep all their state on chip, by mask size (0: none)

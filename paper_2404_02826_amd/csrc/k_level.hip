@@ -42,11 +42,6 @@ namespace bbx {
 
 __device__ inline uint32_t popc64(uint64_t v) { return (uint32_t)__popcll(v); }
 
-// element d of a 3-array held in registers (d is wave-uniform; no dynamic indexing)
-__device__ inline uint32_t pick3(const uint32_t* k, uint32_t d) {
-  return d == 0 ? k[0] : (d == 1 ? k[1] : k[2]);
-}
-
 // Block-wide exclusive scan of one u64 per thread (256 threads); returns the
 // exclusive prefix and writes the block total to *total.
 __device__ inline uint64_t block_exscan_u64(uint64_t v, uint64_t* total) {
@@ -1074,7 +1069,7 @@ __device__ __forceinline__ void scatter_stage(uint32_t g, uint32_t end, const ui
                                               uint32_t be, uint32_t lbg, uint32_t nl,
                                               uint32_t v, uint32_t jeq, bool cl, bool cr,
                                               uint32_t shn, uint32_t maskn, uint32_t* lhist,
-                                              uint32_t* stg, bool track, DevParams* P) {
+                                              uint32_t* stg, DevParams* P) {
   const uint32_t lane = threadIdx.x & 63;
   const uint32_t wv = (uint32_t)__builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
   const uint32_t base = g + wv * (kGroup / (kBlock / 64));
@@ -1168,10 +1163,10 @@ __device__ __forceinline__ void scatter_range(uint32_t beg, uint32_t end, const 
       const uint32_t nl = lt_run + umin32(eq_run, jeq) - lbg;
       if (full)
         scatter_stage<NA, true, TRACK>(g, end, k, ki, rr, bl, be, lbg, nl, v, jeq, cl, cr, shn,
-                                       maskn, lhist, stg, is != nullptr, P);
+                                       maskn, lhist, stg, P);
       else
         scatter_stage<NA, false, TRACK>(g, end, k, ki, rr, bl, be, lbg, nl, v, jeq, cl, cr, shn,
-                                        maskn, lhist, stg, is != nullptr, P);
+                                        maskn, lhist, stg, P);
       __syncthreads();
       scatter_drain<KT, NA, TRACK>(g, full ? (uint32_t)kGroup : end - g, lbg, nl, sz >> 1, sz, B0, B1,
                                    B2, id, stg, P);
@@ -1705,11 +1700,6 @@ __global__ void __launch_bounds__(kBlock) k_level_wave(uint32_t depth, uint32_t 
 // wavefront holding R = kFuseNode / 64 rows of 64 consecutive members
 // (wavefront w: members [w kFuseNode, (w + 1) kFuseNode)).
 constexpr int kFuseRows = (int)(kFuseNode / 64);
-
-// sum over the wavefront (uniform result)
-__device__ inline uint32_t wave_sum(uint32_t x) {
-  return (uint32_t)__builtin_amdgcn_readlane((int)wave_incl(x), 63);
-}
 
 template <int W>
 __device__ inline void fuse_sync() {
@@ -2827,9 +2817,9 @@ hipError_t launch_pair(const BatchPlan& bp, const Ws& w, uint32_t k, hipStream_t
 
 static void launch_scatter(const BatchPlan& bp, const Ws& w, uint32_t k, hipStream_t s) {
   auto kern = bp.track ? k_scatter<true, kPartRuns> : k_scatter<false, kPartRuns>;
-  if (bp.scatter_mode == kPartStaged && bp.scat_stage[k])
+  if (bp.scatter_mode == kPartStaged)
     kern = bp.track ? k_scatter<true, kPartStaged> : k_scatter<false, kPartStaged>;
-  else if (bp.scatter_mode != kPartRuns)
+  else if (bp.scatter_mode == kPartDirect)
     kern = bp.track ? k_scatter<true, kPartDirect> : k_scatter<false, kPartDirect>;
   BBX_LAUNCH("level_scatter", kern,
              bp.g_lv[k], kBlock, 0, s, k, bp.fold, bp.nsets, w.pre + bp.o_lv[k], w.sets, w.params, w.sel,

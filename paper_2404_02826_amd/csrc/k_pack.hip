@@ -383,46 +383,7 @@ __device__ inline u128 member_code(const KT* keys, uint64_t stride, uint32_t dim
 
 __device__ inline uint32_t sum_m(uint32_t m) { return (m & 0xffu) + ((m >> 8) & 0xffu) + ((m >> 16) & 0xffu); }
 
-// largest i in [lo, hi] with off[i] - base <= b (offsets non-decreasing)
-__device__ inline uint64_t search_off(const uint64_t* off, uint64_t base, uint64_t lo, uint64_t hi,
-                                      uint64_t b) {
-  while (lo < hi) {
-    const uint64_t mid = lo + (hi - lo + 1) / 2;
-    if (off[mid] - base <= b)
-      lo = mid;
-    else
-      hi = mid - 1;
-  }
-  return lo;
-}
-
 constexpr uint32_t kLeafStage = 256;   // leaves per block (leaves_per_block)
-
-// 64-bit forms for members whose code has at most 64 bits (the usual case)
-template <typename KT>
-__device__ inline uint64_t member_code64(const KT* base, uint64_t stride, uint32_t dims,
-                                         const LeafRec& rec, uint64_t t) {
-  uint64_t v = 0;
-  uint32_t at = 0;
-#pragma unroll
-  for (uint32_t d = 0; d < 3; ++d) {
-    if (d >= dims) break;
-    const uint32_t m = (rec.m >> (8 * d)) & 0xffu;
-    if (m == 0) continue;
-    const uint32_t q = base[d * stride + t];
-    const uint64_t u = (uint64_t)((int64_t)q - (int64_t)rec.qref[d] + ((int64_t)1 << (m - 1)));
-    v |= u << at;
-    at += m;
-  }
-  return v;
-}
-// OR a code of len <= 64 bits starting at absolute bit `at` into the word at w0
-__device__ inline void or_into64(uint64_t& word, uint64_t w0, uint64_t val, uint64_t at) {
-  if (at >= w0)
-    word |= val << (uint32_t)(at - w0);  // at - w0 < 64 (callers keep at < w0 + 64)
-  else
-    word |= val >> (uint32_t)(w0 - at);  // w0 - at < len <= 64
-}
 
 // 16 bytes of consecutive codes, of any element alignment
 template <typename KT>
