@@ -245,10 +245,10 @@ static void plan_batch(const SetIn* in, uint32_t nsets, BatchPlan* bp, std::vect
   // block target of the global levels: kSoloLevelBlocks for a set alone (a
   // larger target makes the levels' blocks too short: cosmology 2^24 1.69
   // against 2.03 ms per round trip at 4096); in a batch each set's share of
-  // kLevelBlocks by particle count (256 sets of 10^3..10^6 particles: 4.21 ms
-  // against 4.35 and 4.55 with shares of 2 and 4 kLevelBlocks, 4.13 and 4.25
-  // with a half and a quarter; 1,024 such sets: 10.99, 11.18 and 11.56 ms with
-  // one, a half and a quarter)
+  // kLevelBlocks by particle count (256 sets of 10^3..10^6 particles: 3.40 ms
+  // against 3.54 and 3.70 with shares of 2 and 4 kLevelBlocks, 3.31 and 3.39
+  // with a half and a quarter; 1,024 such sets: 9.77 against 9.82 and 10.08,
+  // 9.89 and 10.19)
   uint64_t n_total = 0;
   for (uint32_t s = 0; s < nsets; ++s) n_total += in[s].n;
   auto level_blocks = [&](uint64_t n, uint32_t cap) -> uint32_t {
@@ -892,6 +892,8 @@ static uint64_t stream_bytes_of(const HostHeader& h) {
   return kHeaderBytes + ((h.meta_bits + 63) / 64) * 8 + ((h.payload_bits + 63) / 64) * 8;
 }
 
+// (leaves: a record per leaf for the exports and for version 2; decoding a
+// version-1 stream keeps each leaf's first slot there)
 static size_t carve_decompress(const HostHeader& h, uint8_t* base, DecompressWs* w) {
   Carve c;
   const size_t o_params = c.take(sizeof(DevParams));

@@ -21,8 +21,8 @@
 //   level, as batches with paired levels have (k_hist_mid, k_select_mid,
 //   k_hist_last, k_select_last), cost more than the work of a small set's
 //   level: eight launches a level against four, or two where a block finds
-//   the middle digits by itself (compress of 65,536 particles 285 -> 233 us,
-//   2^24 1,476 -> 1,333, 2^27 9,930 -> 9,770, 256 sets 4,490 -> 4,215).
+//   the middle digits by itself (compress of 65,536 particles 278 -> 207 us,
+//   2^24 1,476 -> 1,333, 2^27 9,930 -> 9,772, 256 sets 4,486 -> 4,195).
 //   k_level_local  a level whose nodes each fit one block: median and
 //                  partition per block, no global histograms
 //   k_level_wave   a level of nodes of <= 4096 members: one wavefront each

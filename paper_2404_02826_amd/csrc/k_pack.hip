@@ -17,11 +17,12 @@
 //   pack_payload    leaf-aligned blocks: each block owns the payload words
 //                   that start inside its leaves, ORs every member code
 //                   q - q_ref + 2^(m-1) into an LDS copy of those words (LDS
-//                   atomics; 8 consecutive members per thread, assembled in
-//                   registers and ORed a word at a time when they share a
-//                   leaf), completes its last word from the next leaves (a
-//                   member per lane), then writes every owned word once with
-//                   a coalesced plain store (no global atomics, no zeroing of
+//                   atomics; a run of 8 or 4 consecutive members of one leaf
+//                   per thread, 16 bytes an axis, codes of up to 32 bits put
+//                   together in registers and ORed a word at a time),
+//                   completes its last word from the next leaves (a member
+//                   per lane), then writes every owned word once with a
+//                   coalesced plain store (no global atomics, no zeroing of
 //                   the output)
 #include <type_traits>
 
@@ -99,7 +100,9 @@ __global__ void __launch_bounds__(kBlock) k_scan_top(uint64_t nparts, uint64_t* 
 
 // fold: part holds the block totals themselves (no k_scan_top before): each
 // block sums those before its own, and the last one also reports the total as
-// k_scan_top does.
+// k_scan_top does.  (It may set the status while other blocks start: what they
+// then do is of no use, but stays within bits, which every later launch of the
+// call leaves alone.)
 constexpr uint64_t kScanFold = 1024;
 __global__ void __launch_bounds__(kBlock) k_scan_down(uint64_t count, uint64_t* bits,
                                                       const uint64_t* part, uint32_t fold, uint64_t* total,
@@ -404,9 +407,10 @@ constexpr uint32_t kPackLdsWords = 3072;  // payload words of one block's member
 // of a run of a leaf's members into an LDS copy of the payload words the
 // leaves' bits touch (LDS atomics), and the block stores the words whose first
 // bit lies in its leaves' bit range with coalesced plain stores.  The last such
-// word can also hold the first bits of the next block's leaves: one thread
-// adds those few members from global memory.  Blocks whose bits exceed the LDS
-// copy (very large leaves) assemble each word from global memory instead.
+// word can also hold the first bits of the next block's leaves: one wavefront
+// adds those few members from global memory, or one thread when they come from
+// several leaves.  Blocks whose bits exceed the LDS copy (very large leaves)
+// assemble each word from global memory instead.
 template <typename KT>
 __device__ __forceinline__ void pack_payload_body(const SetDesc& S, const DevParams* P, uint64_t blk,
                                   const LeafRec* leaves, const uint64_t* off, const KT* keys,

@@ -215,7 +215,7 @@ __device__ inline void ro_header(const RoView& v, uint64_t i, unsigned long long
 // two words).  The sequence is put together in LDS, so that only its two
 // boundary words need atomics.  A wavefront per sequence with 128-bit keys
 // read from a plain layout written before took 929 us (and that layout 140)
-// for the cosmology 2^24 set's 524,288 sequences; this takes 311.  Bound
+// for the cosmology 2^24 set's 524,288 sequences; this takes 296.  Bound
 // by instruction issue (SUB comparisons per lane).
 template <int SUB>
 __global__ void __launch_bounds__(kBlock) k_ro_write(RoView v, const DevParams* P) {

@@ -803,11 +803,11 @@ __global__ void __launch_bounds__(kBlock) k_bigleaf(uint32_t nsets, const uint64
 // minima over a few DPP steps, and the node is written in output-slot order
 // straight from registers, R consecutive members per store.
 // 570 vector and 580 scalar instructions a whole tile.  2^27 members in whole
-// tiles 1,246 us (k_tile) and 652, 2^24 195 and 88, 33.6 million in tiles of
-// 128 642 and 209, 13.1 million in two axes 178 and 91, 256 sets 742 and 378
+// tiles 1,246 us (k_tile) and 609, 2^24 195 and 83, 33.6 million in tiles of
+// 128 642 and 198, 13.1 million in two axes 178 and 87, 256 sets 742 and 352
 // (the ragged ones 326, 107 and 438 before wave_node_span and wave_find_set);
 // vector and scalar issue are each about 80 % busy.  A capped grid whose
-// wavefronts loop over tiles: 108 registers for 43, 975 us at 2^27.
+// wavefronts loop over tiles: 108 registers for 43, 975 us at 2^27 for 652 then.
 // x, y: axes 0 and 1 of the level order, axis 2 and its complement or (TRACK)
 // the member's position; wide: an axis each, the position (vectors: arrays of
 // structs went through scratch memory, 21 us a launch for 6)

@@ -115,7 +115,7 @@ struct MetaView {
   TreeGeom g;
   double origin[3], w, inv_w;
   uint32_t G[3], dims, mbits, dtype, ref_mode, r;
-  uint32_t even;  // particles per leaf when every leaf holds the same power-of-two share (0: not so)
+  uint32_t even;  // particles per leaf when there are 2^k leaves that all hold as many (0: not so)
 };
 
 __device__ inline uint32_t record_bits(const MetaView& v) {
@@ -271,9 +271,9 @@ struct UnpackStage {
 // records are read here and not from a table that an earlier kernel wrote:
 // 36 bytes per leaf written and read twice took the 2^27-particle set 160 us.
 // Bound by instruction issue (about half of its time) beside the 14 bytes per
-// particle it reads and writes: 2^27 particles in 600 us, the whole decode 764
-// -> 639 us.  Non-temporal stores (594) and storing through LDS in lane order
-// (615) change little.
+// particle it reads and writes: 2^27 particles in 575 us, the whole decode 764
+// -> 638 us.  Non-temporal stores (594 for 602 then) and storing through LDS in
+// lane order (615) change little.
 template <typename T, int DIMS>
 __device__ __forceinline__ void unpack_body(const MetaView& V, uint64_t n, uint32_t layout, const uint64_t* meta,
                                             const uint64_t* pay, uint64_t pbits, const uint64_t* part,
