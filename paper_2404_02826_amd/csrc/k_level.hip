@@ -1996,8 +1996,8 @@ __device__ __forceinline__ void reg_fence(RegRun<T, R>& q) {
 // last, keep their slots and are never written back.  Element loads and
 // stores, before, made nodes off a 16-byte boundary cost 2-3 times as much
 // (all nodes but those of power-of-two sets): the three pairs of the 2-D set
-// of 13,077,313 took 512 us and take 200, those of 33,554,467 FP64 particles
-// 1,719 and 834.  What bounds the pass is instruction issue and, for W = 16,
+// of 13,077,313 took 512 us and take 196, those of 33,554,467 FP64 particles
+// 1,719 and 788.  What bounds the pass is instruction issue and, for W = 16,
 // its barriers.  A node too large for off + s slots -- only just below the
 // capacity -- keeps off = 0 and single loads.
 template <typename KT, bool TRACK, int W, bool FULL>
@@ -2224,7 +2224,7 @@ __device__ __forceinline__ void level_fused_node(uint32_t depth, const SetDesc& 
 
 // FULL: nodes of exactly W kFuseNode members that start on a 16-byte boundary
 // (power-of-two sets) take a body without the slots around the node (fluid
-// 2^27: the three pairs 1.40 ms against 1.54 in the general body).
+// 2^27: the three pairs 1.40 ms against 1.54 in the general body, 1.33 now).
 template <typename KT, bool TRACK, int W>
 __device__ __forceinline__ void level_fused_body(uint32_t depth, const SetDesc& S, DevParams* P,
                                                  uint64_t j, uint8_t* keys, uint32_t* idx,

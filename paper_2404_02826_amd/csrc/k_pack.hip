@@ -674,7 +674,7 @@ __global__ void __launch_bounds__(kBlock) k_pack_payload(uint32_t nsets, const u
 // Both in one launch, for few payload blocks (up to kPackOnce): a launch
 // costs such sets more than the payload's LDS takes from the meta words'
 // occupancy.  With more blocks that is the other way round (fluid 2^27: 633
-// us in one launch, 478 + 77 in two).
+// us in one launch for 478 + 77 in two, which are 434 + 58 now).
 constexpr uint64_t kPackOnce = 2048;
 __global__ void __launch_bounds__(kBlock) k_pack(uint32_t nsets, const uint64_t* pre_pp, uint64_t g_pp,
                                                  const uint64_t* pre_pm, uint64_t g_pm, const SetDesc* sets,
