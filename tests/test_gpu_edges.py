@@ -6,7 +6,8 @@ import numpy as np
 import pytest
 
 import props
-from oracle import Oracle, OracleError
+from oracle import Oracle
+from oracle import OracleError
 from test_gpu_parity import check_parity, gen
 
 torch = pytest.importorskip("torch")
